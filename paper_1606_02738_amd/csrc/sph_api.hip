@@ -162,7 +162,7 @@ sph_status sph_create(const sph_params* params, void* workspace, size_t bytes, v
     c->stream = (hipStream_t)hip_stream;
     sph_status s = SPH_OK;
     if (s == SPH_OK) s = buf_ensure(c->flags, FI_NFLAGS * sizeof(int));
-    if (s == SPH_OK) s = buf_ensure(c->counters, CNT_ALLOC * 8);
+    if (s == SPH_OK) s = buf_ensure(c->counters, CNT_TOTAL * 8);
     if (s == SPH_OK) s = buf_ensure(c->dparam, 8 * sizeof(double));
     if (s == SPH_OK && hipMemsetAsync(c->dparam.p, 0, 8 * sizeof(double), c->stream) != hipSuccess) s = SPH_ERR_HIP;
     if (s == SPH_OK) s = buf_ensure(c->dom_d, (size_t)p.n_domains * sizeof(DomainInfo));
@@ -185,7 +185,7 @@ sph_status sph_create(const sph_params* params, void* workspace, size_t bytes, v
         }
     }
     if (s == SPH_OK && hipMemsetAsync(c->flags.p, 0, FI_NFLAGS * sizeof(int), c->stream) != hipSuccess) s = SPH_ERR_HIP;
-    if (s == SPH_OK && hipMemsetAsync(c->counters.p, 0, CNT_ALLOC * 8, c->stream) != hipSuccess) s = SPH_ERR_HIP;
+    if (s == SPH_OK && hipMemsetAsync(c->counters.p, 0, CNT_TOTAL * 8, c->stream) != hipSuccess) s = SPH_ERR_HIP;
     if (s != SPH_OK) {
         sph_destroy(c);
         return s;

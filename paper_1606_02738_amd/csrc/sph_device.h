@@ -199,6 +199,18 @@ __device__ inline int mask_rank(unsigned long long mask, int lane)
     return __popcll(mask & lt);
 }
 
+// Add v to a partial count (PART_*) of the workgroup's line.
+__device__ inline void count_add(unsigned long long* counters, int what, unsigned long long v)
+{
+    atomicAdd(&counters[CNT_PART + (blockIdx.x & (PART_N - 1)) * PART_STRIDE + what], v);
+}
+
+__device__ inline unsigned long long wave_sum(unsigned long long v)
+{
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    return v;
+}
+
 // Neighbour-entry batch of one wave, in LDS.
 template <typename T, int NE = 64>
 struct EBatch {
@@ -298,10 +310,10 @@ __device__ inline int load_batch(const ListEntry* list, int eb, int nbt, int lan
 // and otherwise updates H inside the particle's bracket.  hlA: the largest H
 // the particle's neighbour list covers (beyond it the list must be rebuilt);
 // hlim: a third of the box edge; s0min: the smallest top-cell edge.
-// Returns true if the particle is left unconverged.
+// Returns true if the particle is left unconverged; conv: it is converged.
 template <bool EXTRAP>
 __device__ inline bool dens_newton(const DensArgs& a, int i, double H, double Sw, double Sd, double S2, int cnt,
-                                   double hlA, double hlim, double s0min)
+                                   double hlA, double hlim, double s0min, bool& conv)
 {
     const double rho = INV_PI_8 / (H * H * H) * Sw;
     const double drho = -INV_PI_8 / (H * H * H * H) * Sd;
@@ -372,11 +384,22 @@ __device__ inline bool dens_newton(const DensArgs& a, int i, double H, double Sw
             }
         }
     }
-    if (done) {
-        a.conv[i] = 1;
-        atomicAdd(&a.counters[CNT_NDENS], (unsigned long long)cnt);
-    }
+    if (done) a.conv[i] = 1;
+    conv = done;
     return left;
+}
+
+// Counts of one wave's particles after their Newton step: interactions
+// evaluated by the sweep, interactions of the converged particles, particles left.
+__device__ inline void dens_count(const DensArgs& a, bool act, bool left, bool conv, int cnt, int lane)
+{
+    const unsigned long long ev = wave_sum(act ? (unsigned long long)cnt : 0ull);
+    const unsigned long long lm = __ballot(left);
+    const unsigned long long nd = __ballot(act && !conv) ? wave_sum(conv ? (unsigned long long)cnt : 0ull) : ev;
+    if (lane != 0) return;
+    if (ev) count_add(a.counters, PART_DEVAL, ev);
+    if (nd) count_add(a.counters, PART_NDENS, nd);
+    if (lm) count_add(a.counters, PART_UNCONV, (unsigned long long)__popcll(lm));
 }
 
 // Sums of one sweep -> rho, d rho/dH, neighbour count, and the FP64 Newton
@@ -396,14 +419,10 @@ __device__ inline bool dens_finish(const DensArgs& a, int i, bool act, int jg, i
         if (EXTRAP) S2 += __shfl_xor(S2, off);
         cnt += __shfl_xor(cnt, off);
     }
-    {
-        // interactions evaluated by this sweep (lanes of group 0 hold the totals)
-        unsigned long long ev = (jg == 0 && act) ? (unsigned long long)cnt : 0ull;
-        for (int off = 32; off > 0; off >>= 1) ev += __shfl_xor(ev, off);
-        if (lane == 0 && ev) atomicAdd(&a.counters[CNT_DEVAL], ev);
-    }
-    if (jg == 0 && act) return dens_newton<EXTRAP>(a, i, Hd, Sw, Sd, S2, cnt, hlA, hlim, s0min);
-    return false;
+    bool left = false, conv = false;
+    if (jg == 0 && act) left = dens_newton<EXTRAP>(a, i, Hd, Sw, Sd, S2, cnt, hlA, hlim, s0min, conv);
+    dens_count(a, jg == 0 && act, left, conv, cnt, lane);
+    return left;
 }
 
 // Neighbour-entry batch with each cell's box (at the build, A's frame,

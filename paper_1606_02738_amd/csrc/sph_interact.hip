@@ -181,7 +181,6 @@ __device__ void density_leaf_packed(const DensArgs& a, int A, PTile<T, NE>& L, i
     if (ncand > 0) run_tile(ncand);
     const bool left = dens_finish<T>(a, i, act, 0, 64, Hd, sw.total(), sd.total(), (double)s2, cnt, hlA, hlim, s0min);
     const unsigned long long lm = __ballot(left);
-    if (lm && lane == 0) atomicAdd(&a.counters[CNT_UNCONV], (unsigned long long)__popcll(lm));
     if (lane == 0) a.l_active[A] = lm ? 1 : 0;
 }
 
@@ -341,10 +340,7 @@ __device__ void density_leaf(const DensArgs& a, int A, DTile<T>& L, int lane)
         const bool left = dens_finish<T>(a, i, act, jg, CI, Hd, sw.total(), sd.total(), (double)s2, cnt, hlA, hlim,
                                          s0min);
         const unsigned long long lm = __ballot(left);
-        if (lm) {
-            any_left = true;
-            if (lane == 0) atomicAdd(&a.counters[CNT_UNCONV], (unsigned long long)__popcll(lm));
-        }
+        if (lm) any_left = true;
     }
     if (lane == 0) a.l_active[A] = any_left ? 1 : 0;
 }
@@ -858,12 +854,10 @@ __device__ void force_leaf(const ForceArgs& a, int A, FTile<T>& tl, int lane)
             ndens_w += nni;
         }
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        npairs += __shfl_xor(npairs, off);
-        ndens_w += __shfl_xor(ndens_w, off);
-    }
-    if (lane == 0 && npairs) atomicAdd(&a.counters[CNT_NFORCE], npairs);
-    if (lane == 0 && ndens_w) atomicAdd(&a.counters[CNT_NDENS_F], ndens_w);
+    npairs = wave_sum(npairs);
+    ndens_w = wave_sum(ndens_w);
+    if (lane == 0 && npairs) count_add(a.counters, PART_NFORCE, npairs);
+    if (lane == 0 && ndens_w) count_add(a.counters, PART_NDENS_F, ndens_w);
 }
 
 template <typename T, bool COMP, int PRUNE>
@@ -1103,12 +1097,10 @@ __device__ void force_leaf_gather(const ForceArgs& a, int A, GTile<T, NE>& L, in
         }
         wave_sync();
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        npairs += __shfl_xor(npairs, off);
-        ndens_w += __shfl_xor(ndens_w, off);
-    }
-    if (lane == 0 && npairs) atomicAdd(&a.counters[CNT_NFORCE], npairs);
-    if (lane == 0 && ndens_w) atomicAdd(&a.counters[CNT_NDENS_F], ndens_w);
+    npairs = wave_sum(npairs);
+    ndens_w = wave_sum(ndens_w);
+    if (lane == 0 && npairs) count_add(a.counters, PART_NFORCE, npairs);
+    if (lane == 0 && ndens_w) count_add(a.counters, PART_NDENS_F, ndens_w);
 }
 
 template <typename T, bool COMP, int WPE, int NE>
@@ -1258,6 +1250,29 @@ __global__ __launch_bounds__(256) void k_sums_final(const double* __restrict__ p
     }
     if (tid < 5) out[5 * d + tid] = red[tid][0];
 }
+
+// Move the partial counts of the last interaction kernel into the counters
+// (one workgroup of PART_N threads).
+__device__ inline void fold_counts(unsigned long long* cnt)
+{
+    __shared__ unsigned long long red[PART_USED][PART_N / 64];
+    const int tid = threadIdx.x;
+    unsigned long long* line = cnt + CNT_PART + tid * PART_STRIDE;
+    for (int k = 0; k < PART_USED; k++) {
+        const unsigned long long v = line[k];
+        if (v) line[k] = 0ull;
+        const unsigned long long t = wave_sum(v);
+        if ((tid & 63) == 0) red[k][tid >> 6] = t;
+    }
+    __syncthreads();
+    const int to[PART_USED] = {CNT_UNCONV, CNT_NDENS, CNT_DEVAL, CNT_NFORCE, CNT_NDENS_F};
+    if (tid == 0)
+        for (int k = 0; k < PART_USED; k++)
+            for (int w = 0; w < PART_N / 64; w++) cnt[to[k]] += red[k][w];
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(PART_N) void k_count_fold(unsigned long long* cnt) { fold_counts(cnt); }
 
 // ---------------------------------------------------------------------------
 // Host orchestration
@@ -1469,6 +1484,8 @@ static sph_status density_loop(sph_ctx* c, int done_sweeps, unsigned long long u
         SPH_CHECK_HIP(hipEventRecord(c->kev[0], c->stream));
         SPH_TRY(launch_density(c, nullptr));
         SPH_CHECK_HIP(hipEventRecord(c->kev[1], c->stream));
+        k_count_fold<<<1, PART_N, 0, c->stream>>>(cnt);
+        SPH_CHECK_LAUNCH();
         unsigned long long hc[CNT_N];
         SPH_CHECK_HIP(hipMemcpyAsync(hc, cnt, sizeof(hc), hipMemcpyDeviceToHost, c->stream));
         SPH_CHECK_HIP(hipMemcpyAsync(&fl, flags, sizeof(int), hipMemcpyDeviceToHost, c->stream));
@@ -1569,7 +1586,7 @@ sph_status density_all(sph_ctx* c)
     for (int k = 0; k < sweeps; k++) {
         k_sweep_begin<<<1, 64, 0, c->stream>>>(cnt, flags, gate);
         SPH_TRY(launch_density(c, gate));
-        k_sweep_end<<<1, 64, 0, c->stream>>>(cnt, flags, gate);
+        k_sweep_end<<<1, PART_N, 0, c->stream>>>(cnt, flags, gate);
         SPH_CHECK_LAUNCH();
     }
     SPH_CHECK_HIP(hipEventRecord(c->kev[1], c->stream));
@@ -1730,10 +1747,12 @@ static sph_status launch_force(sph_ctx* c, const int* gate, bool graph = false)
 
 // Running totals of the interaction counters (device, no host round trip):
 // the force stage's N_force (ordered, as counted) and N_dens are added to
-// CNT_NFORCE_SUM / CNT_NDENS_SUM after every force launch.
-__global__ void k_count_totals(unsigned long long* cnt, const int* gate)
+// CNT_NFORCE_SUM / CNT_NDENS_SUM after every force launch, which leaves its
+// counts in the partial lines.
+__global__ __launch_bounds__(PART_N) void k_count_totals(unsigned long long* cnt, const int* gate)
 {
     if (gate && *gate != 1) return;
+    fold_counts(cnt);
     if (threadIdx.x == 0 && blockIdx.x == 0) {
         cnt[CNT_NFORCE_SUM] += cnt[CNT_NFORCE];
         cnt[CNT_NDENS_SUM] += cnt[CNT_NDENS_F];
@@ -1760,7 +1779,7 @@ sph_status force_all(sph_ctx* c)
     SPH_CHECK_HIP(hipEventRecord(c->kev[2], c->stream));
     SPH_TRY(launch_force(c, nullptr));
     SPH_CHECK_HIP(hipEventRecord(c->kev[3], c->stream));
-    k_count_totals<<<1, 64, 0, c->stream>>>(cnt, nullptr);
+    k_count_totals<<<1, PART_N, 0, c->stream>>>(cnt, nullptr);
     SPH_CHECK_LAUNCH();
     SPH_CHECK_HIP(hipEventRecord(c->ev[5], c->stream));
     c->force_pending = true;
@@ -1806,9 +1825,11 @@ __global__ void k_sweep_begin(unsigned long long* cnt, int* flags, const int* ga
 }
 
 // same decision order as the host loop: box limit, converged, rebuild/relist
-__global__ void k_sweep_end(unsigned long long* cnt, const int* flags, int* gate)
+__global__ __launch_bounds__(PART_N) void k_sweep_end(unsigned long long* cnt, const int* flags, int* gate)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0 && *gate == 0) {
+    if (*gate != 0) return;
+    fold_counts(cnt);
+    if (threadIdx.x == 0) {
         const int f = flags[FI_FLAGS];
         const unsigned long long k = cnt[CNT_GSWEEPS];
         if (k >= 1 && k <= CNT_N - CNT_UHIST) cnt[CNT_UHIST + k - 1] = cnt[CNT_UNCONV];
@@ -1910,13 +1931,13 @@ static sph_status capture_dgf(sph_ctx* c, const double* u, const double* vx, con
     for (int k = 0; k < sweeps && st == SPH_OK; k++) {
         k_sweep_begin<<<1, 64, 0, c->stream>>>(cnt, flags, gate);
         st = launch_density(c, gate, true);
-        k_sweep_end<<<1, 64, 0, c->stream>>>(cnt, flags, gate);
+        k_sweep_end<<<1, PART_N, 0, c->stream>>>(cnt, flags, gate);
     }
     if (st == SPH_OK) st = launch_ghost(c, u, vx, vy, vz, gate);
     k_force_zero<<<blocks_for(c->n, 256), 256, 0, c->stream>>>(c->n, c->P.ax, c->P.ay, c->P.az, c->P.dudt, c->P.nngb,
                                                               cnt, gate);
     if (st == SPH_OK) st = launch_force(c, gate, true);
-    k_count_totals<<<1, 64, 0, c->stream>>>(cnt, gate);
+    k_count_totals<<<1, PART_N, 0, c->stream>>>(cnt, gate);
     hipGraph_t g = nullptr;
     const hipError_t e = hipStreamEndCapture(c->stream, &g);
     c->stream = user;

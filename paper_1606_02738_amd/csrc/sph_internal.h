@@ -137,6 +137,14 @@ enum { XQ_N = 8, XQ_STRIDE = 16, XQ_FORCE = CNT_N };
 enum { CNT_STALE_MOVED = CNT_N + XQ_N * XQ_STRIDE, CNT_STALE_GROWN,
        // running totals of the force stage's counts since sph_create
        CNT_NFORCE_SUM, CNT_NDENS_SUM, CNT_FORCE_CALLS, CNT_ALLOC };
+// Partial counts of the interaction kernels: a workgroup adds to one of
+// PART_N lines of 128 bytes and fold_counts moves them into the counters
+// above.  With every leaf adding to the counters themselves, all additions
+// met on one line and bounded the kernels: density stage 3.9 -> 2.6 ms at
+// 127^3 clustered, 1.63 -> 0.90 ms for the 1.1M-particle shock tube, 10.1 ->
+// 9.3 ms at 256^3.
+enum { PART_N = 256, PART_STRIDE = 16, CNT_PART = (CNT_ALLOC + 15) / 16 * 16, CNT_TOTAL = CNT_PART + PART_N * PART_STRIDE };
+enum { PART_UNCONV = 0, PART_NDENS, PART_DEVAL, PART_NFORCE, PART_NDENS_F, PART_USED };
 
 // Leaf arrays (device SoA).
 struct LeafArrays {

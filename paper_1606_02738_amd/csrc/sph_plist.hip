@@ -733,12 +733,7 @@ __global__ __launch_bounds__(64) void k_density_chunks(DensChunkArgs la)
             }
         });
     }
-    {
-        unsigned long long ev = act ? (unsigned long long)cnt : 0ull;
-        for (int off = 32; off > 0; off >>= 1) ev += __shfl_xor(ev, off);
-        if (lane == 0 && ev) atomicAdd(&a.counters[CNT_DEVAL], ev);
-    }
-    bool left = false;
+    bool left = false, conv = false;
     if (act) {
         const double hlim = fmin(fmin(I.L[0], I.L[1]), I.L[2]) / 3.0;
         // the top cells cover the list radii plus twice the box's largest skin
@@ -746,10 +741,9 @@ __global__ __launch_bounds__(64) void k_density_chunks(DensChunkArgs la)
         // the list holds every neighbour within R_i while the particles stay
         // within their skins (checked at every drift)
         const double hlA = (double)((const T*)la.R)[i];
-        left = dens_newton<EXTRAP>(a, i, Hd, sw.total(), sd.total(), (double)s2, cnt, hlA, hlim, s0min);
+        left = dens_newton<EXTRAP>(a, i, Hd, sw.total(), sd.total(), (double)s2, cnt, hlA, hlim, s0min, conv);
     }
-    const unsigned long long lm = __ballot(left);
-    if (lm && lane == 0) atomicAdd(&a.counters[CNT_UNCONV], (unsigned long long)__popcll(lm));
+    dens_count(a, act, left, conv, cnt, lane);
 }
 
 // Force over the chunk lists, eqs. (dvdt) and (dudt): each particle sums its
@@ -875,12 +869,10 @@ __global__ __launch_bounds__(64) void k_force_chunks(ForceChunkArgs a)
         np = (unsigned long long)nmax;
         nd_w = (unsigned long long)nni;
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        np += __shfl_xor(np, off);
-        nd_w += __shfl_xor(nd_w, off);
-    }
-    if (lane == 0 && np) atomicAdd(&a.counters[CNT_NFORCE], np);
-    if (lane == 0 && nd_w) atomicAdd(&a.counters[CNT_NDENS_F], nd_w);
+    np = wave_sum(np);
+    nd_w = wave_sum(nd_w);
+    if (lane == 0 && np) count_add(a.counters, PART_NFORCE, np);
+    if (lane == 0 && nd_w) count_add(a.counters, PART_NDENS_F, nd_w);
 }
 
 // ---------------------------------------------------------------------------
