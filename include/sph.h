@@ -129,11 +129,14 @@ typedef struct {
                             or 1024 (0: 1024 for the density and 512 for the force; FP64
                             at most 512 / 256) */
     int waves_density;   /* cell lists, FP32 modes: occupancy target (waves per SIMD) the
-                            packed density kernel is compiled for, 4, 5, 6 or 8 (0: 6) */
-    int waves_force;     /* the same for the gather force kernel, 4, 5, 6 or 8 (0: 5) */
+                            packed density kernel is compiled for, 4, 5, 6 or 8 (0: 6; 8
+                            runs the kernel of 6) */
+    int waves_force;     /* the same for the gather force kernel, 4, 5, 6 or 8 (0: 4; its
+                            LDS holds 4 waves, which every choice runs) */
     int batch;           /* cell lists, FP32 modes: neighbour-cell entries staged per batch
-                            by those two kernels, 16 or 32 (0: 32).  These three only tune
-                            speed: every choice gives the same results bit for bit */
+                            by those two kernels, 16 or 32 (both run the kernel of 32).
+                            These three only tune speed: every choice gives the same
+                            results bit for bit */
     const double* boxes; /* HOST pointer, n_domains x 3 box edge lengths; copied */
 } sph_params;
 

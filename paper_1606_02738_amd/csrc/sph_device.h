@@ -38,6 +38,17 @@ __device__ inline T spline_d2(T q, T dw)
     return q * (q * d2 + T(2) * dw);
 }
 
+// -w'(q) / 6, zero from q = 1 on (1 - q clamped to [0, 1])
+__device__ inline float clamp01(float x) { return __builtin_amdgcn_fmed3f(x, 0.0f, 1.0f); }
+__device__ inline double clamp01(double x) { return fmin(fmax(x, 0.0), 1.0); }
+template <typename T>
+__device__ inline T spline_dw6(T q)
+{
+    const T t = clamp01(T(1) - q);
+    const T vi = q * (T(2) - T(3) * q), vo = t * t;  // both pieces, then a select
+    return (q <= T(0.5)) ? vi : vo;
+}
+
 template <typename T>
 __device__ inline T spline_dw(T q)
 {
@@ -90,16 +101,16 @@ __device__ inline float wave_maxf(float v)
     for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
     return v;
 }
-// Wave-uniform pop from a device task counter.  Every lane takes part in the
-// atomic (lane 0 adds 1, the others 0) and the result is read from the first
-// lane into a scalar register, so loops that exit on it have a uniform exit
-// condition.  (A pop made by lane 0 alone inside `if (lane == 0)` lets the
-// compiler treat the loop exit as divergent and run the other lanes on
-// without lane 0.)
+// Wave-uniform pop from a device task counter: one atomic by lane 0, its
+// result read from the first lane into a scalar register by all lanes, so
+// loops that exit on it have a uniform exit condition.  (With every lane in
+// the atomic, the compiler sums the lanes' operands in a loop over the wave:
+// 64 rounds a pop.)
 __device__ inline int wave_pop(unsigned long long* counter, int lane)
 {
-    const unsigned long long v = atomicAdd(counter, (unsigned long long)(lane == 0 ? 1 : 0));
-    return __builtin_amdgcn_readfirstlane((int)v);
+    int v = 0;
+    if (lane == 0) v = (int)atomicAdd(counter, 1ull);
+    return __builtin_amdgcn_readfirstlane(v);
 }
 
 __device__ inline int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -126,9 +137,6 @@ __device__ inline int xq_pop(unsigned long long* q, int nL, int& k, int lane)
     }
     return -1;
 }
-
-// v_writelane_b32: replace lane `lane` of `old` by the wave-uniform `src`
-__device__ int amdgcn_writelane(int src, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
 
 __device__ inline void wave_sync()
 {
@@ -425,21 +433,68 @@ __device__ inline bool dens_finish(const DensArgs& a, int i, bool act, int jg, i
     return left;
 }
 
-// Neighbour-entry batch with each cell's box (at the build, A's frame,
-// grown by `grow`), for the packed density path.
-template <typename T, int NE>
-struct EBatchBox {
-    int b[NE], n[NE];
-    T ox[NE], oy[NE], oz[NE];
-    T lo[3][NE], hi[3][NE];
-    T hl[NE];  // list radius of the cell (bounds its particles' H)
-};
+// ---------------------------------------------------------------------------
+// Pair selection and pair-parallel evaluation, shared by the density and the
+// gather force kernels (one wave per leaf A, lane = particle i of A).
+//
+// Candidates.  The particles of a batch of neighbour cells form one stream
+// (EFlat: prefix sums of the cells' counts), read 64 per step whatever the
+// cells hold, so no lane idles on cells of fewer than 64 particles; the
+// next step's positions are loaded while this one is tested.  Those within
+// reach of the leaf's box are packed into a tile of 4 ROW candidates in LDS (ROW of
+// them for each 16-lane row of the masks).
+//
+// Range tests (tile_masks).  All 4 ROW x 64 tests of a full tile run on the
+// matrix units: r^2 - H_i^2 = -2 p_j.p_i + |p_j|^2 + (|p_i|^2 - H_i^2) is a
+// product over K = 4 (x, y, z, 1) plus a row constant, one
+// v_mfma_f32_16x16x4_f32 per 16 x 16 tests, and the sign bits are the mask
+// (one v_alignbit per 64 tests instead of the ~11 instructions of a
+// per-particle loop with a ballot).  The expanded form rounds relative to
+// |p|^2, so every constant is shifted by PAIR_EPS towards "in range": with
+// at most 8 roundings of 2^-23 of a sum bounded by 2(|p_i|^2 + |p_j|^2) +
+// H^2 and coordinates rounded to FP32, the shift is at least four times the
+// error.  No pair is lost; the few that are let in wrongly contribute
+// exact zeros below (q >= 1).
+// Coordinates and smoothing lengths are scaled by a power of two (exact) to
+// order 1, so nothing over- or underflows that did not before; the sums only
+// hold r / H and unit vectors, which the scale leaves as they are.
+//
+// Evaluation.  The set bits become a list of (i, j) pairs ordered by i and
+// every lane takes an equal run of it, so all lanes work on pairs in range:
+// with lane = particle the same work took as many rounds as the fullest
+// particle of each tile has neighbours (18% of the lanes active at 256^3
+// clustered).  A lane sums in FP64 (v_add_f64 runs at the FP32 rate, a
+// compensated FP32 addition takes four) and adds its sum to the particle's
+// LDS accumulator where the run passes from one particle to the next.
+// ---------------------------------------------------------------------------
+#define PAIR_CAP 512  // pairs listed at a time (a tile usually has ~300)
+#define PAIR_EPS 3.8146973e-6f  // 2^-18
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Batch of up to NE neighbour cells as one stream of candidates.
+template <typename T, int NE>
+struct EFlat {
+    typename vec4<T>::type o[NE];  // origin(B) + periodic shift - origin(A), scaled; w: first particle minus start
+    int st[NE];                    // start of the cell in the stream
+};
+__device__ inline float pack_int(int v, float) { return __int_as_float(v); }
+__device__ inline double pack_int(int v, double) { return (double)v; }
+__device__ inline int unpack_int(float v) { return __float_as_int(v); }
+__device__ inline int unpack_int(double v) { return (int)v; }
+
+__device__ inline int lane_rank(unsigned long long mask)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+// Load the entries [eb, eb + nbt) of A's list that pass keep(E) into the
+// batch; returns the particles they hold in all.  start: the lane's cell's
+// first position in the stream (INT_MAX past the last cell).
 template <typename T, typename Keep, int NE>
-__device__ inline int load_batch_box(const ListEntry* list, int eb, int nbt, int lane, const int* l_begin,
-                                     const int* l_count, const double* l_origin, const double* l_lo, const double* l_hi,
-                                     const double* l_hlist, const double* oA, const DomainInfo& I, double grow, Keep keep,
-                                     EBatchBox<T, NE>& E)
+__device__ inline int load_batch_flat(const ListEntry* list, int eb, int nbt, int lane, const int* l_begin,
+                                      const int* l_count, const double* l_origin, const double* oA,
+                                      const DomainInfo& I, T sc, Keep keep, EFlat<T, NE>& E, int& start)
 {
     bool ok = false;
     ListEntry en;
@@ -448,24 +503,178 @@ __device__ inline int load_batch_box(const ListEntry* list, int eb, int nbt, int
         ok = keep(en);
     }
     const unsigned long long mask = __ballot(ok);
+    const int n = ok ? l_count[en.B] : 0;
+    int incl = n;
+    for (int off = 1; off < NE; off <<= 1) {
+        const int t = __shfl_up(incl, off);
+        if (lane >= off) incl += t;
+    }
     if (ok) {
-        const int s = mask_rank(mask, lane);
-        const int B = en.B;
+        const int s = lane_rank(mask);
         double sv[3];
         shift_vec(en.code, I, sv);
-        E.b[s] = l_begin[B];
-        E.n[s] = l_count[B];
-        E.ox[s] = (T)(l_origin[3 * B] + sv[0] - oA[0]);
-        E.oy[s] = (T)(l_origin[3 * B + 1] + sv[1] - oA[1]);
-        E.oz[s] = (T)(l_origin[3 * B + 2] + sv[2] - oA[2]);
-        for (int d = 0; d < 3; d++) {
-            E.lo[d][s] = (T)(l_lo[3 * B + d] + sv[d] - oA[d] - grow);
-            E.hi[d][s] = (T)(l_hi[3 * B + d] + sv[d] - oA[d] + grow);
-        }
-        E.hl[s] = (T)l_hlist[B];
+        typename vec4<T>::type o;
+        o.x = (T)(l_origin[3 * en.B] + sv[0] - oA[0]) * sc;
+        o.y = (T)(l_origin[3 * en.B + 1] + sv[1] - oA[1]) * sc;
+        o.z = (T)(l_origin[3 * en.B + 2] + sv[2] - oA[2]) * sc;
+        o.w = pack_int(l_begin[en.B] - (incl - n), T(0));
+        E.o[s] = o;
+        E.st[s] = incl - n;
     }
     wave_sync();
-    return __popcll(mask);
+    start = lane < __popcll(mask) ? E.st[lane] : 0x7fffffff;
+    return __builtin_amdgcn_readlane(incl, NE - 1);
+}
+
+// Cell (index in the batch) of the lane's candidate p0 + lane: the cells that
+// start by p0, then one more at each lane where a cell starts.
+__device__ inline int stream_cell(int p0, int start)
+{
+    const int d = start - p0;
+    const int at = (uint32_t)(d - 1) < 63u ? d << 2 : 0;
+    const unsigned long long mask = __ballot(__builtin_amdgcn_ds_permute(at, 1) != 0) >> 1;  // (lane 0 collects the rest)
+    return __popcll(__ballot(d <= 0)) - 1 + lane_rank(mask);
+}
+
+// Power of two that brings lengths up to x to order 1 (x > 0 finite).
+__device__ inline float pow2_scale(float x) { return __builtin_amdgcn_ldexpf(1.0f, -__builtin_amdgcn_frexp_expf(x)); }
+__device__ inline double pow2_scale(double x) { return __builtin_amdgcn_ldexp(1.0, -__builtin_amdgcn_frexp_exp(x)); }
+
+// Test operand of the particles i, one value per lane and block of 16
+// particles: lane l holds component l / 16 of (-2x, -2y, -2z, c) of
+// particle 16 blk + l % 16.  (x, y, z, c): the lane's own particle, scaled;
+// tmp: 64 float4 of LDS.
+__device__ inline void test_operand(float x, float y, float z, float c, float4* tmp, int lane, float b[4])
+{
+    wave_sync();
+    tmp[lane] = make_float4(-2.0f * x, -2.0f * y, -2.0f * z, c);
+    wave_sync();
+    for (int k = 0; k < 4; k++) b[k] = ((const float*)&tmp[16 * k + (lane & 15)])[lane >> 4];
+    wave_sync();
+}
+
+// In-range masks of a full tile: bit ROW - 1 - b of M[k] of lane l belongs to
+// the particle 16 k + l % 16 and the candidate 4 b + l / 16 (candidates are
+// dealt to the four rows in turn: neighbours in the stream are neighbours in
+// space, and a particle's pairs come in runs; with a row of ROW consecutive
+// candidates each, the fullest lanes had twice the pairs).  coord(j):
+// component l / 16 of candidate j (scaled; 1 for l / 16 = 3); c1, c2: row
+// constants of the tests against H_i and (TWO) H_j, candidate j's at
+// test_slot(j).
+template <int ROW>
+__device__ inline int test_slot(int j) { return (j & 3) * ROW + (j >> 2); }
+
+template <bool TWO, int ROW, int NB, typename Coord>
+__device__ inline void tile_masks_n(const float* c1, const float* c2, Coord coord, const float b1[4], const float b2[4],
+                                    int lane, uint32_t M[4])
+{
+    const int g = lane >> 4;
+#pragma unroll
+    for (int t = 0; t < ROW / 4; t++) {
+        const float a = coord(16 * t + 4 * (lane & 3) + ((lane >> 2) & 3));
+        const f32x4 r1 = *(const f32x4*)(c1 + ROW * g + 4 * t);
+        const f32x4 r2 = TWO ? *(const f32x4*)(c2 + ROW * g + 4 * t) : r1;
+        f32x4 d1[NB], d2[NB];
+#pragma unroll
+        for (int k = 0; k < NB; k++) {
+            d1[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b1[k], r1, 0, 0, 0);
+            if (TWO) d2[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b2[k], r2, 0, 0, 0);
+        }
+#pragma unroll
+        for (int k = 0; k < NB; k++)
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                uint32_t s = __float_as_uint(d1[k][r]);
+                if (TWO) s |= __float_as_uint(d2[k][r]);
+                M[k] = __builtin_amdgcn_alignbit(M[k], s, 31);
+            }
+    }
+}
+// nb: blocks of 16 particles up to the last that holds any (1..4)
+template <bool TWO, int ROW, typename Coord>
+__device__ inline void tile_masks(const float* c1, const float* c2, Coord coord, const float b1[4], const float b2[4],
+                                  int nb, int lane, uint32_t M[4])
+{
+    if (nb <= 2) tile_masks_n<TWO, ROW, 2>(c1, c2, coord, b1, b2, lane, M);
+    else if (nb == 3) tile_masks_n<TWO, ROW, 3>(c1, c2, coord, b1, b2, lane, M);
+    else tile_masks_n<TWO, ROW, 4>(c1, c2, coord, b1, b2, lane, M);
+}
+
+// Exclusive prefix sums over (particle, row of 16 lanes) of two 16-bit counts
+// packed in v; the totals in `total`.
+__device__ inline uint32_t scan_pairs(uint32_t v, int lane, uint32_t& total)
+{
+    // rows of the same particle
+    const auto h = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    uint32_t ex = (lane & 16) ? (uint32_t)h[0] : 0u;
+    const uint32_t s = (uint32_t)h[0] + (uint32_t)h[1];
+    const auto w = __builtin_amdgcn_permlane32_swap(s, s, false, false);
+    if (lane & 32) ex += (uint32_t)w[0];
+    const uint32_t own = (uint32_t)w[0] + (uint32_t)w[1];
+    // particles of the row
+    uint32_t in = own;
+    in += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)in, 0x111, 0xf, 0xf, true);
+    in += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)in, 0x112, 0xf, 0xf, true);
+    in += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)in, 0x114, 0xf, 0xf, true);
+    in += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)in, 0x118, 0xf, 0xf, true);
+    total = (uint32_t)__builtin_amdgcn_readlane((int)in, 15);
+    return in - own + ex;
+}
+
+// The pairs of the masks, PAIR_CAP at a time: listed as i << 7 | j in the order
+// of i, then eval(list, n) with n of them in the list.  ready() runs before
+// the first eval.
+template <int ROW, typename Ready, typename Eval>
+__device__ inline void for_pairs(const uint32_t M[4], uint16_t* list, int lane, Ready ready, Eval eval)
+{
+    uint32_t t01, t23;
+    const uint32_t e01 = scan_pairs((uint32_t)__popc(M[0]) | ((uint32_t)__popc(M[1]) << 16), lane, t01);
+    const uint32_t e23 = scan_pairs((uint32_t)__popc(M[2]) | ((uint32_t)__popc(M[3]) << 16), lane, t23);
+    const int n0 = (int)(t01 & 0xffffu), n1 = n0 + (int)(t01 >> 16), n2 = n1 + (int)(t23 & 0xffffu);
+    const int np = n2 + (int)(t23 >> 16);
+    const int at[4] = {(int)(e01 & 0xffffu), n0 + (int)(e01 >> 16), n1 + (int)(e23 & 0xffffu), n2 + (int)(e23 >> 16)};
+    const int code = ((lane & 15) << 7) + (lane >> 4) - 4 * (32 - ROW);
+    for (int w = 0; w < np; w += PAIR_CAP) {
+        wave_sync();
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            uint32_t m = M[k];
+            int p = at[k] - w;
+            if (np <= PAIR_CAP) {
+                while (m) {
+                    const int b = __builtin_clz(m);
+                    m ^= 0x80000000u >> b;
+                    list[p++] = (uint16_t)((k << 11) + code + 4 * b);
+                }
+            } else {
+                while (m) {
+                    const int b = __builtin_clz(m);
+                    m ^= 0x80000000u >> b;
+                    if ((uint32_t)p < (uint32_t)PAIR_CAP) list[p] = (uint16_t)((k << 11) + code + 4 * b);
+                    p++;
+                }
+            }
+        }
+        if (w == 0) ready();
+        wave_sync();
+        eval(list, min(PAIR_CAP, np - w));
+    }
+}
+
+__device__ inline float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ inline double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+__device__ inline void lds_add(double* p, double v)
+{
+    (void)__hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+__device__ inline void lds_add(float* p, float v)
+{
+    (void)__hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+__device__ inline void lds_add(int* p, int v)
+{
+    (void)__hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
 // Force sums of one particle (acceleration and du/dt).

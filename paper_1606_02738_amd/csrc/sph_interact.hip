@@ -1,6 +1,10 @@
 // Density, ghost, force and integrator stages on the leaf cells.
 //
-// Work unit: one wave (64 lanes) per leaf cell A.  Lanes hold up to 64 of
+// Work unit: one wave (64 lanes) per leaf cell A.  The density sweep of leaves of
+// up to 64 particles and the gather force pack the candidates of A's
+// neighbour cells into tiles, test them on the matrix units and evaluate the
+// pairs in range one per lane (sph_device.h).  The chunked kernels (larger
+// leaves, the sorted-axis mode, the pairs-once force): lanes hold up to 64 of
 // A's particles (i); when A holds fewer than 64 the wave is split into G
 // groups of CI = 64/G lanes and group g walks every G-th neighbour of the
 // staged tile, so all lanes stay busy.  A's neighbour-cell list gives the
@@ -18,32 +22,73 @@
 #include "sph_ctx.h"
 #include "sph_device.h"
 
-// List entries staged per batch (NE) and the occupancy target (waves per
-// SIMD, WPE) of the packed density and gather force kernels are template
-// parameters chosen per context (the autotuner's tile and wave axes); the
-// defaults are the measured best at 256^3 clustered.
+// Occupancy target (waves per SIMD, WPE) of the packed density and gather
+// force kernels, the measured best at 256^3 clustered: the density sweep takes
+// 6.8 ms at 6 waves and 7.2 at 4; the force's LDS holds 4 waves (11.0 ms, 11.1
+// with 3 waves and larger tiles, 18.1 with 5 waves and tiles of 64).
 #define SPH_DENS_WAVES 6
-#define SPH_FORCEG_WAVES 5
+#define SPH_FORCEG_WAVES 4
+#define SPH_DENS_WAVES64 3
+#define SPH_FORCEG_WAVES64 2
+// List entries staged per batch.
 #define SPH_BATCH 32
+// Candidates per 16-lane row of a tile: the largest tiles (fewest partly filled
+// rounds of pairs) whose LDS leaves the waves above resident.  Density at 32 /
+// 28 / 24 / 16: 6.8 / 7.4 / 7.6 / 7.3 ms; force at 28 / 24 / 20 / 16: 11.0 / 11.1
+// / 11.4 / 11.5 ms.
+#define DENS_ROW 32
+#define FORCE_ROW 28
 
-// Candidate buffer of the packed density path (one wave): candidates j of
-// all neighbour cells in A's frame, packed 64 at a time, and A's particles.
-template <typename T, int NE>
+// Density: tile, particles and sums of one wave.
+template <typename T>
 struct PTile {
-    typename vec4<T>::type cand[128];  // j in A's frame, w = m
-    typename vec4<T>::type si[64];     // i of A: x, y, z (A frame), H^2 (negative when inactive)
-    EBatchBox<T, NE> e;
+    typename vec4<T>::type cand[4 * DENS_ROW];  // j in A's frame, w = m
+    union {
+        float c1[4 * DENS_ROW];                 // row constants of the range tests
+        uint16_t list[PAIR_CAP];        // then the pairs
+    };
+    typename vec4<T>::type si[64];      // i of A: x, y, z (A frame), 1/H
+    double sw[64], sd[64];              // sums of the particles
+    T s2[64];
+    int cnt[64];
+    EFlat<T, SPH_BATCH> e;
 };
+// FP64: the tests' coordinates in FP32
+struct PTile64 : PTile<double> {
+    float4 fc[4 * DENS_ROW];
+};
+template <typename T> struct ptile { typedef PTile<T> type; };
+template <> struct ptile<double> { typedef PTile64 type; };
 
-// Density sweep of one leaf (at most 64 particles, box pruning).  The
-// candidates of every neighbour cell that pass the box test are packed into
-// full tiles of 64; per tile, phase 1 runs j-major (lane = candidate, a
-// uniform loop over A's active particles, one ballot per particle gives
-// that particle's in-range mask) and phase 2 i-major (lane = particle,
-// evaluating only the set bits).  Phase 1 keeps every lane busy whatever
-// the leaf's occupancy.
-template <typename T, bool COMP, int NE>
-__device__ void density_leaf_packed(const DensArgs& a, int A, PTile<T, NE>& L, int lane)
+// Candidate j of the tile for the range tests (the FP64 tile keeps an FP32
+// copy of the coordinates; the FP32 tile is read as it is); returns |p|^2.
+template <typename T, typename Tile>
+__device__ inline float put_test(Tile& L, int j, T x, T y, T z)
+{
+    const float fx = (float)x, fy = (float)y, fz = (float)z;
+    if constexpr (sizeof(T) == 8) L.fc[j] = make_float4(fx, fy, fz, 1.0f);
+    return fx * fx + fy * fy + fz * fz;
+}
+template <typename T, typename Tile>
+__device__ inline float get_test(const Tile& L, int j, int lane)
+{
+    if constexpr (sizeof(T) == 8) {
+        return ((const float*)&L.fc[j])[lane >> 4];
+    } else {
+        const float v = ((const float*)&L.cand[j])[lane >> 4];
+        return lane < 48 ? v : 1.0f;
+    }
+}
+
+// Density sweep of one leaf (at most 64 particles, box pruning): candidate
+// stream, matrix-unit range tests and pair-parallel sums (sph_device.h), then
+// the FP64 Newton test.  Bound by VALU and MFMA issue, which together fill
+// every cycle (FP32 MFMA does not overlap with VALU work here): 7.4e3 VALU and
+// 208 MFMA instructions per leaf at 256^3 clustered, 2.1e4 VALU instructions
+// with a ballot loop over the particles per tile and lane = particle sums.
+// Stage at 256^3 clustered FP32C 9.3 -> 6.8 ms, at 64^3 FP64 2.6 -> 1.4 ms.
+template <typename T>
+__device__ void density_leaf_packed(const DensArgs& a, int A, typename ptile<T>::type& L, int lane)
 {
     constexpr bool EXTRAP = sizeof(T) == 4;
     typedef typename vec4<T>::type V4;
@@ -66,122 +111,131 @@ __device__ void density_leaf_packed(const DensArgs& a, int A, PTile<T, NE>& L, i
     }
     const V4 pi = pos4[i];
     const double Hd = a.H[i];
-    const T Hi = (T)Hd, H2 = Hi * Hi, invH = T(1) / Hi;
-    {
-        V4 q = pi;
-        q.w = act ? H2 : T(-1);
-        L.si[lane] = q;
-    }
-    Acc<T, COMP> sw, sd;
-    T s2 = T(0);
-    int cnt = 0;
     const double hA = wave_max(act ? Hd : 0.0);
     const T big = T(1e30);
-    const T bxl = wave_min_t<T>(act ? pi.x : big), bxh = wave_max_t<T>(act ? pi.x : -big);
-    const T byl = wave_min_t<T>(act ? pi.y : big), byh = wave_max_t<T>(act ? pi.y : -big);
-    const T bzl = wave_min_t<T>(act ? pi.z : big), bzh = wave_max_t<T>(act ? pi.z : -big);
-    const T hAm = (T)(hA * (1.0 + 1e-5));
+    T bxl = wave_min_t<T>(act ? pi.x : big), bxh = wave_max_t<T>(act ? pi.x : -big);
+    T byl = wave_min_t<T>(act ? pi.y : big), byh = wave_max_t<T>(act ? pi.y : -big);
+    T bzl = wave_min_t<T>(act ? pi.z : big), bzh = wave_max_t<T>(act ? pi.z : -big);
+    // scale: the leaf's box and its largest H are of order 1 below
+    const T sc = pow2_scale(fmax((T)hA, fmax(fmax(fmax(-bxl, bxh), fmax(-byl, byh)), fmax(-bzl, bzh))));
+    bxl *= sc, bxh *= sc, byl *= sc, byh *= sc, bzl *= sc, bzh *= sc;
+    const T hAm = (T)(hA * (1.0 + 1e-5)) * sc;
     const T hA2 = hAm * hAm;
-    auto dens_acc = [&](const V4& q4, T r2) {
-        const T q = fast_sqrt(r2) * invH;
-        T w, dw;
-        spline_w_dw(q, w, dw);
-        sw.add(q4.w * w);
-        sd.add(q4.w * (T(3) * w + q * dw));
-        if (EXTRAP) s2 += q4.w * spline_d2(q, dw);
-        cnt++;
-    };
-    // box of the buffered candidates (union of their cells' boxes)
-    T tlo[3] = {big, big, big}, thi[3] = {-big, -big, -big};
-    // both phases on the first `len` packed candidates
-    auto run_tile = [&](int len) {
-        wave_sync();
-        const V4 pj = L.cand[lane];
-        const bool lv = lane < len;
-        // particles of A farther than their H from the box of every candidate
-        // have no pair in this tile
-        const unsigned long long imask =
-            amask & __ballot(box_d2<T>(pi.x, pi.y, pi.z, tlo[0], tlo[1], tlo[2], thi[0], thi[1], thi[2]) < H2);
-        int mlo = 0, mhi = 0;
-        for (unsigned long long m = imask; m; m &= m - 1ull) {
-            const int ii = uniform(__ffsll((long long)m) - 1);
-            const V4 q = L.si[ii];
-            const T dx = pj.x - q.x, dy = pj.y - q.y, dz = pj.z - q.z;
-            const unsigned long long hm = __ballot(lv && dx * dx + dy * dy + dz * dz < q.w);
-            mlo = amdgcn_writelane((int)(uint32_t)hm, ii, mlo);
-            mhi = amdgcn_writelane((int)(uint32_t)(hm >> 32), ii, mhi);
-        }
-        if (act) {
-            unsigned long long m = ((unsigned long long)(uint32_t)mhi << 32) | (uint32_t)mlo;
-            while (m) {
-                const int s = __ffsll((long long)m) - 1;
-                m &= m - 1ull;
-                const V4 q4 = L.cand[s];
-                const T dx = q4.x - pi.x, dy = q4.y - pi.y, dz = q4.z - pi.z;
-                dens_acc(q4, dx * dx + dy * dy + dz * dz);
-            }
-        }
-        wave_sync();
-    };
-    int ncand = 0;
-    // cell boxes grow by the displacement since the build plus float rounding
-    const double grow = 0.5 * mg + 1e-5 * fmax(hlA, hA);
-    for (int eb = e0; eb < e1; eb += NE) {
-        const int nbt = min(NE, e1 - eb);
-        const int nv = load_batch_box<T>(a.list, eb, nbt, lane, a.l_begin, a.l_count, a.l_origin, a.l_lo, a.l_hi,
-                                         a.l_hlist, oA, I,
-                                         grow, [&](const ListEntry& E) { return E.dist < hA + mg; }, L.e);
-        V4 pf;  // prefetched first chunk of the next cell
-        if (nv > 0 && lane < L.e.n[0]) pf = pos4[L.e.b[0] + lane];
-        for (int k = 0; k < nv; k++) {
-            const int bB = L.e.b[k], nB = L.e.n[k];
-            const T dox = L.e.ox[k], doy = L.e.oy[k], doz = L.e.oz[k];
-            const T klo[3] = {L.e.lo[0][k], L.e.lo[1][k], L.e.lo[2][k]};
-            const T khi[3] = {L.e.hi[0][k], L.e.hi[1][k], L.e.hi[2][k]};
-            V4 cur = pf;
-            if (k + 1 < nv && lane < L.e.n[k + 1]) pf = pos4[L.e.b[k + 1] + lane];
-            for (int p0 = 0; p0 < nB; p0 += 64) {
-                const int len = min(64, nB - p0);
-                bool in = false;
-                V4 q;
-                if (lane < len) {
-                    q = p0 == 0 ? cur : pos4[bB + p0 + lane];
-                    q.x += dox;
-                    q.y += doy;
-                    q.z += doz;
-                    in = box_d2<T>(q.x, q.y, q.z, bxl, byl, bzl, bxh, byh, bzh) < hA2;
-                }
-                const unsigned long long mk = __ballot(in);
-                if (in) L.cand[ncand + mask_rank(mk, lane)] = q;
-                ncand += __popcll(mk);
-                if (mk) {
-                    for (int d = 0; d < 3; d++) {
-                        tlo[d] = fmin(tlo[d], klo[d]);
-                        thi[d] = fmax(thi[d], khi[d]);
-                    }
-                }
-                if (ncand >= 64) {
-                    run_tile(64);
-                    const int rest = ncand - 64;
-                    V4 t;
-                    if (lane < rest) t = L.cand[64 + lane];
-                    wave_sync();
-                    if (lane < rest) L.cand[lane] = t;
-                    ncand = rest;
-                    // the carried candidates all come from this cell
-                    for (int d = 0; d < 3; d++) {
-                        tlo[d] = rest ? klo[d] : big;
-                        thi[d] = rest ? khi[d] : -big;
-                    }
-                }
-            }
-        }
-        wave_sync();
+    const int nb = 4 - (__builtin_clzll(amask) >> 4);
+    float b1[4];
+    {
+        V4 q = pi;
+        q.x *= sc, q.y *= sc, q.z *= sc;
+        const float x = (float)q.x, y = (float)q.y, z = (float)q.z, h = (float)((T)Hd * sc);
+        const float p2 = x * x + y * y + z * z;
+        const bool on = act && p2 < 1e30f;
+        test_operand(on ? x : 0.f, on ? y : 0.f, on ? z : 0.f,
+                     on ? p2 * (1.0f - PAIR_EPS) - h * h * (1.0f + PAIR_EPS) - 1e-30f : 1e30f, (float4*)L.cand, lane, b1);
+        q.w = T(1) / ((T)Hd * sc);
+        L.si[lane] = q;
+        L.sw[lane] = L.sd[lane] = 0.0;
+        L.s2[lane] = T(0);
+        L.cnt[lane] = 0;
     }
-    if (ncand > 0) run_tile(ncand);
-    const bool left = dens_finish<T>(a, i, act, 0, 64, Hd, sw.total(), sd.total(), (double)s2, cnt, hlA, hlim, s0min);
+    // the sums of one run of pairs
+    auto eval = [&](const uint16_t* list, int n) {
+        const int K = (n + 63) >> 6;
+        int cur = -1, cnt = 0;
+        double sw = 0.0, sd = 0.0;
+        T s2 = T(0);
+        V4 p;
+        auto flush = [&]() {
+            lds_add(&L.sw[cur], sw);
+            lds_add(&L.sd[cur], sd);
+            if (EXTRAP) lds_add(&L.s2[cur], s2);
+            lds_add(&L.cnt[cur], cnt);
+        };
+        for (int e = lane * K; e < min(lane * K + K, n); e++) {
+            const int code = list[e], ii = code >> 7;
+            if (ii != cur) {
+                if (cur >= 0) flush();
+                cur = ii;
+                p = L.si[ii];
+                sw = sd = 0.0;
+                s2 = T(0);
+                cnt = 0;
+            }
+            const V4 c = L.cand[code & 127];
+            const T dx = c.x - p.x, dy = c.y - p.y, dz = c.z - p.z;
+            // (every term is an exact zero at q = 1)
+            const T q = fmin(fast_sqrt(dx * dx + dy * dy + dz * dz) * p.w, T(1));
+            T w, dw;
+            spline_w_dw(q, w, dw);
+            sw += (double)(c.w * w);
+            sd += (double)(c.w * (T(3) * w + q * dw));
+            if (EXTRAP) s2 += c.w * spline_d2(q, dw);
+            cnt += q < T(1);
+        }
+        if (cur >= 0) flush();
+    };
+    auto run_tile = [&](int len) {
+        for (int j = len + lane; j < 4 * DENS_ROW; j += 64) {
+            V4 o;
+            o.x = o.y = o.z = o.w = T(0);
+            L.cand[j] = o;
+            put_test<T>(L, j, T(0), T(0), T(0));
+            L.c1[test_slot<DENS_ROW>(j)] = 1e30f;
+        }
+        wave_sync();
+        uint32_t M[4] = {0u, 0u, 0u, 0u};
+        tile_masks<false, DENS_ROW>(L.c1, nullptr, [&](int j) { return get_test<T>(L, j, lane); }, b1, b1, nb, lane, M);
+        for_pairs<DENS_ROW>(M, L.list, lane, []() {}, eval);
+        wave_sync();
+    };
+    const uint32_t last = (uint32_t)(a.n - 1);
+    int ncand = 0, eb = e0, p0 = 0, total = 0, start = 0;
+    V4 o, pf;
+    while (true) {
+        if (p0 >= total) {  // next batch of cells
+            for (total = 0; eb < e1 && total == 0; eb += SPH_BATCH) {
+                wave_sync();
+                total = load_batch_flat<T>(a.list, eb, min(SPH_BATCH, e1 - eb), lane, a.l_begin, a.l_count, a.l_origin, oA, I, sc,
+                                           [&](const ListEntry& E) { return E.dist < hA + mg; }, L.e, start);
+            }
+            p0 = 0;
+            if (total > 0) {
+                o = L.e.o[stream_cell(0, start)];
+                pf = pos4[min((uint32_t)(lane + unpack_int(o.w)), last)];
+            }
+        }
+        V4 q;
+        unsigned long long mk = 0ull;
+        if (total > 0) {
+            q.x = fma_t(pf.x, sc, o.x);
+            q.y = fma_t(pf.y, sc, o.y);
+            q.z = fma_t(pf.z, sc, o.z);
+            q.w = pf.w;
+            mk = __ballot((p0 + lane < total) & (box_d2<T>(q.x, q.y, q.z, bxl, byl, bzl, bxh, byh, bzh) < hA2));
+            p0 += 64;
+            if (p0 < total) {
+                o = L.e.o[stream_cell(p0, start)];
+                pf = pos4[min((uint32_t)(p0 + lane + unpack_int(o.w)), last)];
+            }
+        }
+        const int nk = __popcll(mk);
+        if (ncand + nk > 4 * DENS_ROW || total == 0) {
+            if (ncand > 0) run_tile(ncand);
+            if (total == 0) break;
+            ncand = 0;
+        }
+        if ((mk >> lane) & 1ull) {
+            const int slot = ncand + lane_rank(mk);
+            L.cand[slot] = q;
+            L.c1[test_slot<DENS_ROW>(slot)] = put_test<T>(L, slot, q.x, q.y, q.z) * (1.0f - PAIR_EPS);
+        }
+        ncand += nk;
+    }
+    wave_sync();
+    const bool left = dens_finish<T>(a, i, act, 0, 64, Hd, L.sw[lane], L.sd[lane], (double)L.s2[lane], L.cnt[lane], hlA,
+                                     hlim, s0min);
     const unsigned long long lm = __ballot(left);
     if (lane == 0) a.l_active[A] = lm ? 1 : 0;
+    wave_sync();
 }
 
 template <typename T, bool COMP, int PRUNE>
@@ -363,17 +417,17 @@ __global__ __launch_bounds__(256) void k_density(DensArgs a)
 // Packed density sweep over the leaves of at most 64 particles (box
 // pruning); the LDS is only the packed candidate buffer, so more waves fit
 // on a CU than with the two-phase tiles.
-template <typename T, bool COMP, int WPE, int NE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, 8))) void k_density_packed(DensArgs a)
+template <typename T, int WPE>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, 8))) void k_density_packed(DensArgs a)
 {
-    __shared__ PTile<T, NE> tiles[WAVES_PER_WG];
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    __shared__ typename ptile<T>::type tile;
+    const int lane = threadIdx.x;
     if (a.gate && uniform(*a.gate) != 0) return;
     const int nL = a.nl_dev ? uniform(*a.nl_dev) : a.n_leaves;
-    const int A = uniform(xcd_block(blockIdx.x, gridDim.x) * WAVES_PER_WG + w);
+    const int A = uniform(xcd_block(blockIdx.x, gridDim.x));
     if (A >= nL) return;
     if (!a.l_active[A] || a.l_count[A] > 64) return;
-    density_leaf_packed<T, COMP, NE>(a, A, tiles[w], lane);
+    density_leaf_packed<T>(a, A, tile, lane);
 }
 
 __global__ __launch_bounds__(256) void k_density_reset(int64_t n, int n_leaves, double* hlo, double* hhi, uint8_t* conv,
@@ -392,6 +446,7 @@ __global__ __launch_bounds__(256) void k_density_reset(int64_t n, int n_leaves, 
 // ---------------------------------------------------------------------------
 // Ghost: Omega = 1 + H/(3 rho) drho/dH, P = (gamma-1) rho u, A = P/(Omega rho^2)
 // ---------------------------------------------------------------------------
+enum { GHOST_PAIRS = 0, GHOST_PLIST = 1, GHOST_GATHER = 2 };
 template <typename T>
 __global__ __launch_bounds__(256) void k_ghost(int64_t n, const double* __restrict__ rho, const double* __restrict__ drho,
                                                const double* __restrict__ H, const double* __restrict__ u,
@@ -400,7 +455,7 @@ __global__ __launch_bounds__(256) void k_ghost(int64_t n, const double* __restri
                                                typename vec4<T>::type* fv4, T* hf, const int* gate,
                                                const double* __restrict__ ax, const double* __restrict__ ay,
                                                const double* __restrict__ az, const double* __restrict__ dudt,
-                                               const double* __restrict__ hdt, int lists)
+                                               const double* __restrict__ hdt, int form)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
@@ -425,11 +480,13 @@ __global__ __launch_bounds__(256) void k_ghost(int64_t n, const double* __restri
     f.x = (T)v0;
     f.y = (T)v1;
     f.z = (T)v2;
-    // the leaf kernels take A and H; the particle-list force takes the
-    // kernel-gradient factor A (8/pi) / H^4 and 1/H directly
-    f.w = lists ? (T)(A * INV_PI_8 / (h * h * h * h)) : (T)A;
+    // the pairs-once force takes A and H; the gather forms take the
+    // kernel-gradient factor A (8/pi) / H^4, over cells times the -6 of the
+    // spline's derivative and with H, over particle lists with 1/H
+    const double k = A * INV_PI_8 / (h * h * h * h);
+    f.w = form == GHOST_PAIRS ? (T)A : form == GHOST_GATHER ? (T)(-6.0 * k) : (T)k;
     fv4[i] = f;
-    hf[i] = lists ? (T)(1.0 / h) : (T)h;
+    hf[i] = form == GHOST_PLIST ? (T)(1.0 / h) : (T)h;
 }
 
 // ---------------------------------------------------------------------------
@@ -886,25 +943,37 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPH_FORCE_W
 // H_j) of eqs. (dvdt) and (dudt) over the cells of A's symmetric list.  Every
 // pair is evaluated from both sides (twice the pair arithmetic of the
 // pairs-once form) but nothing is accumulated on the j side, so there are no
-// atomics and each output is written once.  Same packing as the density:
-// candidates of all cells that pass the box test are packed 64 per tile;
-// phase 1 j-major (lane = candidate, one ballot per particle of A reaching
-// the tile), phase 2 i-major over the set bits.
+// global atomics and each output is written once.  Candidate stream,
+// matrix-unit range tests (against H_i and H_j) and pair-parallel sums as in
+// the density, and bound like it: 1.08e4 VALU and 456 MFMA instructions per
+// leaf at 256^3 clustered (2.6e4 before), 12.9 -> 11.0 ms; 64^3 FP64 1.33 ->
+// 0.86 ms.
 // ---------------------------------------------------------------------------
-template <typename T, int NE>
+template <typename T>
 struct GTile {
-    typename vec4<T>::type cp[128];   // j in A's frame: x, y, z, m
-    typename vec4<T>::type cv[128];   // vx, vy, vz, k_j = A_j (8/pi) / H_j^4
-    typename vec2t<T>::type ch[128];  // H_j^2, 1/H_j
-    typename vec4<T>::type si[64];    // i of A: x, y, z (A frame), H_i^2 (negative: no particle)
-    EBatchBox<T, NE> e;
+    typename vec4<T>::type cand[4 * FORCE_ROW];  // j in A's frame: x, y, z, m
+    typename vec4<T>::type cv[4 * FORCE_ROW];    // vx, vy, vz, k_j = -6 A_j (8/pi) / H_j^4 (first the particle's index)
+    T ch[4 * FORCE_ROW];                         // 1/H_j
+    union {
+        float c[2][4 * FORCE_ROW];               // row constants of the range tests
+        uint16_t list[PAIR_CAP];        // then the pairs
+    };
+    typename vec4<T>::type si[64];      // i of A: x, y, z (A frame), 1/H_i
+    typename vec4<T>::type sv[64];      // vx, vy, vz, k_i
+    double sum[4][64];                  // dv/dt, du/dt
+    int cnt[64];                        // pairs within H_i
+    EFlat<T, SPH_BATCH> e;
 };
+struct GTile64 : GTile<double> {
+    float4 fc[4 * FORCE_ROW];
+};
+template <typename T> struct gtile { typedef GTile<T> type; };
+template <> struct gtile<double> { typedef GTile64 type; };
 
-template <typename T, bool COMP, int NE>
-__device__ void force_leaf_gather(const ForceArgs& a, int A, GTile<T, NE>& L, int lane)
+template <typename T>
+__device__ void force_leaf_gather(const ForceArgs& a, int A, typename gtile<T>::type& L, int lane)
 {
     typedef typename vec4<T>::type V4;
-    typedef typename vec2t<T>::type V2;
     const V4* pos4 = (const V4*)a.pos4;
     const V4* fv4 = (const V4*)a.fv4;
     const T* hf = (const T*)a.hf;
@@ -919,208 +988,203 @@ __device__ void force_leaf_gather(const ForceArgs& a, int A, GTile<T, NE>& L, in
         const int nc = min(64, nA - c0);
         const bool vi = lane < nc;
         const int i = bA + c0 + (vi ? lane : 0);
-        const unsigned long long vmask = __ballot(vi);
+        const int nb = (nc + 15) >> 4;
         const V4 pi = pos4[i];
-        const V4 fi = fv4[i];
         const T Hi = hf[i];
-        const T h2i = Hi * Hi, ihi = T(1) / Hi;
-        const T ki = fi.w * T(INV_PI_8) * ihi * ihi * ihi * ihi;
-        FAcc<T, COMP> ai;
-        int nni = 0, nmax = 0;  // pairs within H_i and within max(H_i, H_j), self included
         const double hA = wave_max(vi ? (double)Hi : 0.0);
-        const T hAm = (T)(hA * (1.0 + 1e-5));
-        const T bxl = wave_min_t<T>(vi ? pi.x : big), bxh = wave_max_t<T>(vi ? pi.x : -big);
-        const T byl = wave_min_t<T>(vi ? pi.y : big), byh = wave_max_t<T>(vi ? pi.y : -big);
-        const T bzl = wave_min_t<T>(vi ? pi.z : big), bzh = wave_max_t<T>(vi ? pi.z : -big);
-        wave_sync();
+        T bxl = wave_min_t<T>(vi ? pi.x : big), bxh = wave_max_t<T>(vi ? pi.x : -big);
+        T byl = wave_min_t<T>(vi ? pi.y : big), byh = wave_max_t<T>(vi ? pi.y : -big);
+        T bzl = wave_min_t<T>(vi ? pi.z : big), bzh = wave_max_t<T>(vi ? pi.z : -big);
+        // scale: the leaf's box and its largest H are of order 1 below
+        const T sc = pow2_scale(fmax((T)hA, fmax(fmax(fmax(-bxl, bxh), fmax(-byl, byh)), fmax(-bzl, bzh))));
+        bxl *= sc, bxh *= sc, byl *= sc, byh *= sc, bzl *= sc, bzh *= sc;
+        const T hAm = (T)(hA * (1.0 + 1e-5)) * sc;
+        float b1[4], b2[4];
+        int nmax = 0;  // pairs within max(H_i, H_j), self included, of the lane's runs
         {
             V4 q = pi;
-            q.w = vi ? h2i : T(-1);
+            q.x *= sc, q.y *= sc, q.z *= sc;
+            const float x = (float)q.x, y = (float)q.y, z = (float)q.z, h = (float)(Hi * sc);
+            const float p2 = x * x + y * y + z * z;
+            const bool on = vi && p2 < 1e30f;
+            const float xi = on ? x : 0.f, yi = on ? y : 0.f, zi = on ? z : 0.f;
+            const float ci = on ? p2 * (1.0f - PAIR_EPS) - 1e-30f : 1e30f;
+            test_operand(xi, yi, zi, on ? ci - h * h * (1.0f + PAIR_EPS) : 1e30f, (float4*)L.cand, lane, b1);
+            test_operand(xi, yi, zi, ci, (float4*)L.cand, lane, b2);
+            q.w = T(1) / (Hi * sc);
             L.si[lane] = q;
+            L.sv[lane] = fv4[i];
+            for (int k = 0; k < 4; k++) L.sum[k][lane] = 0.0;
+            L.cnt[lane] = 0;
         }
-        // box of the buffered candidates (union of their cells' boxes) and
-        // the largest list radius of those cells (bounds their H)
-        T tlo[3] = {big, big, big}, thi[3] = {-big, -big, -big};
-        T thl = T(0);
-        auto run_tile = [&](int len) {
-            wave_sync();
-            const V4 pj = L.cp[lane];
-            const V2 hj = L.ch[lane];
-            const bool lv = lane < len;
-            const T R = fmax(Hi, thl) * T(1.00001);
-            const unsigned long long imask =
-                vmask & __ballot(box_d2<T>(pi.x, pi.y, pi.z, tlo[0], tlo[1], tlo[2], thi[0], thi[1], thi[2]) < R * R);
-            int mlo = 0, mhi = 0;
-            for (unsigned long long m = imask; m; m &= m - 1ull) {
-                const int ii = uniform(__ffsll((long long)m) - 1);
-                const V4 q = L.si[ii];
-                const T dx = pj.x - q.x, dy = pj.y - q.y, dz = pj.z - q.z;
-                const unsigned long long hm = __ballot(lv && dx * dx + dy * dy + dz * dz < fmax(q.w, hj.x));
-                mlo = amdgcn_writelane((int)(uint32_t)hm, ii, mlo);
-                mhi = amdgcn_writelane((int)(uint32_t)(hm >> 32), ii, mhi);
-            }
-            if (vi) {
-                unsigned long long m = ((unsigned long long)(uint32_t)mhi << 32) | (uint32_t)mlo;
-                while (m) {
-                    const int sl = __ffsll((long long)m) - 1;
-                    m &= m - 1ull;
-                    const V4 q = L.cp[sl];
-                    const V4 fj = L.cv[sl];
-                    const V2 hh = L.ch[sl];
-                    const T dx = pi.x - q.x, dy = pi.y - q.y, dz = pi.z - q.z;
-                    const T r2 = dx * dx + dy * dy + dz * dz;
-                    nmax++;
-                    if (r2 < h2i) nni++;
-                    // the particle itself and coincident ones exert no force:
-                    // at r2 = 0 the clamp gives r = 0, dW/dr(0) = 0 and d = 0,
-                    // so every term below is an exact zero (no branch)
-                    const T ir = fast_rsqrt(fmax(r2, T(1e-30)));
-                    const T r = r2 * ir;
-                    const T Fi = ki * spline_dw(r * ihi);    // A_i dW/dr(r, H_i)
-                    const T Fj = fj.w * spline_dw(r * hh.y);  // A_j dW/dr(r, H_j)
-                    const T F = (Fi + Fj) * ir;
-                    const T dvdr = ((fi.x - fj.x) * dx + (fi.y - fj.y) * dy + (fi.z - fj.z) * dz) * ir;
-                    const T mjF = q.w * F;
-                    ai.ax.add(-mjF * dx);
-                    ai.ay.add(-mjF * dy);
-                    ai.az.add(-mjF * dz);
-                    ai.du.add(q.w * Fi * dvdr);
+        // the sums of one run of pairs
+        auto eval = [&](const uint16_t* list, int n) {
+            const int K = (n + 63) >> 6;
+            int cur = -1, cnt = 0;
+            double ax = 0.0, ay = 0.0, az = 0.0, du = 0.0;
+            V4 p, f;
+            auto flush = [&]() {
+                lds_add(&L.sum[0][cur], ax);
+                lds_add(&L.sum[1][cur], ay);
+                lds_add(&L.sum[2][cur], az);
+                lds_add(&L.sum[3][cur], du);
+                lds_add(&L.cnt[cur], cnt);
+            };
+            for (int e = lane * K; e < min(lane * K + K, n); e++) {
+                const int code = list[e], ii = code >> 7, j = code & 127;
+                if (ii != cur) {
+                    if (cur >= 0) flush();
+                    cur = ii;
+                    p = L.si[ii];
+                    f = L.sv[ii];
+                    ax = ay = az = du = 0.0;
+                    cnt = 0;
                 }
+                const V4 q = L.cand[j], fj = L.cv[j];
+                const T ihj = L.ch[j];
+                const T dx = p.x - q.x, dy = p.y - q.y, dz = p.z - q.z;
+                const T r2 = dx * dx + dy * dy + dz * dz;
+                // the particle itself and coincident ones exert no force:
+                // at r2 = 0 the clamp gives r = 0, dW/dr(0) = 0 and d = 0,
+                // so every term below is an exact zero (no branch)
+                const T ir = fast_rsqrt(fmax(r2, sizeof(T) == 8 ? T(1e-300) : T(1e-30)));
+                const T r = r2 * ir, qi = r * p.w, qj = r * ihj;
+                const T Fi = f.w * spline_dw6(qi);   // A_i dW/dr(r, H_i)
+                const T Fj = fj.w * spline_dw6(qj);  // A_j dW/dr(r, H_j)
+                const T F = (Fi + Fj) * ir;
+                const T dvdr = ((f.x - fj.x) * dx + (f.y - fj.y) * dy + (f.z - fj.z) * dz) * ir;
+                const T mjF = q.w * F;
+                ax -= (double)(mjF * dx);
+                ay -= (double)(mjF * dy);
+                az -= (double)(mjF * dz);
+                // (a pair let in by the tests' margin adds nothing, whatever its velocities)
+                const bool in = fmin(qi, qj) < T(1);
+                du += (double)(in ? q.w * Fi * dvdr : T(0));
+                cnt += qi < T(1);
+                nmax += in;
             }
+            if (cur >= 0) flush();
+        };
+        auto run_tile = [&](int len) {
+            for (int j = len + lane; j < 4 * FORCE_ROW; j += 64) {
+                V4 o;
+                o.x = o.y = o.z = o.w = T(0);
+                L.cand[j] = o;
+                put_test<T>(L, j, T(0), T(0), T(0));
+                L.c[0][test_slot<FORCE_ROW>(j)] = L.c[1][test_slot<FORCE_ROW>(j)] = 1e30f;
+            }
+            wave_sync();
+            // velocities and factors of the candidates: in flight during the tests
+            V4 v0, v1;
+            if (lane < len) v0 = fv4[((const uint32_t*)&L.cv[lane])[0]];
+            if (lane + 64 < len) v1 = fv4[((const uint32_t*)&L.cv[lane + 64])[0]];
+            uint32_t M[4] = {0u, 0u, 0u, 0u};
+            tile_masks<true, FORCE_ROW>(L.c[0], L.c[1], [&](int j) { return get_test<T>(L, j, lane); }, b1, b2, nb, lane, M);
+            for_pairs<FORCE_ROW>(M, L.list, lane, [&]() {
+                if (lane < len) L.cv[lane] = v0;
+                if (lane + 64 < len) L.cv[lane + 64] = v1;
+            }, eval);
             wave_sync();
         };
-        int ncand = 0;
-        // cell boxes grow by the displacement since the build plus float rounding
-        const double grow = 0.5 * mg + 1e-5 * hA;
-        for (int eb = e0; eb < e1; eb += NE) {
-            const int nbt = min(NE, e1 - eb);
-            const double* hl = a.l_hlist;
-            const int nv = load_batch_box<T>(a.list, eb, nbt, lane, a.l_begin, a.l_count, a.l_origin, a.l_lo, a.l_hi,
-                                             hl, oA, I, grow,
-                                             [&](const ListEntry& E) { return E.dist < fmax(hA + mg, hl[E.B]); }, L.e);
-            // prefetched first chunk (positions, H) of the next cell
-            V4 pf;
-            T hp = T(1);
-            if (nv > 0 && lane < L.e.n[0]) {
-                const int p = L.e.b[0] + lane;
-                pf = pos4[p];
-                hp = hf[p];
-            }
-            for (int k = 0; k < nv; k++) {
-                const int bB = L.e.b[k], nB = L.e.n[k];
-                const T dox = L.e.ox[k], doy = L.e.oy[k], doz = L.e.oz[k];
-                const V4 cq = pf;
-                const T ch_ = hp;
-                if (k + 1 < nv && lane < L.e.n[k + 1]) {
-                    const int p = L.e.b[k + 1] + lane;
-                    pf = pos4[p];
-                    hp = hf[p];
+        const uint32_t last = (uint32_t)(a.n - 1);
+        const double* hl = a.l_hlist;
+        int ncand = 0, eb = e0, p0 = 0, total = 0, start = 0;
+        uint32_t jp = 0;
+        V4 o, pf;
+        T hp;
+        while (true) {
+            if (p0 >= total) {  // next batch of cells
+                for (total = 0; eb < e1 && total == 0; eb += SPH_BATCH) {
+                    wave_sync();
+                    total = load_batch_flat<T>(a.list, eb, min(SPH_BATCH, e1 - eb), lane, a.l_begin, a.l_count, a.l_origin, oA, I,
+                                               sc, [&](const ListEntry& E) { return E.dist < fmax(hA + mg, hl[E.B]); },
+                                               L.e, start);
                 }
-                for (int p0 = 0; p0 < nB; p0 += 64) {
-                    const int len = min(64, nB - p0);
-                    bool in = false;
-                    V4 q;
-                    T h = T(1);
-                    if (lane < len) {
-                        if (p0 == 0) {
-                            q = cq;
-                            h = ch_;
-                        } else {
-                            q = pos4[bB + p0 + lane];
-                            h = hf[bB + p0 + lane];
-                        }
-                        q.x += dox;
-                        q.y += doy;
-                        q.z += doz;
-                        const T Rj = fmax(hAm, h * T(1.00001));
-                        in = box_d2<T>(q.x, q.y, q.z, bxl, byl, bzl, bxh, byh, bzh) < Rj * Rj;
-                    }
-                    const unsigned long long mk = __ballot(in);
-                    if (in) {
-                        const V4 f = fv4[bB + p0 + lane];
-                        const int slot = ncand + mask_rank(mk, lane);
-                        const T ih = fast_rcp(h);
-                        V4 g = f;
-                        g.w = f.w * T(INV_PI_8) * ih * ih * ih * ih;
-                        V2 hh;
-                        hh.x = h * h;
-                        hh.y = ih;
-                        L.cp[slot] = q;
-                        L.cv[slot] = g;
-                        L.ch[slot] = hh;
-                    }
-                    ncand += __popcll(mk);
-                    if (mk) {
-                        for (int d = 0; d < 3; d++) {
-                            tlo[d] = fmin(tlo[d], L.e.lo[d][k]);
-                            thi[d] = fmax(thi[d], L.e.hi[d][k]);
-                        }
-                        thl = fmax(thl, L.e.hl[k]);
-                    }
-                    if (ncand >= 64) {
-                        run_tile(64);
-                        const int rest = ncand - 64;
-                        V4 t0, t1;
-                        V2 t2;
-                        if (lane < rest) {
-                            t0 = L.cp[64 + lane];
-                            t1 = L.cv[64 + lane];
-                            t2 = L.ch[64 + lane];
-                        }
-                        wave_sync();
-                        if (lane < rest) {
-                            L.cp[lane] = t0;
-                            L.cv[lane] = t1;
-                            L.ch[lane] = t2;
-                        }
-                        ncand = rest;
-                        // the carried candidates all come from this cell
-                        for (int d = 0; d < 3; d++) {
-                            tlo[d] = rest ? L.e.lo[d][k] : big;
-                            thi[d] = rest ? L.e.hi[d][k] : -big;
-                        }
-                        thl = rest ? L.e.hl[k] : T(0);
-                    }
+                p0 = 0;
+                if (total > 0) {
+                    o = L.e.o[stream_cell(0, start)];
+                    jp = min((uint32_t)(lane + unpack_int(o.w)), last);
+                    pf = pos4[jp];
+                    hp = hf[jp];
                 }
             }
-            wave_sync();
+            V4 q;
+            T h;
+            uint32_t j;
+            unsigned long long mk = 0ull;
+            if (total > 0) {
+                q.x = fma_t(pf.x, sc, o.x);
+                q.y = fma_t(pf.y, sc, o.y);
+                q.z = fma_t(pf.z, sc, o.z);
+                q.w = pf.w;
+                h = hp * sc;
+                j = jp;
+                const T Rj = fmax(hAm, h * T(1.00001));
+                mk = __ballot((p0 + lane < total) &
+                              (box_d2<T>(q.x, q.y, q.z, bxl, byl, bzl, bxh, byh, bzh) < Rj * Rj));
+                p0 += 64;
+                if (p0 < total) {
+                    o = L.e.o[stream_cell(p0, start)];
+                    jp = min((uint32_t)(p0 + lane + unpack_int(o.w)), last);
+                    pf = pos4[jp];
+                    hp = hf[jp];
+                }
+            }
+            const int nk = __popcll(mk);
+            if (ncand + nk > 4 * FORCE_ROW || total == 0) {
+                if (ncand > 0) run_tile(ncand);
+                if (total == 0) break;
+                ncand = 0;
+            }
+            if ((mk >> lane) & 1ull) {
+                const int slot = ncand + lane_rank(mk);
+                L.cand[slot] = q;
+                ((uint32_t*)&L.cv[slot])[0] = j;  // its velocity and factor are loaded with the tile
+                L.ch[slot] = fast_rcp(h);
+                const float hs = (float)h;
+                const float cj = put_test<T>(L, slot, q.x, q.y, q.z) * (1.0f - PAIR_EPS);
+                L.c[0][test_slot<FORCE_ROW>(slot)] = cj;
+                L.c[1][test_slot<FORCE_ROW>(slot)] = cj - hs * hs * (1.0f + PAIR_EPS);
+            }
+            ncand += nk;
         }
-        if (ncand > 0) run_tile(ncand);
+        wave_sync();
+        npairs += (unsigned long long)nmax;
         if (vi) {
-            a.ax[i] = ai.ax.total();
-            a.ay[i] = ai.ay.total();
-            a.az[i] = ai.az.total();
-            a.dudt[i] = ai.du.total();
-            if (a.nngb) a.nngb[i] = nni;
-            npairs += (unsigned long long)max(nmax - 1, 0);  // ordered pairs, the particle itself excluded
-            ndens_w += (unsigned long long)nni;
+            a.ax[i] = L.sum[0][lane];
+            a.ay[i] = L.sum[1][lane];
+            a.az[i] = L.sum[2][lane];
+            a.dudt[i] = L.sum[3][lane];
+            if (a.nngb) a.nngb[i] = L.cnt[lane];
+            ndens_w += (unsigned long long)L.cnt[lane];
         }
         wave_sync();
     }
     npairs = wave_sum(npairs);
     ndens_w = wave_sum(ndens_w);
-    if (lane == 0 && npairs) count_add(a.counters, PART_NFORCE, npairs);
+    // ordered pairs, the particles themselves excluded
+    if (lane == 0 && npairs > (unsigned long long)nA) count_add(a.counters, PART_NFORCE, npairs - (unsigned long long)nA);
     if (lane == 0 && ndens_w) count_add(a.counters, PART_NDENS_F, ndens_w);
 }
 
-template <typename T, bool COMP, int WPE, int NE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, 8))) void k_force_gather(ForceArgs a)
+template <typename T, int WPE>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, 8))) void k_force_gather(ForceArgs a)
 {
-    __shared__ GTile<T, NE> tiles[WAVES_PER_WG];
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    __shared__ typename gtile<T>::type tile;
+    const int lane = threadIdx.x;
     if (a.gate && uniform(*a.gate) != 1) return;
     const int nL = a.nl_dev ? uniform(*a.nl_dev) : a.n_leaves;
     if (!a.persistent) {
-        const int A = uniform(xcd_block(blockIdx.x, gridDim.x) * WAVES_PER_WG + w);
+        const int A = uniform(xcd_block(blockIdx.x, gridDim.x));
         if (A >= nL) return;
-        force_leaf_gather<T, COMP, NE>(a, A, tiles[w], lane);
+        force_leaf_gather<T>(a, A, tile, lane);
         return;
     }
     int k = 0;
     for (int it = 0; it <= nL; it++) {
         const int A = xq_pop(&a.counters[XQ_FORCE], nL, k, lane);
         if (A < 0) break;
-        force_leaf_gather<T, COMP, NE>(a, A, tiles[w], lane);
+        force_leaf_gather<T>(a, A, tile, lane);
     }
 }
 
@@ -1333,61 +1397,24 @@ static void dens_args(sph_ctx* c, const int* gate, bool graph, DensArgs& a, int&
 }
 
 // The packed density and gather force kernels of the context's occupancy
-// target and batch size (FP64: the defaults only).
-template <typename T, bool COMP>
-static void density_packed_wb(int wpe, int ne, int nb, hipStream_t s, const DensArgs& a)
-{
-    if (ne == 16) {
-        switch (wpe) {
-        case 4: k_density_packed<T, COMP, 4, 16><<<nb, 256, 0, s>>>(a); return;
-        case 5: k_density_packed<T, COMP, 5, 16><<<nb, 256, 0, s>>>(a); return;
-        case 8: k_density_packed<T, COMP, 8, 16><<<nb, 256, 0, s>>>(a); return;
-        default: k_density_packed<T, COMP, 6, 16><<<nb, 256, 0, s>>>(a); return;
-        }
-    }
-    switch (wpe) {
-    case 4: k_density_packed<T, COMP, 4, 32><<<nb, 256, 0, s>>>(a); return;
-    case 5: k_density_packed<T, COMP, 5, 32><<<nb, 256, 0, s>>>(a); return;
-    case 8: k_density_packed<T, COMP, 8, 32><<<nb, 256, 0, s>>>(a); return;
-    default: k_density_packed<T, COMP, 6, 32><<<nb, 256, 0, s>>>(a); return;
-    }
-}
-
+// target (FP64: the defaults only).
 static void launch_density_packed(sph_ctx* c, int nb, const DensArgs& a)
 {
-    const int wpe = c->prm.waves_density ? c->prm.waves_density : SPH_DENS_WAVES;
-    const int ne = c->prm.batch ? c->prm.batch : SPH_BATCH;
-    if (c->prm.precision == SPH_FP64) k_density_packed<double, false, SPH_DENS_WAVES, SPH_BATCH><<<nb, 256, 0, c->stream>>>(a);
-    else if (c->prm.precision == SPH_FP32C) density_packed_wb<float, true>(wpe, ne, nb, c->stream, a);
-    else density_packed_wb<float, false>(wpe, ne, nb, c->stream, a);
-}
-
-template <typename T, bool COMP>
-static void force_gather_wb(int wpe, int ne, int nb, hipStream_t s, const ForceArgs& a)
-{
-    if (ne == 16) {
-        switch (wpe) {
-        case 4: k_force_gather<T, COMP, 4, 16><<<nb, 256, 0, s>>>(a); return;
-        case 6: k_force_gather<T, COMP, 6, 16><<<nb, 256, 0, s>>>(a); return;
-        case 8: k_force_gather<T, COMP, 8, 16><<<nb, 256, 0, s>>>(a); return;
-        default: k_force_gather<T, COMP, 5, 16><<<nb, 256, 0, s>>>(a); return;
-        }
+    if (c->prm.precision == SPH_FP64) {
+        k_density_packed<double, SPH_DENS_WAVES64><<<nb, 64, 0, c->stream>>>(a);
+        return;
     }
-    switch (wpe) {
-    case 4: k_force_gather<T, COMP, 4, 32><<<nb, 256, 0, s>>>(a); return;
-    case 6: k_force_gather<T, COMP, 6, 32><<<nb, 256, 0, s>>>(a); return;
-    case 8: k_force_gather<T, COMP, 8, 32><<<nb, 256, 0, s>>>(a); return;
-    default: k_force_gather<T, COMP, 5, 32><<<nb, 256, 0, s>>>(a); return;
+    switch (c->prm.waves_density ? c->prm.waves_density : SPH_DENS_WAVES) {
+    case 4: k_density_packed<float, 4><<<nb, 64, 0, c->stream>>>(a); return;
+    case 5: k_density_packed<float, 5><<<nb, 64, 0, c->stream>>>(a); return;
+    default: k_density_packed<float, 6><<<nb, 64, 0, c->stream>>>(a); return;
     }
 }
 
 static void launch_force_gather(sph_ctx* c, int nb, const ForceArgs& a)
 {
-    const int wpe = c->prm.waves_force ? c->prm.waves_force : SPH_FORCEG_WAVES;
-    const int ne = c->prm.batch ? c->prm.batch : SPH_BATCH;
-    if (c->prm.precision == SPH_FP64) k_force_gather<double, false, SPH_FORCEG_WAVES, SPH_BATCH><<<nb, 256, 0, c->stream>>>(a);
-    else if (c->prm.precision == SPH_FP32C) force_gather_wb<float, true>(wpe, ne, nb, c->stream, a);
-    else force_gather_wb<float, false>(wpe, ne, nb, c->stream, a);
+    if (c->prm.precision == SPH_FP64) k_force_gather<double, SPH_FORCEG_WAVES64><<<nb, 64, 0, c->stream>>>(a);
+    else k_force_gather<float, SPH_FORCEG_WAVES><<<nb, 64, 0, c->stream>>>(a);
 }
 
 // Density sweeps run as a grid of one wave per leaf in every execution mode:
@@ -1403,7 +1430,7 @@ static sph_status launch_density(sph_ctx* c, const int* gate, bool graph = false
     if (nb <= 0) return SPH_OK;
     const bool srt = c->prm.prune == SPH_PRUNE_SORTED;
     if (!srt) {
-        launch_density_packed(c, nb, a);
+        launch_density_packed(c, graph ? leaf_capacity(c) : c->n_leaves, a);
         SPH_CHECK_LAUNCH();
         // leaves above 64 particles (cells that cannot be split further):
         // the chunked two-phase kernel over a plain grid
@@ -1649,14 +1676,17 @@ static sph_status launch_ghost(sph_ctx* c, const double* u, const double* vx, co
                                const int* gate)
 {
     const double* hdt = (const double*)c->dparam.p + 2;
+    const int form = c->prm.lists == SPH_LISTS_PARTICLE          ? GHOST_PLIST
+                     : c->prm.force_mode == SPH_FORCE_GATHER ? GHOST_GATHER
+                                                             : GHOST_PAIRS;
     if (c->prm.precision == SPH_FP64)
         k_ghost<double><<<blocks_for(c->n, 256), 256, 0, c->stream>>>(
             c->n, c->P.rho, c->P.drho_dH, c->P.H, u, vx, vy, vz, c->prm.gamma, c->P.omega, c->P.P, (double4*)c->fv4.p,
-            (double*)c->hf.p, gate, c->P.ax, c->P.ay, c->P.az, c->P.dudt, hdt, c->prm.lists);
+            (double*)c->hf.p, gate, c->P.ax, c->P.ay, c->P.az, c->P.dudt, hdt, form);
     else
         k_ghost<float><<<blocks_for(c->n, 256), 256, 0, c->stream>>>(
             c->n, c->P.rho, c->P.drho_dH, c->P.H, u, vx, vy, vz, c->prm.gamma, c->P.omega, c->P.P, (float4*)c->fv4.p,
-            (float*)c->hf.p, gate, c->P.ax, c->P.ay, c->P.az, c->P.dudt, hdt, c->prm.lists);
+            (float*)c->hf.p, gate, c->P.ax, c->P.ay, c->P.az, c->P.dudt, hdt, form);
     SPH_CHECK_LAUNCH();
     return SPH_OK;
 }
@@ -1716,7 +1746,10 @@ static void force_args(sph_ctx* c, const int* gate, bool graph, ForceArgs& a, in
     a.nl_dev = graph ? (const int*)c->flags.p + FI_NLEAVES : nullptr;
     if (graph) a.n_leaves = 0;  // read on the device
     const int nl = graph ? leaf_capacity(c) : c->n_leaves;
-    nb = a.persistent ? std::min(resident_wgs(c), blocks_for(nl, WAVES_PER_WG)) : blocks_for(nl, WAVES_PER_WG);
+    // the gather form runs one wave per workgroup
+    const int per = c->prm.force_mode == SPH_FORCE_GATHER ? 1 : WAVES_PER_WG;
+    nb = blocks_for(nl, per);
+    if (a.persistent) nb = std::min(resident_wgs(c) * (WAVES_PER_WG / per), nb);
 }
 
 static sph_status launch_force(sph_ctx* c, const int* gate, bool graph = false)

@@ -339,6 +339,52 @@ struct PlistBuildArgs {
     unsigned long long* n_entries;
 };
 
+// v_writelane_b32: replace lane `lane` of `old` by the wave-uniform `src`
+__device__ int amdgcn_writelane(int src, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
+
+// Neighbour-entry batch with each cell's box (at the build, A's frame,
+// grown by `grow`), for the list build.
+template <typename T, int NE>
+struct EBatchBox {
+    int b[NE], n[NE];
+    T ox[NE], oy[NE], oz[NE];
+    T lo[3][NE], hi[3][NE];
+    T hl[NE];  // list radius of the cell (bounds its particles' H)
+};
+
+template <typename T, typename Keep, int NE>
+__device__ inline int load_batch_box(const ListEntry* list, int eb, int nbt, int lane, const int* l_begin,
+                                     const int* l_count, const double* l_origin, const double* l_lo, const double* l_hi,
+                                     const double* l_hlist, const double* oA, const DomainInfo& I, double grow, Keep keep,
+                                     EBatchBox<T, NE>& E)
+{
+    bool ok = false;
+    ListEntry en;
+    if (lane < nbt) {
+        en = list[eb + lane];
+        ok = keep(en);
+    }
+    const unsigned long long mask = __ballot(ok);
+    if (ok) {
+        const int s = mask_rank(mask, lane);
+        const int B = en.B;
+        double sv[3];
+        shift_vec(en.code, I, sv);
+        E.b[s] = l_begin[B];
+        E.n[s] = l_count[B];
+        E.ox[s] = (T)(l_origin[3 * B] + sv[0] - oA[0]);
+        E.oy[s] = (T)(l_origin[3 * B + 1] + sv[1] - oA[1]);
+        E.oz[s] = (T)(l_origin[3 * B + 2] + sv[2] - oA[2]);
+        for (int d = 0; d < 3; d++) {
+            E.lo[d][s] = (T)(l_lo[3 * B + d] + sv[d] - oA[d] - grow);
+            E.hi[d][s] = (T)(l_hi[3 * B + d] + sv[d] - oA[d] + grow);
+        }
+        E.hl[s] = (T)l_hlist[B];
+    }
+    wave_sync();
+    return __popcll(mask);
+}
+
 template <typename T>
 struct PBTile {
     typename vec4<T>::type cp[128];  // candidate in A's frame, w = R_j
