@@ -1273,6 +1273,18 @@ sph_status node_hmax_all(sph_ctx* c, bool set_hlist)
     return SPH_OK;
 }
 
+// Leaves with long lists, for the kernels that share them among waves (in no
+// particular order: each is worked on by itself).
+__global__ __launch_bounds__(256) void k_wide_list(int n_leaves, const int* __restrict__ l_off, int* wide, int* n_wide,
+                                                   int* wide_min)
+{
+    const int A = blockIdx.x * blockDim.x + threadIdx.x;
+    const long long m = 5ll * l_off[n_leaves] / (2 * n_leaves);
+    const int len = n_leaves >= SPH_WIDE_MANY ? SPH_WIDE_MAX : (int)min((long long)SPH_WIDE_MAX, max((long long)SPH_WIDE_MIN, m));
+    if (A == 0) *wide_min = len;
+    if (A < n_leaves && l_off[A + 1] - l_off[A] > len) wide[atomicAdd(n_wide, 1)] = A;
+}
+
 sph_status relist(sph_ctx* c)
 {
     // particle lists: radii and skins from the current H
@@ -1322,10 +1334,19 @@ sph_status relist(sph_ctx* c)
     }
     SPH_CHECK_LAUNCH();
     SPH_TRY(scan_exclusive(c, counts, counts, nL + 1, flags + FI_NLIST));
-    int hf[FI_WINC - FI_NLIST + 1];
+    const bool wide = nL > SPH_WIDE_ALL && c->prm.prune == SPH_PRUNE_BOX && c->prm.lists == SPH_LISTS_CELL;
+    if (wide) {
+        SPH_TRY(buf_ensure(c->wide, (size_t)nL * sizeof(int)));
+        SPH_CHECK_HIP(hipMemsetAsync(flags + FI_NWIDE, 0, sizeof(int), c->stream));
+        k_wide_list<<<blocks_for(nL, 256), 256, 0, c->stream>>>(nL, counts, (int*)c->wide.p, flags + FI_NWIDE,
+                                                         flags + FI_WIDEMIN);
+        SPH_CHECK_LAUNCH();
+    }
+    int hf[FI_NWIDE - FI_NLIST + 1];
     SPH_CHECK_HIP(hipMemcpyAsync(hf, flags + FI_NLIST, sizeof(hf), hipMemcpyDeviceToHost, c->stream));
     SPH_CHECK_HIP(hipStreamSynchronize(c->stream));
     const int total = hf[0], incomplete = one_pass ? hf[FI_WINC - FI_NLIST] : 0;
+    c->n_wide = wide ? hf[FI_NWIDE - FI_NLIST] : 0;
     // particles in the fullest leaf above 64 (0: none), set by the leaf fill
     // of the last build (only a build clears the flags past FI_FLAGS)
     c->max_leaf = hf[FI_MAXLEAF - FI_NLIST];

@@ -90,6 +90,8 @@ struct sph_ctx {
     DevBuf leaf_node;             // leaf -> node
     DevBuf l_begin, l_count, l_origin, l_lo, l_hi, l_hlist, l_dom, l_off, l_active, l_sorted, l_cnt;
     DevBuf list;
+    DevBuf wide;                  // leaves with lists above SPH_WIDE_MIN (more than SPH_WIDE_ALL leaves)
+    int n_wide = 0;
     DevBuf walk_scratch;          // per-leaf slots of the one-pass list walk
     DevBuf walk_ovf, walk_link;   // its overflow chunks; chunk links (head, incomplete, next)
     int walk_cap = 128;           // entries per slot (grows after an overflow)

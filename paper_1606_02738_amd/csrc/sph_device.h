@@ -86,20 +86,88 @@ struct Acc {
     __device__ inline double total() const { return COMP ? (double)s - (double)c : (double)s; }
 };
 
-__device__ inline double wave_max(double v)
+// Reductions over the wave, the result in every lane: rotations within the rows
+// of 16 lanes (DPP), then swaps of rows and halves.  (Six ds_bpermute steps, at
+// the latency of LDS each, took 2 us of the 37 us of a leaf in a small box.)
+template <int CTRL>
+__device__ inline float lane_move(float v)
 {
-    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off));
-    return v;
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
 }
-__device__ inline float wave_minf(float v)
+template <int CTRL>
+__device__ inline unsigned long long lane_move(unsigned long long v)
 {
-    for (int off = 32; off > 0; off >>= 1) v = fminf(v, __shfl_xor(v, off));
-    return v;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, 0xf, 0xf, true);
+    return ((unsigned long long)hi << 32) | lo;
 }
-__device__ inline float wave_maxf(float v)
+template <int CTRL>
+__device__ inline double lane_move(double v)
 {
-    for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
-    return v;
+    return __builtin_bit_cast(double, lane_move<CTRL>(__builtin_bit_cast(unsigned long long, v)));
+}
+// v of the lane and of its partner in the next row (HALF: the other half), in
+// the same order in both lanes
+template <bool HALF>
+__device__ inline void lane_pair(uint32_t v, uint32_t& x, uint32_t& y)
+{
+    if (HALF) {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        x = r[0], y = r[1];
+    } else {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        x = r[0], y = r[1];
+    }
+}
+template <bool HALF>
+__device__ inline void lane_pair(float v, float& x, float& y)
+{
+    uint32_t a, b;
+    lane_pair<HALF>(__builtin_bit_cast(uint32_t, v), a, b);
+    x = __builtin_bit_cast(float, a), y = __builtin_bit_cast(float, b);
+}
+template <bool HALF>
+__device__ inline void lane_pair(unsigned long long v, unsigned long long& x, unsigned long long& y)
+{
+    uint32_t a, b, c, d;
+    lane_pair<HALF>((uint32_t)v, a, b);
+    lane_pair<HALF>((uint32_t)(v >> 32), c, d);
+    x = ((unsigned long long)c << 32) | a, y = ((unsigned long long)d << 32) | b;
+}
+template <bool HALF>
+__device__ inline void lane_pair(double v, double& x, double& y)
+{
+    unsigned long long a, b;
+    lane_pair<HALF>(__builtin_bit_cast(unsigned long long, v), a, b);
+    x = __builtin_bit_cast(double, a), y = __builtin_bit_cast(double, b);
+}
+template <typename V, typename Op>
+__device__ inline V wave_reduce(V v, Op op)
+{
+    v = op(v, lane_move<0x121>(v));
+    v = op(v, lane_move<0x122>(v));
+    v = op(v, lane_move<0x124>(v));
+    v = op(v, lane_move<0x128>(v));
+    V x, y;
+    lane_pair<false>(v, x, y);
+    v = op(x, y);
+    lane_pair<true>(v, x, y);
+    return op(x, y);
+}
+template <typename T> __device__ inline T wave_min_t(T v)
+{
+    return wave_reduce(v, [](T a, T b) { return fmin(a, b); });
+}
+template <typename T> __device__ inline T wave_max_t(T v)
+{
+    return wave_reduce(v, [](T a, T b) { return fmax(a, b); });
+}
+__device__ inline double wave_max(double v) { return wave_max_t<double>(v); }
+__device__ inline float wave_minf(float v) { return wave_min_t<float>(v); }
+__device__ inline float wave_maxf(float v) { return wave_max_t<float>(v); }
+__device__ inline unsigned long long wave_sum(unsigned long long v)
+{
+    return wave_reduce(v, [](unsigned long long a, unsigned long long b) { return a + b; });
 }
 // Wave-uniform pop from a device task counter: one atomic by lane 0, its
 // result read from the first lane into a scalar register by all lanes, so
@@ -179,17 +247,6 @@ __device__ inline bool sorted_window(const float* skey, int64_t n, int dir, int 
 // ---------------------------------------------------------------------------
 enum { PRUNE_BOX = 0, PRUNE_SORTED = 1 };
 
-template <typename T> __device__ inline T wave_min_t(T v)
-{
-    for (int off = 32; off > 0; off >>= 1) v = fmin(v, __shfl_xor(v, off));
-    return v;
-}
-template <typename T> __device__ inline T wave_max_t(T v)
-{
-    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off));
-    return v;
-}
-
 // Squared distance from p to the box [lo, hi].
 template <typename T>
 __device__ inline T box_d2(T px, T py, T pz, T lx, T ly, T lz, T hx, T hy, T hz)
@@ -211,12 +268,6 @@ __device__ inline int mask_rank(unsigned long long mask, int lane)
 __device__ inline void count_add(unsigned long long* counters, int what, unsigned long long v)
 {
     atomicAdd(&counters[CNT_PART + (blockIdx.x & (PART_N - 1)) * PART_STRIDE + what], v);
-}
-
-__device__ inline unsigned long long wave_sum(unsigned long long v)
-{
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    return v;
 }
 
 // Neighbour-entry batch of one wave, in LDS.
@@ -268,6 +319,10 @@ struct DensArgs {
     const int* gate;    // graph mode: skip the sweep unless *gate == 0 (NULL: always run)
     const int* nl_dev;  // graph mode: leaf count read from the device (NULL: n_leaves)
     int big_only;       // skip leaves of at most 64 particles (done by the packed kernel)
+    const int* wide;        // leaves with lists above *wide_min (NULL: all are taken as such)
+    const int* n_wide_dev;  // graph mode: their number
+    const int* wide_min;
+    int n_wide;
 };
 
 #define NTD 4  // neighbour cells per two-phase batch (density)
@@ -321,11 +376,11 @@ __device__ inline int load_batch(const ListEntry* list, int eb, int nbt, int lan
 // Returns true if the particle is left unconverged; conv: it is converged.
 template <bool EXTRAP>
 __device__ inline bool dens_newton(const DensArgs& a, int i, double H, double Sw, double Sd, double S2, int cnt,
-                                   double hlA, double hlim, double s0min, bool& conv)
+                                   double hlA, double hlim, double s0min, double mi, bool& conv)
 {
     const double rho = INV_PI_8 / (H * H * H) * Sw;
     const double drho = -INV_PI_8 / (H * H * H * H) * Sd;
-    const double C = a.C_fac * a.m[i];
+    const double C = a.C_fac * mi;
     const double f = INV_PI_8 * Sw - C;              // rho H^3 - C
     const double fp = INV_PI_8 * (3.0 * Sw - Sd) / H; // 3 H^2 rho + H^3 drho/dH
     const double F2 = INV_PI_8 * S2 / (H * H);         // d^2 (rho H^3) / dH^2
@@ -416,7 +471,7 @@ __device__ inline void dens_count(const DensArgs& a, bool act, bool left, bool c
 // is left unconverged.
 template <typename T>
 __device__ inline bool dens_finish(const DensArgs& a, int i, bool act, int jg, int CI, double Hd, double Sw0,
-                                   double Sd0, double S20, int cnt, double hlA, double hlim, double s0min)
+                                   double Sd0, double S20, int cnt, double hlA, double hlim, double s0min, double mi)
 {
     constexpr bool EXTRAP = sizeof(T) == 4;
     const int lane = threadIdx.x & 63;
@@ -428,7 +483,7 @@ __device__ inline bool dens_finish(const DensArgs& a, int i, bool act, int jg, i
         cnt += __shfl_xor(cnt, off);
     }
     bool left = false, conv = false;
-    if (jg == 0 && act) left = dens_newton<EXTRAP>(a, i, Hd, Sw, Sd, S2, cnt, hlA, hlim, s0min, conv);
+    if (jg == 0 && act) left = dens_newton<EXTRAP>(a, i, Hd, Sw, Sd, S2, cnt, hlA, hlim, s0min, mi, conv);
     dens_count(a, jg == 0 && act, left, conv, cnt, lane);
     return left;
 }
@@ -496,28 +551,32 @@ __device__ inline int load_batch_flat(const ListEntry* list, int eb, int nbt, in
                                       const int* l_count, const double* l_origin, const double* oA,
                                       const DomainInfo& I, T sc, Keep keep, EFlat<T, NE>& E, int& start)
 {
-    bool ok = false;
-    ListEntry en;
-    if (lane < nbt) {
-        en = list[eb + lane];
-        ok = keep(en);
-    }
+    // everything of the entry's cell is loaded at once: one latency
+    ListEntry en = {0, 0, INFINITY};
+    if (lane < nbt) en = list[eb + lane];
+    const bool ok = (lane < nbt) && keep(en);
+    const int n0 = ok ? l_count[en.B] : 0;
     const unsigned long long mask = __ballot(ok);
-    const int n = ok ? l_count[en.B] : 0;
+    const int n = ok ? n0 : 0;
+    static_assert(NE == 32, "the prefix sum below covers two rows");
     int incl = n;
-    for (int off = 1; off < NE; off <<= 1) {
-        const int t = __shfl_up(incl, off);
-        if (lane >= off) incl += t;
-    }
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xf, 0xf, true);
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xf, 0xf, true);
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xf, 0xf, true);
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xf, 0xf, true);
+    if (lane >= 16) incl += __builtin_amdgcn_readlane(incl, 15);
     if (ok) {
         const int s = lane_rank(mask);
         double sv[3];
         shift_vec(en.code, I, sv);
         typename vec4<T>::type o;
-        o.x = (T)(l_origin[3 * en.B] + sv[0] - oA[0]) * sc;
-        o.y = (T)(l_origin[3 * en.B + 1] + sv[1] - oA[1]) * sc;
-        o.z = (T)(l_origin[3 * en.B + 2] + sv[2] - oA[2]) * sc;
-        o.w = pack_int(l_begin[en.B] - (incl - n), T(0));
+        const double* q = l_origin + 3 * (size_t)en.B;
+        const double q0 = q[0], q1 = q[1], q2 = q[2];
+        const int b0 = l_begin[en.B];
+        o.x = (T)(q0 + sv[0] - oA[0]) * sc;
+        o.y = (T)(q1 + sv[1] - oA[1]) * sc;
+        o.z = (T)(q2 + sv[2] - oA[2]) * sc;
+        o.w = pack_int(b0 - (incl - n), T(0));
         E.o[s] = o;
         E.st[s] = incl - n;
     }

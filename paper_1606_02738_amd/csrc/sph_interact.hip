@@ -30,6 +30,8 @@
 #define SPH_FORCEG_WAVES 4
 #define SPH_DENS_WAVES64 3
 #define SPH_FORCEG_WAVES64 2
+// ... and of their forms with several waves per leaf (at 6 the density spills).
+#define SPH_WIDE_OCC 4
 // List entries staged per batch.
 #define SPH_BATCH 32
 // Candidates per 16-lane row of a tile: the largest tiles (fewest partly filled
@@ -86,10 +88,13 @@ __device__ inline float get_test(const Tile& L, int j, int lane)
 // every cycle (FP32 MFMA does not overlap with VALU work here): 7.4e3 VALU and
 // 208 MFMA instructions per leaf at 256^3 clustered, 2.1e4 VALU instructions
 // with a ballot loop over the particles per tile and lane = particle sums.
-// Stage at 256^3 clustered FP32C 9.3 -> 6.8 ms, at 64^3 FP64 2.6 -> 1.4 ms.
-template <typename T>
-__device__ void density_leaf_packed(const DensArgs& a, int A, typename ptile<T>::type& L, int lane)
+// Stage at 256^3 clustered FP32C 9.3 -> 6.3 ms, at 64^3 FP64 2.6 -> 1.2 ms.
+// With NW > 1 the waves of the workgroup share the leaf's list; wave 0 adds up
+// their sums.
+template <typename T, int NW>
+__device__ __forceinline__ void density_leaf_packed(const DensArgs& a, int A, typename ptile<T>::type* tiles, int lane, int wave)
 {
+    typename ptile<T>::type& L = tiles[wave];
     constexpr bool EXTRAP = sizeof(T) == 4;
     typedef typename vec4<T>::type V4;
     const V4* pos4 = (const V4*)a.pos4;
@@ -98,7 +103,8 @@ __device__ void density_leaf_packed(const DensArgs& a, int A, typename ptile<T>:
     const DomainInfo& I = a.di[a.l_dom[A]];
     const double hlim = fmin(fmin(I.L[0], I.L[1]), I.L[2]) / 3.0;
     const double s0min = fmin(fmin(I.s0[0], I.s0[1]), I.s0[2]);
-    const int e0 = a.l_off[A], e1 = a.l_off[A + 1];
+    const int ea = a.l_off[A], ne = a.l_off[A + 1] - ea;
+    const int e0 = ea + (int)((long long)ne * wave / NW), e1 = ea + (int)((long long)ne * (wave + 1) / NW);
     const double mg = *a.margin;  // list margin (see density_leaf)
     const double hlA = a.l_hlist[A] - mg;
     const bool vi = lane < nA;
@@ -106,7 +112,8 @@ __device__ void density_leaf_packed(const DensArgs& a, int A, typename ptile<T>:
     const bool act = vi && !a.conv[i];
     const unsigned long long amask = __ballot(act);
     if (amask == 0ull) {
-        if (lane == 0) a.l_active[A] = 0;
+        if (NW == 1 || wave == 0)
+            if (lane == 0) a.l_active[A] = 0;
         return;
     }
     const V4 pi = pos4[i];
@@ -190,6 +197,10 @@ __device__ void density_leaf_packed(const DensArgs& a, int A, typename ptile<T>:
     const uint32_t last = (uint32_t)(a.n - 1);
     int ncand = 0, eb = e0, p0 = 0, total = 0, start = 0;
     V4 o, pf;
+    auto load = [&](int p) {
+        o = L.e.o[stream_cell(p, start)];
+        pf = pos4[min((uint32_t)(p + lane + unpack_int(o.w)), last)];
+    };
     while (true) {
         if (p0 >= total) {  // next batch of cells
             for (total = 0; eb < e1 && total == 0; eb += SPH_BATCH) {
@@ -198,10 +209,7 @@ __device__ void density_leaf_packed(const DensArgs& a, int A, typename ptile<T>:
                                            [&](const ListEntry& E) { return E.dist < hA + mg; }, L.e, start);
             }
             p0 = 0;
-            if (total > 0) {
-                o = L.e.o[stream_cell(0, start)];
-                pf = pos4[min((uint32_t)(lane + unpack_int(o.w)), last)];
-            }
+            if (total > 0) load(0);
         }
         V4 q;
         unsigned long long mk = 0ull;
@@ -212,10 +220,7 @@ __device__ void density_leaf_packed(const DensArgs& a, int A, typename ptile<T>:
             q.w = pf.w;
             mk = __ballot((p0 + lane < total) & (box_d2<T>(q.x, q.y, q.z, bxl, byl, bzl, bxh, byh, bzh) < hA2));
             p0 += 64;
-            if (p0 < total) {
-                o = L.e.o[stream_cell(p0, start)];
-                pf = pos4[min((uint32_t)(p0 + lane + unpack_int(o.w)), last)];
-            }
+            if (p0 < total) load(p0);
         }
         const int nk = __popcll(mk);
         if (ncand + nk > 4 * DENS_ROW || total == 0) {
@@ -231,8 +236,20 @@ __device__ void density_leaf_packed(const DensArgs& a, int A, typename ptile<T>:
         ncand += nk;
     }
     wave_sync();
-    const bool left = dens_finish<T>(a, i, act, 0, 64, Hd, L.sw[lane], L.sd[lane], (double)L.s2[lane], L.cnt[lane], hlA,
-                                     hlim, s0min);
+    double sw = L.sw[lane], sd = L.sd[lane], s2 = (double)L.s2[lane];
+    int cnt = L.cnt[lane];
+    const double mi = a.m[i];
+    if (NW > 1) {
+        __syncthreads();
+        if (wave != 0) return;
+        for (int w = 1; w < NW; w++) {
+            sw += tiles[w].sw[lane];
+            sd += tiles[w].sd[lane];
+            s2 += (double)tiles[w].s2[lane];
+            cnt += tiles[w].cnt[lane];
+        }
+    }
+    const bool left = dens_finish<T>(a, i, act, 0, 64, Hd, sw, sd, s2, cnt, hlA, hlim, s0min, mi);
     const unsigned long long lm = __ballot(left);
     if (lane == 0) a.l_active[A] = lm ? 1 : 0;
     wave_sync();
@@ -392,7 +409,7 @@ __device__ void density_leaf(const DensArgs& a, int A, DTile<T>& L, int lane)
             wave_sync();
         }
         const bool left = dens_finish<T>(a, i, act, jg, CI, Hd, sw.total(), sd.total(), (double)s2, cnt, hlA, hlim,
-                                         s0min);
+                                         s0min, a.m[i]);
         const unsigned long long lm = __ballot(left);
         if (lm) any_left = true;
     }
@@ -414,20 +431,52 @@ __global__ __launch_bounds__(256) void k_density(DensArgs a)
 }
 
 
-// Packed density sweep over the leaves of at most 64 particles (box
-// pruning); the LDS is only the packed candidate buffer, so more waves fit
-// on a CU than with the two-phase tiles.
-template <typename T, int WPE>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, 8))) void k_density_packed(DensArgs a)
+// Leaf of workgroup b of a grid over the leaves (-1: none); a grid of single
+// waves (NW = 1) leaves those with long lists to the wide workgroups.
+template <int NW, typename Args>
+__device__ inline int tile_leaf(const Args& a, int b)
 {
-    __shared__ typename ptile<T>::type tile;
-    const int lane = threadIdx.x;
-    if (a.gate && uniform(*a.gate) != 0) return;
     const int nL = a.nl_dev ? uniform(*a.nl_dev) : a.n_leaves;
-    const int A = uniform(xcd_block(blockIdx.x, gridDim.x));
-    if (A >= nL) return;
-    if (!a.l_active[A] || a.l_count[A] > 64) return;
-    density_leaf_packed<T>(a, A, tile, lane);
+    const int A = uniform(xcd_block(b, gridDim.x));
+    if (A >= nL || (NW == 1 && a.l_off[A + 1] - a.l_off[A] > uniform(*a.wide_min))) return -1;
+    return A;
+}
+
+// The leaves with long lists (a.wide), or every leaf, by workgroups of NW
+// waves: work(A, wave).
+template <int NW, typename Args, typename Work>
+__device__ __forceinline__ void for_wide_leaves(const Args& a, Work work)
+{
+    const int wave = uniform(threadIdx.x >> 6);
+    if (!a.wide) {
+        const int A = tile_leaf<NW>(a, blockIdx.x);
+        if (A >= 0) work(A, wave);
+        return;
+    }
+    const int n = a.nl_dev ? uniform(*a.n_wide_dev) : a.n_wide;
+    for (int b = blockIdx.x; b < n; b += gridDim.x) {
+        work(uniform(a.wide[b]), wave);
+        __syncthreads();  // (the tiles are reused)
+    }
+}
+
+// Packed density sweep over the leaves of at most 64 particles (box
+// pruning), NW waves per leaf.
+template <typename T, int WPE, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, 8))) void k_density_packed(DensArgs a)
+{
+    __shared__ typename ptile<T>::type tiles[NW];
+    if (a.gate && uniform(*a.gate) != 0) return;
+    const int lane = threadIdx.x & 63;
+    auto leaf = [&](int A, int wave) __attribute__((always_inline)) {
+        if (a.l_active[A] && a.l_count[A] <= 64) density_leaf_packed<T, NW>(a, A, tiles, lane, wave);
+    };
+    if (NW > 1) {
+        for_wide_leaves<NW>(a, leaf);
+        return;
+    }
+    const int A = tile_leaf<NW>(a, blockIdx.x);
+    if (A >= 0) leaf(A, 0);
 }
 
 __global__ __launch_bounds__(256) void k_density_reset(int64_t n, int n_leaves, double* hlo, double* hhi, uint8_t* conv,
@@ -525,6 +574,10 @@ struct ForceArgs {
     const double* margin;  // list margin: twice the largest displacement since the lists were built
     const int* gate;    // graph mode: run only if *gate == 1 (NULL: always run)
     const int* nl_dev;  // graph mode: leaf count read from the device (NULL: n_leaves)
+    const int* wide;        // leaves with lists above *wide_min (NULL: all are taken as such)
+    const int* n_wide_dev;  // graph mode: their number
+    const int* wide_min;
+    int n_wide;
     int persistent;
 };
 
@@ -946,8 +999,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPH_FORCE_W
 // global atomics and each output is written once.  Candidate stream,
 // matrix-unit range tests (against H_i and H_j) and pair-parallel sums as in
 // the density, and bound like it: 1.08e4 VALU and 456 MFMA instructions per
-// leaf at 256^3 clustered (2.6e4 before), 12.9 -> 11.0 ms; 64^3 FP64 1.33 ->
-// 0.86 ms.
+// leaf at 256^3 clustered (2.6e4 before), 12.9 -> 10.2 ms; 64^3 FP64 1.33 ->
+// 0.70 ms.
 // ---------------------------------------------------------------------------
 template <typename T>
 struct GTile {
@@ -970,9 +1023,10 @@ struct GTile64 : GTile<double> {
 template <typename T> struct gtile { typedef GTile<T> type; };
 template <> struct gtile<double> { typedef GTile64 type; };
 
-template <typename T>
-__device__ void force_leaf_gather(const ForceArgs& a, int A, typename gtile<T>::type& L, int lane)
+template <typename T, int NW>
+__device__ __forceinline__ void force_leaf_gather(const ForceArgs& a, int A, typename gtile<T>::type* tiles, int lane, int wave)
 {
+    typename gtile<T>::type& L = tiles[wave];
     typedef typename vec4<T>::type V4;
     const V4* pos4 = (const V4*)a.pos4;
     const V4* fv4 = (const V4*)a.fv4;
@@ -980,10 +1034,11 @@ __device__ void force_leaf_gather(const ForceArgs& a, int A, typename gtile<T>::
     const int bA = a.l_begin[A], nA = a.l_count[A];
     const double oA[3] = {a.l_origin[3 * A], a.l_origin[3 * A + 1], a.l_origin[3 * A + 2]};
     const DomainInfo& I = a.di[a.l_dom[A]];
-    const int e0 = a.l_off[A], e1 = a.l_off[A + 1];
+    const int ea = a.l_off[A], ne = a.l_off[A + 1] - ea;
+    const int e0 = ea + (int)((long long)ne * wave / NW), e1 = ea + (int)((long long)ne * (wave + 1) / NW);
     const double mg = *a.margin;  // list margin (see density_leaf)
     const T big = T(1e30);
-    unsigned long long npairs = 0, ndens_w = 0;
+    unsigned long long npairs = 0, ndens_w = 0, nself = 0;
     for (int c0 = 0; c0 < nA; c0 += 64) {
         const int nc = min(64, nA - c0);
         const bool vi = lane < nc;
@@ -1007,6 +1062,7 @@ __device__ void force_leaf_gather(const ForceArgs& a, int A, typename gtile<T>::
             const float x = (float)q.x, y = (float)q.y, z = (float)q.z, h = (float)(Hi * sc);
             const float p2 = x * x + y * y + z * z;
             const bool on = vi && p2 < 1e30f;
+            nself += __popcll(__ballot(on));
             const float xi = on ? x : 0.f, yi = on ? y : 0.f, zi = on ? z : 0.f;
             const float ci = on ? p2 * (1.0f - PAIR_EPS) - 1e-30f : 1e30f;
             test_operand(xi, yi, zi, on ? ci - h * h * (1.0f + PAIR_EPS) : 1e30f, (float4*)L.cand, lane, b1);
@@ -1092,6 +1148,12 @@ __device__ void force_leaf_gather(const ForceArgs& a, int A, typename gtile<T>::
         uint32_t jp = 0;
         V4 o, pf;
         T hp;
+        auto load = [&](int p) {
+            o = L.e.o[stream_cell(p, start)];
+            jp = min((uint32_t)(p + lane + unpack_int(o.w)), last);
+            pf = pos4[jp];
+            hp = hf[jp];
+        };
         while (true) {
             if (p0 >= total) {  // next batch of cells
                 for (total = 0; eb < e1 && total == 0; eb += SPH_BATCH) {
@@ -1101,12 +1163,7 @@ __device__ void force_leaf_gather(const ForceArgs& a, int A, typename gtile<T>::
                                                L.e, start);
                 }
                 p0 = 0;
-                if (total > 0) {
-                    o = L.e.o[stream_cell(0, start)];
-                    jp = min((uint32_t)(lane + unpack_int(o.w)), last);
-                    pf = pos4[jp];
-                    hp = hf[jp];
-                }
+                if (total > 0) load(0);
             }
             V4 q;
             T h;
@@ -1123,12 +1180,7 @@ __device__ void force_leaf_gather(const ForceArgs& a, int A, typename gtile<T>::
                 mk = __ballot((p0 + lane < total) &
                               (box_d2<T>(q.x, q.y, q.z, bxl, byl, bzl, bxh, byh, bzh) < Rj * Rj));
                 p0 += 64;
-                if (p0 < total) {
-                    o = L.e.o[stream_cell(p0, start)];
-                    jp = min((uint32_t)(p0 + lane + unpack_int(o.w)), last);
-                    pf = pos4[jp];
-                    hp = hf[jp];
-                }
+                if (p0 < total) load(p0);
             }
             const int nk = __popcll(mk);
             if (ncand + nk > 4 * FORCE_ROW || total == 0) {
@@ -1150,41 +1202,56 @@ __device__ void force_leaf_gather(const ForceArgs& a, int A, typename gtile<T>::
         }
         wave_sync();
         npairs += (unsigned long long)nmax;
-        if (vi) {
-            a.ax[i] = L.sum[0][lane];
-            a.ay[i] = L.sum[1][lane];
-            a.az[i] = L.sum[2][lane];
-            a.dudt[i] = L.sum[3][lane];
-            if (a.nngb) a.nngb[i] = L.cnt[lane];
-            ndens_w += (unsigned long long)L.cnt[lane];
+        if (NW > 1) __syncthreads();
+        if (vi && wave == 0) {
+            double t[4];
+            for (int k = 0; k < 4; k++) t[k] = L.sum[k][lane];
+            int cnt = L.cnt[lane];
+            for (int w = 1; w < NW; w++) {
+                for (int k = 0; k < 4; k++) t[k] += tiles[w].sum[k][lane];
+                cnt += tiles[w].cnt[lane];
+            }
+            a.ax[i] = t[0];
+            a.ay[i] = t[1];
+            a.az[i] = t[2];
+            a.dudt[i] = t[3];
+            if (a.nngb) a.nngb[i] = cnt;
+            ndens_w += (unsigned long long)cnt;
         }
-        wave_sync();
+        if (NW > 1) __syncthreads();
+        else wave_sync();
     }
     npairs = wave_sum(npairs);
     ndens_w = wave_sum(ndens_w);
-    // ordered pairs, the particles themselves excluded
-    if (lane == 0 && npairs > (unsigned long long)nA) count_add(a.counters, PART_NFORCE, npairs - (unsigned long long)nA);
+    // ordered pairs, the particles themselves excluded (each is found by the
+    // wave that holds the leaf's own entry: the sum modulo 2^64 is right)
+    if (wave == 0) npairs -= nself;
+    if (lane == 0 && npairs) count_add(a.counters, PART_NFORCE, npairs);
     if (lane == 0 && ndens_w) count_add(a.counters, PART_NDENS_F, ndens_w);
 }
 
-template <typename T, int WPE>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, 8))) void k_force_gather(ForceArgs a)
+template <typename T, int WPE, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, 8))) void k_force_gather(ForceArgs a)
 {
-    __shared__ typename gtile<T>::type tile;
-    const int lane = threadIdx.x;
+    __shared__ typename gtile<T>::type tiles[NW];
+    const int lane = threadIdx.x & 63;
     if (a.gate && uniform(*a.gate) != 1) return;
-    const int nL = a.nl_dev ? uniform(*a.nl_dev) : a.n_leaves;
-    if (!a.persistent) {
-        const int A = uniform(xcd_block(blockIdx.x, gridDim.x));
-        if (A >= nL) return;
-        force_leaf_gather<T>(a, A, tile, lane);
+    if (NW > 1) {
+        for_wide_leaves<NW>(a, [&](int A, int wave) __attribute__((always_inline)) { force_leaf_gather<T, NW>(a, A, tiles, lane, wave); });
         return;
     }
+    if (!a.persistent) {
+        const int A = tile_leaf<NW>(a, blockIdx.x);
+        if (A >= 0) force_leaf_gather<T, NW>(a, A, tiles, lane, 0);
+        return;
+    }
+    const int nL = a.nl_dev ? uniform(*a.nl_dev) : a.n_leaves;
     int k = 0;
     for (int it = 0; it <= nL; it++) {
         const int A = xq_pop(&a.counters[XQ_FORCE], nL, k, lane);
         if (A < 0) break;
-        force_leaf_gather<T>(a, A, tile, lane);
+        if (a.l_off[A + 1] - a.l_off[A] > uniform(*a.wide_min)) continue;
+        force_leaf_gather<T, NW>(a, A, tiles, lane, 0);
     }
 }
 
@@ -1391,6 +1458,10 @@ static void dens_args(sph_ctx* c, const int* gate, bool graph, DensArgs& a, int&
     a.gate = gate;
     a.margin = (const double*)c->dparam.p;
     a.nl_dev = graph ? (const int*)c->flags.p + FI_NLEAVES : nullptr;
+    a.wide = (const int*)c->wide.p;
+    a.n_wide_dev = (const int*)c->flags.p + FI_NWIDE;
+    a.n_wide = graph ? 0 : c->n_wide;
+    a.wide_min = (const int*)c->flags.p + FI_WIDEMIN;
     if (graph) a.n_leaves = 0;  // read on the device
     const int nl = graph ? leaf_capacity(c) : c->n_leaves;
     nb = blocks_for(nl, WAVES_PER_WG);
@@ -1398,23 +1469,60 @@ static void dens_args(sph_ctx* c, const int* gate, bool graph, DensArgs& a, int&
 
 // The packed density and gather force kernels of the context's occupancy
 // target (FP64: the defaults only).
-static void launch_density_packed(sph_ctx* c, int nb, const DensArgs& a)
+// Workgroups of the wide launch and its waves per leaf; all: it takes every leaf.
+static int wide_grid(sph_ctx* c, bool graph, bool& all, int& waves)
 {
-    if (c->prm.precision == SPH_FP64) {
-        k_density_packed<double, SPH_DENS_WAVES64><<<nb, 64, 0, c->stream>>>(a);
+    const int nL = graph ? leaf_capacity(c) : c->n_leaves;
+    all = c->n_leaves <= SPH_WIDE_ALL;
+    waves = all && c->n_leaves > SPH_WIDE_FEW ? 4 : SPH_WIDE_WAVES;
+    // (a captured launch covers any number of long lists)
+    return all ? nL : graph ? std::min(nL, 1024) : c->n_wide;
+}
+
+static void launch_density_packed(sph_ctx* c, bool graph, DensArgs a)
+{
+    const bool f64 = c->prm.precision == SPH_FP64;
+    const int nL = graph ? leaf_capacity(c) : c->n_leaves;
+    bool all;
+    int waves;
+    const int nw = wide_grid(c, graph, all, waves);
+    if (all) a.wide = nullptr;
+    if (nw > 0 && waves == 4) {
+        if (f64) k_density_packed<double, SPH_DENS_WAVES64, 4><<<nw, 256, 0, c->stream>>>(a);
+        else k_density_packed<float, SPH_WIDE_OCC, 4><<<nw, 256, 0, c->stream>>>(a);
+    } else if (nw > 0) {
+        if (f64) k_density_packed<double, SPH_DENS_WAVES64, 8><<<nw, 512, 0, c->stream>>>(a);
+        else k_density_packed<float, SPH_WIDE_OCC, 8><<<nw, 512, 0, c->stream>>>(a);
+    }
+    if (all) return;
+    if (f64) {
+        k_density_packed<double, SPH_DENS_WAVES64, 1><<<nL, 64, 0, c->stream>>>(a);
         return;
     }
     switch (c->prm.waves_density ? c->prm.waves_density : SPH_DENS_WAVES) {
-    case 4: k_density_packed<float, 4><<<nb, 64, 0, c->stream>>>(a); return;
-    case 5: k_density_packed<float, 5><<<nb, 64, 0, c->stream>>>(a); return;
-    default: k_density_packed<float, 6><<<nb, 64, 0, c->stream>>>(a); return;
+    case 4: k_density_packed<float, 4, 1><<<nL, 64, 0, c->stream>>>(a); return;
+    case 5: k_density_packed<float, 5, 1><<<nL, 64, 0, c->stream>>>(a); return;
+    default: k_density_packed<float, 6, 1><<<nL, 64, 0, c->stream>>>(a); return;
     }
 }
 
-static void launch_force_gather(sph_ctx* c, int nb, const ForceArgs& a)
+static void launch_force_gather(sph_ctx* c, bool graph, int nb, ForceArgs a)
 {
-    if (c->prm.precision == SPH_FP64) k_force_gather<double, SPH_FORCEG_WAVES64><<<nb, 64, 0, c->stream>>>(a);
-    else k_force_gather<float, SPH_FORCEG_WAVES><<<nb, 64, 0, c->stream>>>(a);
+    const bool f64 = c->prm.precision == SPH_FP64;
+    bool all;
+    int waves;
+    const int nw = wide_grid(c, graph, all, waves);
+    if (all) a.wide = nullptr;
+    if (nw > 0 && waves == 4) {
+        if (f64) k_force_gather<double, SPH_FORCEG_WAVES64, 4><<<nw, 256, 0, c->stream>>>(a);
+        else k_force_gather<float, SPH_WIDE_OCC, 4><<<nw, 256, 0, c->stream>>>(a);
+    } else if (nw > 0) {
+        if (f64) k_force_gather<double, SPH_FORCEG_WAVES64, 8><<<nw, 512, 0, c->stream>>>(a);
+        else k_force_gather<float, SPH_WIDE_OCC, 8><<<nw, 512, 0, c->stream>>>(a);
+    }
+    if (all) return;
+    if (f64) k_force_gather<double, SPH_FORCEG_WAVES64, 1><<<nb, 64, 0, c->stream>>>(a);
+    else k_force_gather<float, SPH_FORCEG_WAVES, 1><<<nb, 64, 0, c->stream>>>(a);
 }
 
 // Density sweeps run as a grid of one wave per leaf in every execution mode:
@@ -1430,7 +1538,7 @@ static sph_status launch_density(sph_ctx* c, const int* gate, bool graph = false
     if (nb <= 0) return SPH_OK;
     const bool srt = c->prm.prune == SPH_PRUNE_SORTED;
     if (!srt) {
-        launch_density_packed(c, graph ? leaf_capacity(c) : c->n_leaves, a);
+        launch_density_packed(c, graph, a);
         SPH_CHECK_LAUNCH();
         // leaves above 64 particles (cells that cannot be split further):
         // the chunked two-phase kernel over a plain grid
@@ -1744,6 +1852,10 @@ static void force_args(sph_ctx* c, const int* gate, bool graph, ForceArgs& a, in
     a.gate = gate;
     a.margin = (const double*)c->dparam.p;
     a.nl_dev = graph ? (const int*)c->flags.p + FI_NLEAVES : nullptr;
+    a.wide = (const int*)c->wide.p;
+    a.n_wide_dev = (const int*)c->flags.p + FI_NWIDE;
+    a.n_wide = graph ? 0 : c->n_wide;
+    a.wide_min = (const int*)c->flags.p + FI_WIDEMIN;
     if (graph) a.n_leaves = 0;  // read on the device
     const int nl = graph ? leaf_capacity(c) : c->n_leaves;
     // the gather form runs one wave per workgroup
@@ -1759,7 +1871,7 @@ static sph_status launch_force(sph_ctx* c, const int* gate, bool graph = false)
     int nb = 0;
     force_args(c, gate, graph, a, nb);
     if (nb > 0 && c->prm.force_mode == SPH_FORCE_GATHER) {
-        launch_force_gather(c, nb, a);
+        launch_force_gather(c, graph, nb, a);
         SPH_CHECK_LAUNCH();
     } else if (nb > 0) {
         const bool srt = c->prm.prune == SPH_PRUNE_SORTED;
@@ -1923,6 +2035,7 @@ static std::vector<uint8_t> graph_key(sph_ctx* c, const double* u, const double*
     key_put(k, c->prm.prune);
     key_put(k, c->prm.exec_mode);
     key_put(k, (int)(c->max_leaf > 64));  // whether the big-leaf density pass is launched
+    key_put(k, (int)(c->n_leaves <= SPH_WIDE_ALL) + (int)(c->n_leaves <= SPH_WIDE_FEW));
     const void* pptrs[] = {c->pq.p, c->pR.p, c->plen.p, c->plist.p, c->prem.p, c->ch_p0.p, c->ch_n.p,
                            c->ch_uo.p, c->ch_ro.p, c->ch_U.p, c->P.domain, c->P.nngb};
     key_put(k, pptrs);

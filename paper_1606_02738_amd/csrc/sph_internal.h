@@ -124,7 +124,24 @@ enum {
 
 // Slots of the int[64] flags buffer.
 enum { FI_FLAGS = 0, FI_SCRATCH = 8, FI_NCHILD = 9, FI_NLEAVES = 10, FI_NLIST = 11, FI_GATE = 12, FI_MAXLEAF = 13, FI_MAXLIST = 14, FI_PLROWS = 15, FI_WOVF = 16,
-       FI_WINC = 17, FI_NCHUNK = 18, FI_NFLAGS = 64 };
+       FI_WINC = 17, FI_NCHUNK = 18, FI_NWIDE = 19, FI_WIDEMIN = 20, FI_NFLAGS = 64 };
+
+// Waves that share a leaf with a long list, and the list length from which
+// they do: one wave on the longest lists of a clustered box (800 entries, the
+// mean is 75) outlasts the rest of the grid.  256 entries, or 2.5 times the mean
+// (at least 128) in boxes of fewer leaves, where the grid is over sooner.
+// Stages at 127^3 clustered 4.8 -> 4.3 ms (4 waves 4.5, 2 waves 5.0), at 64^3 FP64
+// 2.5 -> 2.0 ms. 
+#define SPH_WIDE_WAVES 8
+#define SPH_WIDE_MIN 128
+#define SPH_WIDE_MAX 256
+#define SPH_WIDE_MANY 65536
+// Up to SPH_WIDE_ALL leaves every leaf is shared, by SPH_WIDE_WAVES waves or (more
+// than SPH_WIDE_FEW) by 4: one wave each leaves most of the chip idle.  32^3
+// lattice, 648 leaves: density stage 0.148 -> 0.102 ms, force 0.082 -> 0.060
+// (8 waves 0.126, 0.078); 12^3: 0.085 -> 0.065, 0.026 -> 0.019.
+#define SPH_WIDE_ALL 2048
+#define SPH_WIDE_FEW 256
 
 // Counters written by kernels (device, int64).
 enum { CNT_UNCONV = 0, CNT_NDENS = 1, CNT_NFORCE = 2, CNT_NPLIST = 3, CNT_DEVAL = 5, CNT_NPAIR = 6, CNT_NDENS_F = 7, CNT_GSWEEPS = 8, CNT_UHIST = 9, CNT_N = 16 };

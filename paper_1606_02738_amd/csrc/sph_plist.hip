@@ -787,7 +787,7 @@ __global__ __launch_bounds__(64) void k_density_chunks(DensChunkArgs la)
         // the list holds every neighbour within R_i while the particles stay
         // within their skins (checked at every drift)
         const double hlA = (double)((const T*)la.R)[i];
-        left = dens_newton<EXTRAP>(a, i, Hd, sw.total(), sd.total(), (double)s2, cnt, hlA, hlim, s0min, conv);
+        left = dens_newton<EXTRAP>(a, i, Hd, sw.total(), sd.total(), (double)s2, cnt, hlA, hlim, s0min, a.m[i], conv);
     }
     dens_count(a, act, left, conv, cnt, lane);
 }

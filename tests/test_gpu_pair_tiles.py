@@ -74,3 +74,16 @@ def test_bad_velocity_stays_in_its_range(bad):
     for f in ("ax", "ay", "az", "dudt", "rho"):
         assert np.array_equal(a[f][far], b[f][far]), f
     assert np.isfinite(b["ax"]).all()
+
+
+@pytest.mark.parametrize("prec,mode", [("fp64", "grid"), ("fp64", "persistent"), ("fp32c", "persistent")])
+def test_long_lists_are_shared_among_waves(prec, mode):
+    """More than 2048 leaves, so that one wave takes a leaf and several waves
+    the leaves with long lists (next to a halo); below that, in the other
+    tests of this file, several waves take every leaf."""
+    log("case long lists %s %s" % (prec, mode))
+    d = gen.clustered(32, n_halos=4, seed=35, halo_frac=0.6)
+    g, st = gpu_run(d, precision=prec, exec_mode=mode, n_split=8, force="gather")
+    assert st["n_leaves"] > 2048
+    assert_close(g, oracle_run(d), TOL_FP64 if prec == "fp64" else TOL_FP32, counts_exact=prec == "fp64",
+                 stats=st if prec == "fp64" else None)
