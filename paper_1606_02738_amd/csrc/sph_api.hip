@@ -161,12 +161,20 @@ sph_status sph_create(const sph_params* params, void* workspace, size_t bytes, v
     c->prm.boxes = nullptr;
     c->stream = (hipStream_t)hip_stream;
     sph_status s = SPH_OK;
-    if (s == SPH_OK) s = buf_ensure(c->flags, FI_NFLAGS * sizeof(int));
-    if (s == SPH_OK) s = buf_ensure(c->counters, CNT_TOTAL * 8);
-    if (s == SPH_OK) s = buf_ensure(c->dparam, 8 * sizeof(double));
-    if (s == SPH_OK && hipMemsetAsync(c->dparam.p, 0, 8 * sizeof(double), c->stream) != hipSuccess) s = SPH_ERR_HIP;
+    const size_t b_dstat = ((size_t)p.n_domains * 24 + 127) & ~(size_t)127, b_dparam = 8 * sizeof(double),
+                 b_flags = FI_NFLAGS * sizeof(int), b_state = b_dstat + 128 + b_flags + CNT_TOTAL * 8;
+    if (s == SPH_OK) s = buf_ensure(c->state, b_state);
+    if (s == SPH_OK) {
+        char* q = (char*)c->state.p;
+        // (parts of the block: not given back by themselves)
+        auto part = [](DevBuf& d, char* at, size_t bytes) { d.p = at, d.cap = bytes, d.pool = nullptr; };
+        part(c->dstat, q, b_dstat);
+        part(c->dparam, q + b_dstat + 128 - b_dparam, b_dparam);
+        part(c->flags, q + b_dstat + 128, b_flags);
+        part(c->counters, q + b_dstat + 128 + b_flags, CNT_TOTAL * 8);
+    }
+    if (s == SPH_OK && hipMemsetAsync(c->state.p, 0, b_state, c->stream) != hipSuccess) s = SPH_ERR_HIP;
     if (s == SPH_OK) s = buf_ensure(c->dom_d, (size_t)p.n_domains * sizeof(DomainInfo));
-    if (s == SPH_OK) s = buf_ensure(c->dstat, (size_t)p.n_domains * 24);
     for (int k = 0; k < 8 && s == SPH_OK; k++)
         if (hipEventCreate(&c->ev[k]) != hipSuccess) s = SPH_ERR_HIP;
     for (int k = 0; k < 4 && s == SPH_OK; k++)
@@ -184,8 +192,6 @@ sph_status sph_create(const sph_params* params, void* workspace, size_t bytes, v
             c->side = nullptr;
         }
     }
-    if (s == SPH_OK && hipMemsetAsync(c->flags.p, 0, FI_NFLAGS * sizeof(int), c->stream) != hipSuccess) s = SPH_ERR_HIP;
-    if (s == SPH_OK && hipMemsetAsync(c->counters.p, 0, CNT_TOTAL * 8, c->stream) != hipSuccess) s = SPH_ERR_HIP;
     if (s != SPH_OK) {
         sph_destroy(c);
         return s;
@@ -209,7 +215,7 @@ sph_status sph_destroy(sph_ctx* c)
                      &c->nchild, &c->coff, &c->lvl_cmap, &c->lvl_bnd, &c->leafmark, &c->leafscan, &c->leaf_node, &c->l_begin, &c->l_count,
                      &c->l_origin, &c->l_lo, &c->l_hi, &c->l_hlist, &c->l_dom, &c->l_off, &c->l_active, &c->l_sorted,
                      &c->l_cnt, &c->list, &c->wide, &c->pos4, &c->fv4, &c->hf, &c->skey, &c->sidx,
-                     &c->hlo, &c->hhi, &c->conv, &c->flags, &c->counters,
+                     &c->hlo, &c->hhi, &c->conv, &c->state, &c->flags, &c->counters,
                      &c->scan_tmp, &c->rs_hist, &c->sums, &c->dsum_part, &c->fgrid, &c->fcount, &c->mlp_X, &c->mlp_hprev, &c->mlp_params, &c->mlp_packed, &c->mlp_m, &c->mlp_v, &c->ds_count, &c->dparam, &c->walk_scratch, &c->walk_ovf, &c->walk_link,
                      &c->pq, &c->pR, &c->plist, &c->prem, &c->plen, &c->pskin, &c->pq0, &c->pext, &c->pbox,
                      &c->ch_base, &c->ch_p0, &c->ch_n, &c->ch_uo, &c->ch_ro, &c->ch_U};

@@ -15,6 +15,31 @@
 // Validation: finite inputs, positive m and H, positions inside [0,L) of the
 // particle's box; per-box largest and smallest H.
 // ---------------------------------------------------------------------------
+// The boxes' constants (up to SET_DOMAINS, else they are copied), and for the
+// start of a build the cleared flags, H ranges and displacement margin; at the
+// second call (n >= 0) with one box its particle range.
+#define SET_DOMAINS 16
+struct DomainSet {
+    DomainInfo d[SET_DOMAINS];
+};
+__global__ __launch_bounds__(64) void k_set_domains(DomainSet S, int nd, DomainInfo* di, unsigned long long* dstat,
+                                                    double* dparam, int* flags, int n, int* ranges)
+{
+    const int t = threadIdx.x;
+    if (t < nd && nd <= SET_DOMAINS) di[t] = S.d[t];
+    if (n >= 0) {
+        if (nd == 1 && t < 2) ranges[t] = t * n;
+        return;
+    }
+    for (int d = t; d < nd; d += 64) {
+        dstat[3 * d] = 0ull;
+        dstat[3 * d + 1] = (unsigned long long)__double_as_longlong(INFINITY);
+        dstat[3 * d + 2] = 0ull;
+    }
+    for (int k = t; k < FI_NFLAGS; k += 64) flags[k] = 0;
+    if (t == 0) dparam[0] = 0.0;
+}
+
 __device__ inline void flush_hrange(unsigned long long* dstat, int d, double hmx, double hmn, unsigned long long cnt)
 {
     atomicMax(&dstat[3 * d], (unsigned long long)__double_as_longlong(hmx));
@@ -194,6 +219,30 @@ __global__ __launch_bounds__(256) void k_copy8(int64_t n, const uint64_t* __rest
         *(uint4*)(dst + i0 + 2) = b;
     } else {
         for (int64_t i = i0; i < n; i++) dst[i] = src[i];
+    }
+}
+
+// All arrays of a permutation in two launches (few particles: the launches
+// cost more than the bytes): workgroup row y gathers array y into its part of
+// tmp, then writes it back.  The 8-byte arrays first, then (d4 != NULL) one of
+// 4 bytes.
+struct PermArrays {
+    uint64_t* a[18];
+    uint32_t* d4;
+    int n8;
+};
+__global__ __launch_bounds__(256) void k_gather_all(int n, const uint32_t* __restrict__ perm, PermArrays P,
+                                                    uint64_t* __restrict__ tmp, int back)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, y = blockIdx.y;
+    if (i >= n) return;
+    uint64_t* t = tmp + (size_t)y * n + i;
+    if (y < P.n8) {
+        if (back) P.a[y][i] = *t;
+        else *t = P.a[y][perm[i]];
+    } else {
+        if (back) P.d4[i] = (uint32_t)*t;
+        else *t = P.d4[perm[i]];
     }
 }
 
@@ -379,14 +428,9 @@ __global__ __launch_bounds__(256) void k_level_stats(Node* nodes, int level_star
     }
 }
 
-// Whether each cell of the level is split and into how many children.  One
-// thread per cell.
-__global__ __launch_bounds__(256) void k_level_split(Node* nodes, int level_start, int n_level, int D, int n_split,
-                                                     double h_ratio, const int* __restrict__ bnd, int* nchild)
+// Whether a cell (the k-th of its level) is split and into how many children.
+__device__ inline int split_cell(Node* nd, int k, int D, int n_split, double h_ratio, const int* bnd)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n_level) return;
-    Node* nd = &nodes[level_start + k];
     const bool wide = extent_too_large(*nd, h_ratio);
     const bool split = !nd->merged && nd->level < D && (nd->count > n_split || wide);
     int nc = 0;
@@ -395,26 +439,28 @@ __global__ __launch_bounds__(256) void k_level_split(Node* nodes, int level_star
         for (int q = 0; q < 9; q++) bq[q] = bnd[9 * k + q];
         nc = child_groups(bq, n_split, !wide, gq, gb, gc);
     }
-    nchild[k] = nc;
     nd->n_child = nc;
     nd->first_child = -1;
+    return nc;
 }
 
-// The children of the split cells, at the scanned offsets.  One thread per
-// cell.
-__global__ __launch_bounds__(256) void k_emit_children(Node* nodes, int level_start, int n_level, const int* __restrict__ coff,
-                                                       int child_base, int D, int n_split, double h_ratio,
-                                                       const int* __restrict__ bnd)
+// ... one thread per cell.
+__global__ __launch_bounds__(256) void k_level_split(Node* nodes, int level_start, int n_level, int D, int n_split,
+                                                     double h_ratio, const int* __restrict__ bnd, int* nchild)
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= n_level) return;
-    Node* nd = &nodes[level_start + k];
-    if (nd->n_child == 0) return;
+    nchild[k] = split_cell(&nodes[level_start + k], k, D, n_split, h_ratio, bnd);
+}
+
+// The children of a split cell, from node `out`; bnd: its octant bounds.
+__device__ inline void emit_cell(Node* nodes, int node, int out, int D, int n_split, double h_ratio, const int* bnd)
+{
+    Node* nd = &nodes[node];
     const uint64_t step = 1ull << (3 * (D - nd->level - 1));
     int bq[9], gq[8], gb[8], gc[8];
-    for (int q = 0; q < 9; q++) bq[q] = bnd[9 * k + q];
+    for (int q = 0; q < 9; q++) bq[q] = bnd[q];
     const int ng = child_groups(bq, n_split, !extent_too_large(*nd, h_ratio), gq, gb, gc);
-    const int out = child_base + coff[k];
     nd->first_child = out;
     for (int g = 0; g < ng; g++) {
         const int q = gq[g];
@@ -441,6 +487,81 @@ __global__ __launch_bounds__(256) void k_emit_children(Node* nodes, int level_st
         ch.pad = 0;
         nodes[out + g] = ch;
     }
+}
+
+// ... of a level, at the scanned offsets.  One thread per cell.
+__global__ __launch_bounds__(256) void k_emit_children(Node* nodes, int level_start, int n_level, const int* __restrict__ coff,
+                                                       int child_base, int D, int n_split, double h_ratio,
+                                                       const int* __restrict__ bnd)
+{
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= n_level || nodes[level_start + k].n_child == 0) return;
+    emit_cell(nodes, level_start + k, child_base + coff[k], D, n_split, h_ratio, bnd + 9 * k);
+}
+
+// Levels of few cells by one workgroup: k_level_chunks, its scan and
+// k_chunk_map in one launch, k_level_split, its scan and k_emit_children in
+// another.
+#define LEVEL_ONE 4096
+// Exclusive scan over the 1024 threads of the workgroup; `all`: the total.
+__device__ inline int wg_scan(int v, int* wsum, int& all)
+{
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int incl = v;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int t = __shfl_up(incl, off);
+        if (lane >= off) incl += t;
+    }
+    __syncthreads();
+    if (lane == 63) wsum[w] = incl;
+    __syncthreads();
+    int ex = incl - v;
+    all = 0;
+    for (int q = 0; q < 16; q++) {
+        if (q < w) ex += wsum[q];
+        all += wsum[q];
+    }
+    return ex;
+}
+
+__global__ __launch_bounds__(1024) void k_level_chunks_one(const Node* __restrict__ nodes, int level_start, int n_level,
+                                                           int* coff, int* cmap, int* bnd, int* n_chunks)
+{
+    __shared__ int wsum[16];
+    int base = 0;
+    for (int k0 = 0; k0 < n_level; k0 += 1024) {
+        const int k = k0 + threadIdx.x;
+        int b = 0, c = 0;
+        if (k < n_level) {
+            b = nodes[level_start + k].begin;
+            c = nodes[level_start + k].count;
+            for (int q = 0; q < 9; q++) bnd[9 * k + q] = b + c;
+        }
+        const int nc = (c + STATS_CHUNK - 1) / STATS_CHUNK;
+        int all;
+        const int o = base + wg_scan(nc, wsum, all);
+        if (k < n_level) coff[k] = o;
+        for (int j = 0; j < nc; j++) cmap[o + j] = k;
+        base += all;
+    }
+    if (threadIdx.x == 0) *n_chunks = base;
+}
+
+__global__ __launch_bounds__(1024) void k_level_split_one(Node* nodes, int level_start, int n_level, int child_base,
+                                                          int D, int n_split, double h_ratio,
+                                                          const int* __restrict__ bnd, int* n_children)
+{
+    __shared__ int wsum[16];
+    int base = 0;
+    for (int k0 = 0; k0 < n_level; k0 += 1024) {
+        const int k = k0 + threadIdx.x;
+        const int nc = k < n_level ? split_cell(&nodes[level_start + k], k, D, n_split, h_ratio, bnd) : 0;
+        int all;
+        const int o = base + wg_scan(nc, wsum, all);
+        if (nc > 0) emit_cell(nodes, level_start + k, child_base + o, D, n_split, h_ratio, bnd + 9 * k);
+        base += all;
+    }
+    if (threadIdx.x == 0) *n_children = base;
 }
 
 __global__ __launch_bounds__(256) void k_mark_leaves(const Node* __restrict__ nodes, int n_nodes, int* leafmark)
@@ -633,6 +754,25 @@ __global__ __launch_bounds__(256) void k_wnext(const Node* __restrict__ nodes, i
     if (nd.n_child == 0) return;
     const int pn = w[p].next;
     for (int q = 0; q < nd.n_child; q++) w[nd.first_child + q].next = (q + 1 < nd.n_child) ? nd.first_child + q + 1 : pn;
+}
+
+// All levels by one workgroup (few cells); level l is [off[l], off[l + 1]).
+struct LevelOffsets {
+    int n, off[SPH_MAX_DEPTH + 3];
+};
+__global__ __launch_bounds__(1024) void k_wnext_all(const Node* __restrict__ nodes, LevelOffsets L, WNode* w)
+{
+    for (int l = 0; l < L.n; l++) {
+        for (int p = L.off[l] + threadIdx.x; p < L.off[l + 1]; p += blockDim.x) {
+            const Node& nd = nodes[p];
+            if (nd.n_child == 0) continue;
+            const int pn = w[p].next;
+            for (int q = 0; q < nd.n_child; q++)
+                w[nd.first_child + q].next = (q + 1 < nd.n_child) ? nd.first_child + q + 1 : pn;
+        }
+        __threadfence_block();
+        __syncthreads();
+    }
 }
 
 __device__ inline float box_dist_f(const float* alo, const float* ahi, const float* blo, const float* bhi,
@@ -1122,9 +1262,33 @@ static sph_status read_int(sph_ctx* c, const int* dptr, int* out)
 // has a second stream and side_tmp (8 bytes per particle) is given, on that
 // stream, after the sort (an event) and joined back by perm_join before
 // their first reader, so that they move while the octree is built.
+//
+// Up to PERM_FEW particles all arrays move in two launches instead, where the
+// workspace has the room (32^3: 28 launches of 2.5 us each, 8 us apart).
+#define PERM_FEW 131072
 static sph_status permute_all(sph_ctx* c, const uint32_t* perm, void* side_tmp)
 {
     const int64_t n = c->n;
+    if (n <= PERM_FEW && !c->mlp_pending) {
+        const bool out = !c->dens_outputs_dead;
+        PermArrays P{};
+        double* all[] = {c->P.x, c->P.y, c->P.z, c->P.H, c->P.vx, c->P.vy, c->P.vz, c->P.u, c->P.m,
+                         out ? c->P.rho : nullptr, out ? c->P.drho_dH : nullptr, out ? c->P.omega : nullptr,
+                         out ? c->P.P : nullptr, c->P.ax, c->P.ay, c->P.az, c->P.dudt, (double*)c->P.id};
+        for (double* a : all)
+            if (a) P.a[P.n8++] = (uint64_t*)a;
+        P.d4 = (uint32_t*)c->P.domain;
+        const int rows = P.n8 + (P.d4 ? 1 : 0);
+        DevBuf t;
+        if (buf_ensure(t, (size_t)rows * n * 8) == SPH_OK) {
+            const dim3 g(blocks_for(n, 256), rows);
+            k_gather_all<<<g, 256, 0, c->stream>>>((int)n, perm, P, (uint64_t*)t.p, 0);
+            k_gather_all<<<g, 256, 0, c->stream>>>((int)n, perm, P, (uint64_t*)t.p, 1);
+            buf_free(t);  // (its next owner's work follows on the stream)
+            SPH_CHECK_LAUNCH();
+            return SPH_OK;
+        }
+    }
     SPH_TRY(buf_ensure(c->tmp, (size_t)n * 8));
     // rho, drho_dH, omega and P follow their particles unless the caller's
     // next stages rewrite them before reading (the build inside a step)
@@ -1273,6 +1437,14 @@ sph_status node_hmax_all(sph_ctx* c, bool set_hlist)
     return SPH_OK;
 }
 
+// Counters of the walk, and the end of its counts (the walks write every leaf's).
+__global__ void k_relist_clear(int* count_end, int* flags)
+{
+    const int f[] = {FI_MAXLIST, FI_WOVF, FI_WINC, FI_NWIDE};
+    if (threadIdx.x < 4) flags[f[threadIdx.x]] = 0;
+    if (threadIdx.x == 0) *count_end = 0;
+}
+
 // Leaves with long lists, for the kernels that share them among waves (in no
 // particular order: each is worked on by itself).
 __global__ __launch_bounds__(256) void k_wide_list(int n_leaves, const int* __restrict__ l_off, int* wide, int* n_wide,
@@ -1294,7 +1466,8 @@ sph_status relist(sph_ctx* c)
     const int nL = c->n_leaves;
     int* counts = (int*)c->l_off.p;
     int* flags = (int*)c->flags.p;
-    SPH_CHECK_HIP(hipMemsetAsync(counts, 0, (size_t)(nL + 1) * sizeof(int), c->stream));
+    k_relist_clear<<<1, 64, 0, c->stream>>>(counts + nL, flags);
+    SPH_CHECK_LAUNCH();
     const int with_dir = c->prm.prune == SPH_PRUNE_SORTED;
     // the gather-form force needs every leaf within either radius in both lists
     const int sym = c->prm.force_mode == SPH_FORCE_GATHER;
@@ -1310,8 +1483,6 @@ sph_status relist(sph_ctx* c)
         SPH_TRY(buf_ensure(c->walk_scratch, (size_t)nL * cap * sizeof(ListEntry)));
         SPH_TRY(buf_ensure(c->walk_ovf, (size_t)ovf_chunks * 64 * sizeof(ListEntry)));
         SPH_TRY(buf_ensure(c->walk_link, (2 * (size_t)nL + ovf_chunks) * sizeof(int)));
-        SPH_CHECK_HIP(hipMemsetAsync(flags + FI_MAXLIST, 0, sizeof(int), c->stream));
-        SPH_CHECK_HIP(hipMemsetAsync(flags + FI_WOVF, 0, 2 * sizeof(int), c->stream));
         // one wave per leaf (stack entries hold node << 5)
         if (c->n_nodes < (1 << 27)) {
             k_walk_wave<<<blocks_for(nL, 4), 256, 0, c->stream>>>(
@@ -1337,7 +1508,6 @@ sph_status relist(sph_ctx* c)
     const bool wide = nL > SPH_WIDE_ALL && c->prm.prune == SPH_PRUNE_BOX && c->prm.lists == SPH_LISTS_CELL;
     if (wide) {
         SPH_TRY(buf_ensure(c->wide, (size_t)nL * sizeof(int)));
-        SPH_CHECK_HIP(hipMemsetAsync(flags + FI_NWIDE, 0, sizeof(int), c->stream));
         k_wide_list<<<blocks_for(nL, 256), 256, 0, c->stream>>>(nL, counts, (int*)c->wide.p, flags + FI_NWIDE,
                                                          flags + FI_WIDEMIN);
         SPH_CHECK_LAUNCH();
@@ -1359,6 +1529,7 @@ sph_status relist(sph_ctx* c)
         SPH_CHECK_LAUNCH();
     }
     if (!one_pass || incomplete > 0) {
+        c->rewalked = true;
         // leaves that found no free overflow chunk (all leaves without the
         // one pass): walked again, writing at the scanned offsets
         k_walk<1><<<blocks_for(nL, 128), 128, 0, c->stream>>>(
@@ -1382,6 +1553,22 @@ sph_status relist(sph_ctx* c)
     return SPH_OK;
 }
 
+// c->dom_h to the device; n < 0: the start of a build, else its second call.
+static sph_status set_domains(sph_ctx* c, int n)
+{
+    const int nd = c->prm.n_domains;
+    DomainSet S;
+    if (nd <= SET_DOMAINS) memcpy(S.d, c->dom_h.data(), nd * sizeof(DomainInfo));
+    else
+        SPH_CHECK_HIP(hipMemcpyAsync(c->dom_d.p, c->dom_h.data(), nd * sizeof(DomainInfo), hipMemcpyHostToDevice,
+                                     c->stream));
+    if (n >= 0 && nd > SET_DOMAINS) return SPH_OK;
+    k_set_domains<<<1, 64, 0, c->stream>>>(S, nd, (DomainInfo*)c->dom_d.p, (unsigned long long*)c->dstat.p,
+                                           (double*)c->dparam.p, (int*)c->flags.p, n, (int*)c->dranges.p);
+    SPH_CHECK_LAUNCH();
+    return SPH_OK;
+}
+
 sph_status build_all(sph_ctx* c)
 {
     const int64_t n = c->n;
@@ -1393,17 +1580,9 @@ sph_status build_all(sph_ctx* c)
     c->margin_h = 0.0;
     c->steps_since_build = 0;
     c->n_builds++;
-    SPH_CHECK_HIP(hipMemcpyAsync(c->dparam.p, &c->margin_h, sizeof(double), hipMemcpyHostToDevice, c->stream));
 
     // 1. validate, per-box H range
-    SPH_CHECK_HIP(hipMemsetAsync(flags, 0, FI_NFLAGS * sizeof(int), c->stream));
     std::vector<unsigned long long> dstat_h(3 * nd);
-    for (int d = 0; d < nd; d++) {
-        dstat_h[3 * d] = 0ull;
-        dstat_h[3 * d + 2] = 0ull;
-        double inf = INFINITY;
-        memcpy(&dstat_h[3 * d + 1], &inf, 8);
-    }
     // box extents are needed for validation before the grid is known
     c->dom_h.resize(nd);
     for (int d = 0; d < nd; d++) {
@@ -1411,16 +1590,22 @@ sph_status build_all(sph_ctx* c)
         memset(&I, 0, sizeof(I));
         for (int a = 0; a < 3; a++) I.L[a] = c->boxes[3 * d + a];
     }
-    SPH_CHECK_HIP(hipMemcpyAsync(c->dom_d.p, c->dom_h.data(), nd * sizeof(DomainInfo), hipMemcpyHostToDevice, c->stream));
-    SPH_CHECK_HIP(hipMemcpyAsync(c->dstat.p, dstat_h.data(), 3 * nd * 8, hipMemcpyHostToDevice, c->stream));
+    SPH_TRY(set_domains(c, -1));
     k_validate<<<std::min(blocks_for(n, 256), 2048), 256, 0, c->stream>>>(n, c->P.x, c->P.y, c->P.z, c->P.H, c->P.m, c->P.domain, nd,
                                                         (const DomainInfo*)c->dom_d.p,
                                                         (unsigned long long*)c->dstat.p, flags);
     SPH_CHECK_LAUNCH();
-    int fl = 0;
-    SPH_CHECK_HIP(hipMemcpyAsync(dstat_h.data(), c->dstat.p, 3 * nd * 8, hipMemcpyDeviceToHost, c->stream));
-    SPH_TRY(read_int(c, flags, &fl));
-    if (fl & FLAG_INVALID) return SPH_ERR_INVALID;
+    {
+        // the H ranges and the flags, one copy
+        const size_t to_flags = (size_t)((char*)c->flags.p - (char*)c->dstat.p);
+        std::vector<char> st(to_flags + sizeof(int));
+        SPH_CHECK_HIP(hipMemcpyAsync(st.data(), c->dstat.p, st.size(), hipMemcpyDeviceToHost, c->stream));
+        SPH_CHECK_HIP(hipStreamSynchronize(c->stream));
+        memcpy(dstat_h.data(), st.data(), (size_t)nd * 24);
+        int fl;
+        memcpy(&fl, st.data() + to_flags, sizeof(int));
+        if (fl & FLAG_INVALID) return SPH_ERR_INVALID;
+    }
     // particle lists: the largest list radius and skin of each box
     std::vector<double> pbox;
     if (c->prm.lists == SPH_LISTS_PARTICLE) {
@@ -1496,7 +1681,8 @@ sph_status build_all(sph_ctx* c)
     D = std::min(D, (63 - top_bits) / 3);
     c->D = D;
     c->key_bits = top_bits + 3 * D;
-    SPH_CHECK_HIP(hipMemcpyAsync(c->dom_d.p, c->dom_h.data(), nd * sizeof(DomainInfo), hipMemcpyHostToDevice, c->stream));
+    SPH_TRY(buf_ensure(c->dranges, (size_t)(nd + 1) * sizeof(int)));
+    SPH_TRY(set_domains(c, (int)n));
 
     // 3. Morton keys, radix sort, permutation of the caller's arrays
     for (int q = 0; q < 2; q++) {
@@ -1518,8 +1704,7 @@ sph_status build_all(sph_ctx* c)
         ~PermJoin() { perm_join(c); }
     } join_on_exit{c};
     SPH_TRY(permute_all(c, (const uint32_t*)c->vals[res].p, c->keys[res ^ 1].p));
-    SPH_TRY(buf_ensure(c->dranges, (size_t)(nd + 1) * sizeof(int)));
-    SPH_TRY(domain_ranges(c));
+    if (nd > 1) SPH_TRY(domain_ranges(c));
 
     // 4. octree, level by level
     size_t cap = std::max<size_t>((size_t)top * 2 + 1024, (size_t)(n / 8) + 1024);
@@ -1546,24 +1731,37 @@ sph_status build_all(sph_ctx* c)
         int* ccoff = (int*)c->coff.p;
         int* bnd = (int*)c->lvl_bnd.p;
         const int nbl = blocks_for(n_level, 256);
-        k_level_chunks<<<nbl, 256, 0, c->stream>>>((const Node*)c->nodes.p, level_start, n_level, nchild, bnd);
+        const bool one = n_level <= LEVEL_ONE;
+        if (one) {
+            k_level_chunks_one<<<1, 1024, 0, c->stream>>>((const Node*)c->nodes.p, level_start, n_level, ccoff,
+                                                          (int*)c->lvl_cmap.p, bnd, flags + FI_NCHUNK);
+        } else {
+            k_level_chunks<<<nbl, 256, 0, c->stream>>>((const Node*)c->nodes.p, level_start, n_level, nchild, bnd);
+            SPH_CHECK_LAUNCH();
+            SPH_TRY(scan_exclusive(c, nchild, ccoff, n_level, flags + FI_NCHUNK));
+            k_chunk_map<<<nbl, 256, 0, c->stream>>>(nchild, ccoff, n_level, (int*)c->lvl_cmap.p);
+        }
         SPH_CHECK_LAUNCH();
-        SPH_TRY(scan_exclusive(c, nchild, ccoff, n_level, flags + FI_NCHUNK));
-        k_chunk_map<<<nbl, 256, 0, c->stream>>>(nchild, ccoff, n_level, (int*)c->lvl_cmap.p);
-        SPH_CHECK_LAUNCH();
-        k_level_stats<<<2048, 256, 0, c->stream>>>((Node*)c->nodes.p, level_start, level, ccoff,
+        const int nstat = (int)std::min<int64_t>(2048, (n / STATS_CHUNK + n_level + 3) / 4);
+        k_level_stats<<<nstat, 256, 0, c->stream>>>((Node*)c->nodes.p, level_start, level, ccoff,
                                                    (const int*)c->lvl_cmap.p, flags + FI_NCHUNK, keys, c->P.x, c->P.y,
                                                    c->P.z, c->P.H, D, bnd);
         SPH_CHECK_LAUNCH();
-        k_level_split<<<nbl, 256, 0, c->stream>>>((Node*)c->nodes.p, level_start, n_level, D, c->prm.n_split, h_ratio,
-                                                  bnd, nchild);
-        SPH_CHECK_LAUNCH();
-        SPH_TRY(scan_exclusive(c, nchild, nchild, n_level, flags + FI_NCHILD));
         // the children go at the scanned offsets, whatever their total: when
         // the node buffer holds 8 per cell of the level (the most a split
         // makes), they are written while the host reads the total
         const bool early = (size_t)n_nodes + 8 * (size_t)n_level <= cap;
-        if (early) {
+        if (one && early) {
+            k_level_split_one<<<1, 1024, 0, c->stream>>>((Node*)c->nodes.p, level_start, n_level, n_nodes, D,
+                                                         c->prm.n_split, h_ratio, bnd, flags + FI_NCHILD);
+            SPH_CHECK_LAUNCH();
+        } else {
+            k_level_split<<<nbl, 256, 0, c->stream>>>((Node*)c->nodes.p, level_start, n_level, D, c->prm.n_split,
+                                                      h_ratio, bnd, nchild);
+            SPH_CHECK_LAUNCH();
+            SPH_TRY(scan_exclusive(c, nchild, nchild, n_level, flags + FI_NCHILD));
+        }
+        if (early && !one) {
             k_emit_children<<<nbl, 256, 0, c->stream>>>((Node*)c->nodes.p, level_start, n_level, nchild, n_nodes, D,
                                                          c->prm.n_split, h_ratio, bnd);
             SPH_CHECK_LAUNCH();
@@ -1649,7 +1847,15 @@ sph_status build_all(sph_ctx* c)
     k_wnodes<<<blocks_for(n_nodes, 256), 256, 0, c->stream>>>((const Node*)c->nodes.p, n_nodes, c->skin_abs,
                                                                 (WNode*)c->wnodes.p);
     SPH_CHECK_LAUNCH();
-    for (size_t l = 0; l + 1 < c->level_off.size(); l++) {
+    const int n_lvl = (int)c->level_off.size() - 1;
+    if (n_nodes <= LEVEL_ONE) {
+        LevelOffsets L;
+        L.n = n_lvl;
+        for (int l = 0; l <= n_lvl; l++) L.off[l] = c->level_off[l];
+        k_wnext_all<<<1, 1024, 0, c->stream>>>((const Node*)c->nodes.p, L, (WNode*)c->wnodes.p);
+        SPH_CHECK_LAUNCH();
+    }
+    for (int l = 0; n_nodes > LEVEL_ONE && l < n_lvl; l++) {
         const int ls = c->level_off[l], nl = c->level_off[l + 1] - ls;
         if (nl <= 0) continue;
         k_wnext<<<blocks_for(nl, 256), 256, 0, c->stream>>>((const Node*)c->nodes.p, ls, nl, (WNode*)c->wnodes.p);
@@ -1659,9 +1865,14 @@ sph_status build_all(sph_ctx* c)
     // list radii (leaf fill) and the walk nodes' bounds are those of the
     // current H: the relist need not recompute them
     c->radii_fresh = c->prm.lists == SPH_LISTS_CELL;
+    c->rewalked = false;
     SPH_TRY(relist(c));
-    SPH_TRY(read_int(c, flags, &fl));
-    if (fl & FLAG_INVALID) return SPH_ERR_INVALID;
+    if (c->rewalked) {
+        // (the second walk of a leaf flags a list other than the counted one)
+        int fl = 0;
+        SPH_TRY(read_int(c, flags, &fl));
+        if (fl & FLAG_INVALID) return SPH_ERR_INVALID;
+    }
     c->built = true;
     c->sorted = false;
     return SPH_OK;

@@ -67,7 +67,7 @@ struct sph_ctx {
     bool in_step = false;  // inside sph_step (the refresh of the next step checks the FP32 extent rule)
     bool predicted = false;      // ghost/force use the predicted v, u of a step
     double hdt_h = 0.0;          // half the step in progress (the prediction's interval)
-    double hdt_up = 0.0;         // source of the upload of the prediction's half step
+    double hdt_up = 0.0;         // the prediction's half step on the device
 
     // counters of the last calls
     sph_stats st{};
@@ -92,6 +92,7 @@ struct sph_ctx {
     DevBuf list;
     DevBuf wide;                  // leaves with lists above SPH_WIDE_MIN (more than SPH_WIDE_ALL leaves)
     int n_wide = 0;
+    bool rewalked = false;        // the last list build walked leaves a second time
     DevBuf walk_scratch;          // per-leaf slots of the one-pass list walk
     DevBuf walk_ovf, walk_link;   // its overflow chunks; chunk links (head, incomplete, next)
     int walk_cap = 128;           // entries per slot (grows after an overflow)
@@ -117,7 +118,10 @@ struct sph_ctx {
     int64_t n_plist = 0;          // entries of the current particle lists
     DevBuf skey, sidx;            // per-direction sorted projections
     DevBuf hlo, hhi, conv;        // Newton brackets and converged flags
-    DevBuf flags, counters;       // device flags (int[64], see FI_*) and counters (int64)
+    // one block, so that one copy reads what the host needs: per-box H ranges
+    // (dstat), step parameters (dparam), flags (int[64], see FI_*), counters (int64)
+    DevBuf state;
+    DevBuf flags, counters;
     DevBuf scan_tmp;              // scan block sums
     DevBuf rs_hist;               // radix-sort digit histograms
     DevBuf sums;                  // per-domain FP64 conservation partials

@@ -1420,6 +1420,18 @@ static int resident_wgs(sph_ctx* c)
 // it, and the kernels bound the work by the leaf count read on the device.
 static int leaf_capacity(sph_ctx* c) { return (int)std::min<size_t>(c->l_begin.cap / sizeof(int), INT32_MAX / 2); }
 
+// The flags and the counters, which lie side by side, in one copy.
+struct FlagsCounters {
+    int flags[FI_NFLAGS];
+    unsigned long long cnt[CNT_N];
+};
+static sph_status read_flags(sph_ctx* c, FlagsCounters& fc)
+{
+    SPH_CHECK_HIP(hipMemcpyAsync(&fc, c->flags.p, sizeof(fc), hipMemcpyDeviceToHost, c->stream));
+    SPH_CHECK_HIP(hipStreamSynchronize(c->stream));
+    return SPH_OK;
+}
+
 static void dens_args(sph_ctx* c, const int* gate, bool graph, DensArgs& a, int& nb)
 {
     memset(&a, 0, sizeof(a));
@@ -1621,10 +1633,10 @@ static sph_status density_loop(sph_ctx* c, int done_sweeps, unsigned long long u
         SPH_CHECK_HIP(hipEventRecord(c->kev[1], c->stream));
         k_count_fold<<<1, PART_N, 0, c->stream>>>(cnt);
         SPH_CHECK_LAUNCH();
-        unsigned long long hc[CNT_N];
-        SPH_CHECK_HIP(hipMemcpyAsync(hc, cnt, sizeof(hc), hipMemcpyDeviceToHost, c->stream));
-        SPH_CHECK_HIP(hipMemcpyAsync(&fl, flags, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-        SPH_CHECK_HIP(hipStreamSynchronize(c->stream));
+        FlagsCounters fc;
+        SPH_TRY(read_flags(c, fc));
+        const unsigned long long* hc = fc.cnt;
+        fl = fc.flags[FI_FLAGS];
         {
             float ms = 0.f;
             SPH_CHECK_HIP(hipEventElapsedTime(&ms, c->kev[0], c->kev[1]));
@@ -1703,8 +1715,7 @@ static sph_status density_loop(sph_ctx* c, int done_sweeps, unsigned long long u
 #define SPH_GATED_SWEEPS 3
 
 __global__ void k_graph_begin(unsigned long long* cnt, int* flags, int* gate);
-__global__ void k_sweep_begin(unsigned long long* cnt, int* flags, const int* gate);
-__global__ void k_sweep_end(unsigned long long* cnt, const int* flags, int* gate);
+__global__ void k_sweep_end(unsigned long long* cnt, int* flags, int* gate, int more);
 
 sph_status density_all(sph_ctx* c)
 {
@@ -1719,17 +1730,15 @@ sph_status density_all(sph_ctx* c)
     SPH_CHECK_LAUNCH();
     SPH_CHECK_HIP(hipEventRecord(c->kev[0], c->stream));
     for (int k = 0; k < sweeps; k++) {
-        k_sweep_begin<<<1, 64, 0, c->stream>>>(cnt, flags, gate);
         SPH_TRY(launch_density(c, gate));
-        k_sweep_end<<<1, PART_N, 0, c->stream>>>(cnt, flags, gate);
+        k_sweep_end<<<1, PART_N, 0, c->stream>>>(cnt, flags, gate, k + 1 < sweeps);
         SPH_CHECK_LAUNCH();
     }
     SPH_CHECK_HIP(hipEventRecord(c->kev[1], c->stream));
-    int hfl[FI_GATE + 1];
-    unsigned long long hc[CNT_N];
-    SPH_CHECK_HIP(hipMemcpyAsync(hfl, c->flags.p, sizeof(hfl), hipMemcpyDeviceToHost, c->stream));
-    SPH_CHECK_HIP(hipMemcpyAsync(hc, c->counters.p, sizeof(hc), hipMemcpyDeviceToHost, c->stream));
-    SPH_CHECK_HIP(hipStreamSynchronize(c->stream));
+    FlagsCounters fc;
+    SPH_TRY(read_flags(c, fc));
+    const int* hfl = fc.flags;
+    const unsigned long long* hc = fc.cnt;
     const int g = hfl[FI_GATE], fl = hfl[FI_FLAGS];
     const int done = (int)hc[CNT_GSWEEPS];
     {
@@ -1803,9 +1812,13 @@ static sph_status launch_ghost(sph_ctx* c, const double* u, const double* vx, co
 // in progress) or 0, uploaded to the device slot the ghost reads.
 static sph_status set_prediction(sph_ctx* c)
 {
-    c->hdt_up = c->predicted ? c->hdt_h : 0.0;
-    SPH_CHECK_HIP(hipMemcpyAsync((double*)c->dparam.p + 2, &c->hdt_up, sizeof(double), hipMemcpyHostToDevice,
-                                 c->stream));
+    const double hdt = c->predicted ? c->hdt_h : 0.0;
+    if (hdt == c->hdt_up) return SPH_OK;  // (0 since sph_create)
+    c->hdt_up = hdt;
+    const hipError_t e = hipMemcpyAsync((double*)c->dparam.p + 2, &c->hdt_up, sizeof(double), hipMemcpyHostToDevice,
+                                        c->stream);
+    if (e != hipSuccess) c->hdt_up = NAN;
+    SPH_CHECK_HIP(e);
     return SPH_OK;
 }
 
@@ -1897,8 +1910,11 @@ static sph_status launch_force(sph_ctx* c, const int* gate, bool graph = false)
 __global__ __launch_bounds__(PART_N) void k_count_totals(unsigned long long* cnt, const int* gate)
 {
     if (gate && *gate != 1) return;
+    if (threadIdx.x == 0) cnt[CNT_NFORCE] = cnt[CNT_NDENS_F] = 0ull;
+    if (threadIdx.x < XQ_N) cnt[XQ_FORCE + threadIdx.x * XQ_STRIDE] = 0ull;
+    __syncthreads();
     fold_counts(cnt);
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
+    if (threadIdx.x == 0) {
         cnt[CNT_NFORCE_SUM] += cnt[CNT_NFORCE];
         cnt[CNT_NDENS_SUM] += cnt[CNT_NDENS_F];
         cnt[CNT_FORCE_CALLS] += 1ull;
@@ -1913,14 +1929,15 @@ sph_status force_all(sph_ctx* c)
     const size_t nb8 = (size_t)c->n * 8;
     unsigned long long* cnt = (unsigned long long*)c->counters.p;
     SPH_CHECK_HIP(hipEventRecord(c->ev[4], c->stream));
-    SPH_CHECK_HIP(hipMemsetAsync(c->P.ax, 0, nb8, c->stream));
-    SPH_CHECK_HIP(hipMemsetAsync(c->P.ay, 0, nb8, c->stream));
-    SPH_CHECK_HIP(hipMemsetAsync(c->P.az, 0, nb8, c->stream));
-    SPH_CHECK_HIP(hipMemsetAsync(c->P.dudt, 0, nb8, c->stream));
-    SPH_CHECK_HIP(hipMemsetAsync(&cnt[CNT_NFORCE], 0, 8, c->stream));
-    SPH_CHECK_HIP(hipMemsetAsync(&cnt[XQ_FORCE], 0, XQ_N * XQ_STRIDE * 8, c->stream));
-    SPH_CHECK_HIP(hipMemsetAsync(&cnt[CNT_NDENS_F], 0, 8, c->stream));
-    if (c->P.nngb) SPH_CHECK_HIP(hipMemsetAsync(c->P.nngb, 0, (size_t)c->n * 4, c->stream));
+    // (the gather forms write every output; the counts and the task queues are
+    // set and cleared by the kernel after the force)
+    if (c->prm.force_mode == SPH_FORCE_PAIRS) {
+        SPH_CHECK_HIP(hipMemsetAsync(c->P.ax, 0, nb8, c->stream));
+        SPH_CHECK_HIP(hipMemsetAsync(c->P.ay, 0, nb8, c->stream));
+        SPH_CHECK_HIP(hipMemsetAsync(c->P.az, 0, nb8, c->stream));
+        SPH_CHECK_HIP(hipMemsetAsync(c->P.dudt, 0, nb8, c->stream));
+        if (c->P.nngb) SPH_CHECK_HIP(hipMemsetAsync(c->P.nngb, 0, (size_t)c->n * 4, c->stream));
+    }
     SPH_CHECK_HIP(hipEventRecord(c->kev[2], c->stream));
     SPH_TRY(launch_force(c, nullptr));
     SPH_CHECK_HIP(hipEventRecord(c->kev[3], c->stream));
@@ -1953,24 +1970,16 @@ __global__ void k_graph_begin(unsigned long long* cnt, int* flags, int* gate)
         cnt[CNT_UNCONV] = 0ull;
         cnt[CNT_NDENS] = 0ull;
         cnt[CNT_DEVAL] = 0ull;
-        cnt[CNT_GSWEEPS] = 0ull;
+        cnt[CNT_GSWEEPS] = 1ull;  // the first sweep follows
         for (int k = CNT_UHIST; k < CNT_N; k++) cnt[k] = 0ull;
         flags[FI_FLAGS] = 0;
         *gate = 0;
     }
 }
 
-__global__ void k_sweep_begin(unsigned long long* cnt, int* flags, const int* gate)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0 && *gate == 0) {
-        cnt[CNT_UNCONV] = 0ull;
-        flags[FI_FLAGS] = 0;
-        cnt[CNT_GSWEEPS] += 1ull;
-    }
-}
-
 // same decision order as the host loop: box limit, converged, rebuild/relist
-__global__ __launch_bounds__(PART_N) void k_sweep_end(unsigned long long* cnt, const int* flags, int* gate)
+// more: another sweep is enqueued, and begins here unless the gate is turned
+__global__ __launch_bounds__(PART_N) void k_sweep_end(unsigned long long* cnt, int* flags, int* gate, int more)
 {
     if (*gate != 0) return;
     fold_counts(cnt);
@@ -1981,19 +1990,19 @@ __global__ __launch_bounds__(PART_N) void k_sweep_end(unsigned long long* cnt, c
         if (f & FLAG_BOX_SMALL) *gate = 2;
         else if (cnt[CNT_UNCONV] == 0ull) *gate = 1;
         else if (f & (FLAG_RELIST | FLAG_REBUILD)) *gate = 2;
+        else if (more) {
+            cnt[CNT_UNCONV] = 0ull;
+            flags[FI_FLAGS] = 0;
+            cnt[CNT_GSWEEPS] = k + 1;
+        }
     }
 }
 
 __global__ __launch_bounds__(256) void k_force_zero(int64_t n, double* ax, double* ay, double* az, double* dudt,
-                                                    int32_t* nngb, unsigned long long* cnt, const int* gate)
+                                                    int32_t* nngb, const int* gate)
 {
     if (*gate != 1) return;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i == 0) {
-        cnt[CNT_NFORCE] = 0ull;
-        for (int r = 0; r < XQ_N; r++) cnt[XQ_FORCE + r * XQ_STRIDE] = 0ull;
-        cnt[CNT_NDENS_F] = 0ull;
-    }
     if (i < n) {
         ax[i] = 0.0;
         ay[i] = 0.0;
@@ -2075,13 +2084,13 @@ static sph_status capture_dgf(sph_ctx* c, const double* u, const double* vx, con
         c->n, nlc, (double*)c->hlo.p, (double*)c->hhi.p, (uint8_t*)c->conv.p, (int*)c->l_active.p, nl_dev);
     k_graph_begin<<<1, 64, 0, c->stream>>>(cnt, flags, gate);
     for (int k = 0; k < sweeps && st == SPH_OK; k++) {
-        k_sweep_begin<<<1, 64, 0, c->stream>>>(cnt, flags, gate);
         st = launch_density(c, gate, true);
-        k_sweep_end<<<1, PART_N, 0, c->stream>>>(cnt, flags, gate);
+        k_sweep_end<<<1, PART_N, 0, c->stream>>>(cnt, flags, gate, k + 1 < sweeps);
     }
     if (st == SPH_OK) st = launch_ghost(c, u, vx, vy, vz, gate);
-    k_force_zero<<<blocks_for(c->n, 256), 256, 0, c->stream>>>(c->n, c->P.ax, c->P.ay, c->P.az, c->P.dudt, c->P.nngb,
-                                                              cnt, gate);
+    if (c->prm.force_mode == SPH_FORCE_PAIRS)
+        k_force_zero<<<blocks_for(c->n, 256), 256, 0, c->stream>>>(c->n, c->P.ax, c->P.ay, c->P.az, c->P.dudt,
+                                                                  c->P.nngb, gate);
     if (st == SPH_OK) st = launch_force(c, gate, true);
     k_count_totals<<<1, PART_N, 0, c->stream>>>(cnt, gate);
     hipGraph_t g = nullptr;
@@ -2122,11 +2131,10 @@ sph_status dgf_graph(sph_ctx* c)
     SPH_CHECK_HIP(hipEventRecord(c->ev[0], c->stream));
     SPH_CHECK_HIP(hipGraphLaunch((hipGraphExec_t)c->graph_exec, c->stream));
     SPH_CHECK_HIP(hipEventRecord(c->ev[1], c->stream));
-    int hfl[FI_GATE + 1];
-    unsigned long long hc[CNT_N];
-    SPH_CHECK_HIP(hipMemcpyAsync(hfl, c->flags.p, sizeof(hfl), hipMemcpyDeviceToHost, c->stream));
-    SPH_CHECK_HIP(hipMemcpyAsync(hc, c->counters.p, sizeof(hc), hipMemcpyDeviceToHost, c->stream));
-    SPH_CHECK_HIP(hipStreamSynchronize(c->stream));
+    FlagsCounters fc;
+    SPH_TRY(read_flags(c, fc));
+    const int* hfl = fc.flags;
+    const unsigned long long* hc = fc.cnt;
     const int gate = hfl[FI_GATE], fl = hfl[FI_FLAGS];
     const int gsweeps = (int)hc[CNT_GSWEEPS];
     // the graph's kernels are not timed one by one
@@ -2262,14 +2270,18 @@ static sph_status step_impl(sph_ctx* c, double dt)
         if (c->prm.lists == SPH_LISTS_PARTICLE) SPH_TRY(plist_refresh(c, nullptr));
         else SPH_TRY(refresh_leaves(c, nullptr));
     }
-    double dp[2] = {0.0, 0.0};
-    int fl = 0;
-    SPH_CHECK_HIP(hipMemcpyAsync(dp, c->dparam.p, 16, hipMemcpyDeviceToHost, c->stream));
-    SPH_CHECK_HIP(hipMemcpyAsync(&fl, c->flags.p, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+    // (the flags follow the parameters)
+    struct {
+        double dp[8];
+        int fl;
+    } rb;
+    SPH_CHECK_HIP(hipMemcpyAsync(&rb, c->dparam.p, 8 * sizeof(double) + sizeof(int), hipMemcpyDeviceToHost, c->stream));
     if (keep && c->prm.lists == SPH_LISTS_PARTICLE)
         SPH_CHECK_HIP(hipMemcpyAsync(c->stale_h, (unsigned long long*)c->counters.p + CNT_STALE_MOVED, 16,
                                      hipMemcpyDeviceToHost, c->stream));
     SPH_CHECK_HIP(hipStreamSynchronize(c->stream));
+    const double* dp = rb.dp;
+    const int fl = rb.fl;
     double vmax;
     {
         unsigned long long b;

@@ -53,6 +53,47 @@ __global__ __launch_bounds__(SCAN_T) void k_scan_add(int* out, int n, const int*
     }
 }
 
+// Exclusive scan of up to SCAN_ONE elements by one workgroup, SCAN_T x 4 x
+// SCAN_ITEMS a round: one launch where the tiles, their sums and the addition
+// take three (a launch costs about 5 us between small kernels, a round here 1.5).
+#define SCAN_ONE 32768
+__global__ __launch_bounds__(4 * SCAN_T) void k_scan_one(const int* in, int* out, int n, int* d_total)
+{
+    __shared__ int wsum[4 * SCAN_T / 64];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    int base = 0;
+    for (int t0 = 0; t0 < n; t0 += 4 * SCAN_BLOCK) {
+        const int i0 = t0 + tid * SCAN_ITEMS;
+        int v[SCAN_ITEMS], s = 0;
+#pragma unroll
+        for (int k = 0; k < SCAN_ITEMS; k++) {
+            v[k] = i0 + k < n ? in[i0 + k] : 0;
+            s += v[k];
+        }
+        int incl = s;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int t = __shfl_up(incl, off);
+            if (lane >= off) incl += t;
+        }
+        if (lane == 63) wsum[w] = incl;
+        __syncthreads();
+        int excl = base + incl - s, all = 0;
+        for (int q = 0; q < 4 * SCAN_T / 64; q++) {
+            if (q < w) excl += wsum[q];
+            all += wsum[q];
+        }
+        base += all;
+#pragma unroll
+        for (int k = 0; k < SCAN_ITEMS; k++) {
+            if (i0 + k < n) out[i0 + k] = excl;
+            excl += v[k];
+        }
+        __syncthreads();
+    }
+    if (tid == 0) *d_total = base;
+}
+
 static sph_status scan_rec(sph_ctx* c, const int* in, int* out, int n, int* d_total, int* tmp, long tmp_left)
 {
     const int nb = (n + SCAN_BLOCK - 1) / SCAN_BLOCK;
@@ -77,6 +118,11 @@ sph_status scan_exclusive(sph_ctx* c, const int* in, int* out, int n, int* d_tot
         SPH_CHECK_HIP(hipMemsetAsync(d_total, 0, sizeof(int), c->stream));
         return SPH_OK;
     }
+    if (n > SCAN_BLOCK && n <= SCAN_ONE) {
+        k_scan_one<<<1, 4 * SCAN_T, 0, c->stream>>>(in, out, n, d_total);
+        SPH_CHECK_LAUNCH();
+        return SPH_OK;
+    }
     long need = (long)n / SCAN_BLOCK + 64;
     SPH_TRY(buf_ensure(c->scan_tmp, need * sizeof(int)));
     return scan_rec(c, in, out, n, d_total, (int*)c->scan_tmp.p, need);
@@ -87,14 +133,18 @@ sph_status scan_exclusive(sph_ctx* c, const int* in, int* out, int n, int* d_tot
 // of the workgroup owns the contiguous quarter w of the tile, and lane l of
 // the wave holds keys r*64 + l of that quarter (r = 0..RS_ITEMS-1), so rounds
 // visit the quarter in order.  The per-digit global offsets come from an
-// exclusive scan of the digit-major [256][n_tiles] histogram.
+// exclusive scan of the digit-major [256][n_tiles] histogram; up to RS_FEW keys
+// the tiles are of RS_ITEMS = 4 rounds (more workgroups) and each workgroup of the
+// scatter sums the histogram itself (SUM; a pass is two launches instead of
+// five).
 // ---------------------------------------------------------------------------
 #define RS_WAVES 4
-#define RS_ITEMS 16
-#define RS_TILE (64 * RS_WAVES * RS_ITEMS)
+#define RS_FEW 65536
 
+template <int RS_ITEMS>
 __global__ __launch_bounds__(256) void k_rs_hist(const uint64_t* __restrict__ keys, int n, int shift, int* hist, int nb)
 {
+    constexpr int RS_TILE = 64 * RS_WAVES * RS_ITEMS;
     __shared__ int h[256];
     const int tid = threadIdx.x;
     h[tid] = 0;
@@ -112,10 +162,12 @@ __global__ __launch_bounds__(256) void k_rs_hist(const uint64_t* __restrict__ ke
 // round, lane, i.e. input order within each digit), then written out in
 // that order: consecutive lanes write consecutive positions of one digit's
 // run, so the stores coalesce into runs of ~RS_TILE / 256 keys.
+template <int RS_ITEMS, bool SUM>
 __global__ __launch_bounds__(256) void k_rs_scatter(const uint64_t* __restrict__ kin, const uint32_t* __restrict__ vin,
                                                     uint64_t* __restrict__ kout, uint32_t* __restrict__ vout, int n,
                                                     int shift, const int* __restrict__ offs, int nb)
 {
+    constexpr int RS_TILE = 64 * RS_WAVES * RS_ITEMS;
     __shared__ int wcount[RS_WAVES][256];
     __shared__ int wbase[RS_WAVES][256];
     __shared__ int gshift[256];  // global position - local position, per digit
@@ -157,7 +209,28 @@ __global__ __launch_bounds__(256) void k_rs_scatter(const uint64_t* __restrict__
         __syncthreads();
         int start = inc - cnt;
         for (int q = 0; q < w; q++) start += wsum[q];
-        gshift[d] = offs[(long)d * nb + blockIdx.x] - start;
+        int first;  // of the tile's run of digit d in the output
+        if (SUM) {
+            int all = 0, before = 0;
+            for (int q = 0; q < nb; q++) {
+                const int h = offs[(long)d * nb + q];
+                if (q < (int)blockIdx.x) before += h;
+                all += h;
+            }
+            int in2 = all;
+            for (int off = 1; off < 64; off <<= 1) {
+                const int t = __shfl_up(in2, off);
+                if (lane >= off) in2 += t;
+            }
+            __syncthreads();
+            if (lane == 63) wsum[w] = in2;
+            __syncthreads();
+            first = in2 - all + before;
+            for (int q = 0; q < w; q++) first += wsum[q];
+        } else {
+            first = offs[(long)d * nb + blockIdx.x];
+        }
+        gshift[d] = first - start;
         int run = start;
         for (int q = 0; q < RS_WAVES; q++) {
             wbase[q][d] = run;
@@ -203,8 +276,12 @@ sph_status radix_sort(sph_ctx* c, int n, int bits, DevBuf* kb, DevBuf* vb, int* 
 {
     int cur = 0;
     if (n > 1) {
-        const int nb = (n + RS_TILE - 1) / RS_TILE;
-        SPH_TRY(buf_ensure(c->rs_hist, (size_t)256 * nb * sizeof(int) + 64));
+        const auto hist_bytes = [](int nb) { return (size_t)256 * nb * sizeof(int) + 64; };
+        const int t4 = 64 * RS_WAVES * 4, t16 = 64 * RS_WAVES * 16;
+        // (the smaller tiles' histogram is four times as large)
+        const bool few = n <= RS_FEW && buf_ensure(c->rs_hist, hist_bytes((n + t4 - 1) / t4)) == SPH_OK;
+        const int nb = few ? (n + t4 - 1) / t4 : (n + t16 - 1) / t16;
+        if (!few) SPH_TRY(buf_ensure(c->rs_hist, hist_bytes(nb)));
         int* hist = (int*)c->rs_hist.p;
         int* total = (int*)c->flags.p + FI_SCRATCH;
         for (int shift = 0; shift < bits; shift += 8) {
@@ -212,10 +289,16 @@ sph_status radix_sort(sph_ctx* c, int n, int bits, DevBuf* kb, DevBuf* vb, int* 
             uint32_t* vin = (uint32_t*)vb[cur].p;
             uint64_t* kout = (uint64_t*)kb[cur ^ 1].p;
             uint32_t* vout = (uint32_t*)vb[cur ^ 1].p;
-            k_rs_hist<<<nb, 256, 0, c->stream>>>(kin, n, shift, hist, nb);
-            SPH_CHECK_LAUNCH();
-            SPH_TRY(scan_exclusive(c, hist, hist, 256 * nb, total));
-            k_rs_scatter<<<nb, 256, 0, c->stream>>>(kin, vin, kout, vout, n, shift, hist, nb);
+            if (few) {
+                k_rs_hist<4><<<nb, 256, 0, c->stream>>>(kin, n, shift, hist, nb);
+                SPH_CHECK_LAUNCH();
+                k_rs_scatter<4, true><<<nb, 256, 0, c->stream>>>(kin, vin, kout, vout, n, shift, hist, nb);
+            } else {
+                k_rs_hist<16><<<nb, 256, 0, c->stream>>>(kin, n, shift, hist, nb);
+                SPH_CHECK_LAUNCH();
+                SPH_TRY(scan_exclusive(c, hist, hist, 256 * nb, total));
+                k_rs_scatter<16, false><<<nb, 256, 0, c->stream>>>(kin, vin, kout, vout, n, shift, hist, nb);
+            }
             SPH_CHECK_LAUNCH();
             cur ^= 1;
         }
