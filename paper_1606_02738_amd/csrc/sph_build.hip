@@ -501,8 +501,13 @@ __global__ __launch_bounds__(256) void k_emit_children(Node* nodes, int level_st
 
 // Levels of few cells by one workgroup: k_level_chunks, its scan and
 // k_chunk_map in one launch, k_level_split, its scan and k_emit_children in
-// another.
+// another.  The latter writes every child from one compute unit, so its limit
+// lies lower: 780 cells take it 161 us, the three launches 30 us; 64 cells
+// 12 us against 18 us.
 #define LEVEL_ONE 4096
+#ifndef SPLIT_ONE
+#define SPLIT_ONE 128
+#endif
 // Exclusive scan over the 1024 threads of the workgroup; `all`: the total.
 __device__ inline int wg_scan(int v, int* wsum, int& all)
 {
@@ -1751,7 +1756,8 @@ sph_status build_all(sph_ctx* c)
         // the node buffer holds 8 per cell of the level (the most a split
         // makes), they are written while the host reads the total
         const bool early = (size_t)n_nodes + 8 * (size_t)n_level <= cap;
-        if (one && early) {
+        const bool emitted = early && n_level <= SPLIT_ONE;
+        if (emitted) {
             k_level_split_one<<<1, 1024, 0, c->stream>>>((Node*)c->nodes.p, level_start, n_level, n_nodes, D,
                                                          c->prm.n_split, h_ratio, bnd, flags + FI_NCHILD);
             SPH_CHECK_LAUNCH();
@@ -1761,7 +1767,7 @@ sph_status build_all(sph_ctx* c)
             SPH_CHECK_LAUNCH();
             SPH_TRY(scan_exclusive(c, nchild, nchild, n_level, flags + FI_NCHILD));
         }
-        if (early && !one) {
+        if (early && !emitted) {
             k_emit_children<<<nbl, 256, 0, c->stream>>>((Node*)c->nodes.p, level_start, n_level, nchild, n_nodes, D,
                                                          c->prm.n_split, h_ratio, bnd);
             SPH_CHECK_LAUNCH();
