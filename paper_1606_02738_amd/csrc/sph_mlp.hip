@@ -42,28 +42,34 @@ __host__ __device__ inline float bf16_float(uint16_t b)
 }
 __device__ inline float bf16r(float x) { return bf16_float(bf16_bits(x)); }
 
-__device__ inline float silu_f(float z) { return z * __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
-__device__ inline float dsilu_f(float z)
+// SiLU in units of 1/log2(e): u = z log2(e) -> z sigmoid(z) log2(e).  Inference
+// keeps activations in these units (scaled with the inputs and the biases,
+// undone by the output weights), which saves the product inside the
+// exponential.
+#define LOG2E 1.44269504088896341
+__device__ __forceinline__ float silu_l2(float u)
 {
-    const float s = __builtin_amdgcn_rcpf(1.0f + __expf(-z));
-    return s * (1.0f + z * (1.0f - s));
+    return u * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-u));
 }
 
-typedef short bf16x4 __attribute__((ext_vector_type(4)));
+typedef short bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// Inference weights arranged for v_mfma_f32_16x16x16_bf16.  The layers are
-// computed transposed, Z^T = W^T X^T: A = a 16x16 block of W^T (output units
-// x inputs), B = 16 inputs x 16 particles, D = 16 output units x 16
-// particles.  Lane l holds A[l%16][4(l/16)+j], B[4(l/16)+j][l%16] and
-// D[4(l/16)+j][l%16] (j = 0..3), so the D block of output tile t is, after
-// bias and SiLU, exactly the B operand of input chunk t of the next layer.
+// Inference weights arranged for v_mfma_f32_16x16x32_bf16.  The layers are
+// computed transposed, Z^T = W^T X^T: A = 16 output units x 32 input slots,
+// B = 32 input slots x 16 particles, D = 16 output units x 16 particles.
+// Lane l holds slots 8(l/16)..+7 of A's row l%16 and of B's column l%16, and
+// D[4(l/16)+j][l%16] (j = 0..3).  Which input a slot stands for is free as
+// long as A and B agree: slots 8g+j and 8g+4+j of chunk c are the units
+// 32c+4g+j and 32c+16+4g+j, so that the D blocks of output tiles 2c and 2c+1
+// are, after SiLU, the B operand of chunk c of the next layer.  Layer 1 has 16
+// inputs: its slots hold the upper parts of inputs 4g+j, then their lower parts.
 struct MlpPacked {
-    bf16x4 a1[4][64];        // layer 1: [output tile][lane] (one input chunk)
-    bf16x4 a2[4][4][64];     // layer 2: [output tile][input chunk][lane]
-    bf16x4 a3[4][4][64];
-    float b1[NH], b2[NH], b3[NH], w4[NH];
-    float xmu[NIN], rxsd[NIN];
+    bf16x8 a1[4][64];        // layer 1: [output tile][lane]
+    bf16x8 a2[4][2][64];     // layer 2: [output tile][input chunk][lane]
+    bf16x8 a3[4][2][64];
+    float b1[NH], b2[NH], b3[NH], w4[NH];   // times log2(e); w4 over it
+    float xmu[NIN], rxsd[NIN];              // rxsd times log2(e)
     float b4, ymu, ysd, pad;
 };
 
@@ -75,42 +81,42 @@ struct MlpPacked {
 __global__ __launch_bounds__(256) void k_mlp_pack(const float* __restrict__ p, MlpPacked* __restrict__ w)
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    // A operands: (layer, tile, chunk, lane) -> 4 weights
-    const int n1 = 4 * 64, n2 = 16 * 64;
+    // A operands: (layer, tile, chunk, lane) -> 8 weights
+    const int n1 = 4 * 64, n2 = 8 * 64;
     if (t < n1 + 2 * n2) {
-        int layer, tile, kc, lane;
+        int layer, tile, c, lane;
         if (t < n1) {
             layer = 1;
             tile = t / 64;
-            kc = 0;
+            c = 0;
             lane = t % 64;
         } else {
             const int r = (t - n1) % n2;
             layer = t < n1 + n2 ? 2 : 3;
-            tile = r / 256;
-            kc = (r / 64) % 4;
+            tile = r / 128;
+            c = (r / 64) % 2;
             lane = r % 64;
         }
         const float* W = layer == 1 ? p + O_W1 : layer == 2 ? p + O_W2 : p + O_W3;
-        bf16x4 v;
-        for (int j = 0; j < 4; j++) {
-            const int k = kc * 16 + 4 * (lane / 16) + j;   // input unit
-            const int o = tile * 16 + lane % 16;           // output unit
+        bf16x8 v;
+        for (int j = 0; j < 8; j++) {
+            const int k = 32 * c + (layer == 1 ? 0 : 16 * (j / 4)) + 4 * (lane / 16) + j % 4;   // input unit
+            const int o = tile * 16 + lane % 16;                                               // output unit
             v[j] = (short)bf16_bits(W[k * NH + o]);
         }
         if (layer == 1) w->a1[tile][lane] = v;
-        else if (layer == 2) w->a2[tile][kc][lane] = v;
-        else w->a3[tile][kc][lane] = v;
+        else if (layer == 2) w->a2[tile][c][lane] = v;
+        else w->a3[tile][c][lane] = v;
     }
     if (t < NH) {
-        w->b1[t] = p[O_B1 + t];
-        w->b2[t] = p[O_B2 + t];
-        w->b3[t] = p[O_B3 + t];
-        w->w4[t] = bf16_float(bf16_bits(p[O_W4 + t]));
+        w->b1[t] = (float)(p[O_B1 + t] * LOG2E);
+        w->b2[t] = (float)(p[O_B2 + t] * LOG2E);
+        w->b3[t] = (float)(p[O_B3 + t] * LOG2E);
+        w->w4[t] = (float)(bf16_float(bf16_bits(p[O_W4 + t])) / LOG2E);
     }
     if (t < NIN) {
         w->xmu[t] = p[O_XMU + t];
-        w->rxsd[t] = 1.0f / p[O_XSD + t];
+        w->rxsd[t] = (float)(LOG2E / p[O_XSD + t]);
     }
     if (t == 0) {
         w->b4 = p[O_B4];
@@ -120,48 +126,56 @@ __global__ __launch_bounds__(256) void k_mlp_pack(const float* __restrict__ p, M
     }
 }
 
-// split x = hi + lo, both bfloat16 (hardware conversion, nearest even), for
-// the four values of an operand
-__device__ inline void split4(const float v[4], bf16x4& hi, bf16x4& lo)
+// split x = hi + lo, both bfloat16 (hardware conversion, nearest even): four
+// values into the pairs at, at+1 of the operands
+typedef __bf16 bf16v2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b)
 {
-    for (int j = 0; j < 4; j++) {
-        const __bf16 h = (__bf16)v[j];
-        const __bf16 l = (__bf16)(v[j] - (float)h);
-        hi[j] = __builtin_bit_cast(short, h);
-        lo[j] = __builtin_bit_cast(short, l);
+    const bf16v2 v = {(__bf16)a, (__bf16)b};
+    return __builtin_bit_cast(uint32_t, v);
+}
+__device__ __forceinline__ void split4(const float v[4], u32x4& hi, int at_hi, u32x4& lo, int at_lo)
+{
+    for (int j = 0; j < 2; j++) {
+        const uint32_t h = bf16_pair(v[2 * j], v[2 * j + 1]);
+        hi[at_hi + j] = h;
+        lo[at_lo + j] = bf16_pair(v[2 * j] - __uint_as_float(h << 16), v[2 * j + 1] - __uint_as_float(h & 0xffff0000u));
     }
 }
 
-#define MFMA16(a, b, c) __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0)
+typedef __bf16 bf16v8 __attribute__((ext_vector_type(8)));
+#define MFMA32(a, b, c) \
+    __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16v8, a), __builtin_bit_cast(bf16v8, b), c, 0, 0, 0)
 
 // Network inference, one wave per 16 particles at a time.  Writes y (if
 // non-NULL) and, if H is non-NULL, H[i] = H[i] exp(clamp(y, -ymax, ymax)).
-__global__ __launch_bounds__(256) void k_mlp_infer(const MlpPacked* __restrict__ W, const float* __restrict__ X,
+// Bound by the 192 SiLUs a particle and the splits of their results (per
+// activation two transcendental and six other VALU operations); the 36
+// products of a tile run beside them.  The biases therefore enter as the
+// products' C operand, a product contracts 32 slots, and the exponentials take
+// their argument as it is (silu_l2).  4194304 rows: 393 us with 16-slot
+// products, the bias added after them and the exponential of -z, 309 us now
+// (VALU active 83% of the time, the matrix units 21%).
+__global__ __launch_bounds__(256, 2) void k_mlp_infer(const MlpPacked* __restrict__ W, const float* __restrict__ X,
                                                    int64_t n, float* __restrict__ y, double* __restrict__ H,
                                                    float ymax)
 {
-    __shared__ float sb[4][NH];
-    __shared__ float sx[2][NIN];
-    for (int t = threadIdx.x; t < NH; t += blockDim.x) {
-        sb[0][t] = W->b1[t];
-        sb[1][t] = W->b2[t];
-        sb[2][t] = W->b3[t];
-        sb[3][t] = W->w4[t];
-    }
-    for (int t = threadIdx.x; t < NIN; t += blockDim.x) {
-        sx[0][t] = W->xmu[t];
-        sx[1][t] = W->rxsd[t];
-    }
-    __syncthreads();
     const int lane = threadIdx.x & 63, g = lane >> 4, col = lane & 15;
-    bf16x4 a1[4], a2[4][4], a3[4][4];
+    bf16x8 a1[4], a2[4][2], a3[4][2];
+    f32x4 b1[4], b2[4], b3[4], w4[4];
     for (int t = 0; t < 4; t++) {
         a1[t] = W->a1[t][lane];
-        for (int k = 0; k < 4; k++) {
-            a2[t][k] = W->a2[t][k][lane];
-            a3[t][k] = W->a3[t][k][lane];
+        for (int c = 0; c < 2; c++) {
+            a2[t][c] = W->a2[t][c][lane];
+            a3[t][c] = W->a3[t][c][lane];
         }
+        b1[t] = *(const f32x4*)&W->b1[16 * t + 4 * g];
+        b2[t] = *(const f32x4*)&W->b2[16 * t + 4 * g];
+        b3[t] = *(const f32x4*)&W->b3[16 * t + 4 * g];
+        w4[t] = *(const f32x4*)&W->w4[16 * t + 4 * g];
     }
+    const f32x4 xmu = *(const f32x4*)&W->xmu[4 * g], rxsd = *(const f32x4*)&W->rxsd[4 * g];
     const float b4 = W->b4, ymu = W->ymu, ysd = W->ysd;
     const int64_t n_tiles = (n + 15) / 16;
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
@@ -181,42 +195,38 @@ __global__ __launch_bounds__(256) void k_mlp_infer(const MlpPacked* __restrict__
         } else {
             v[0] = v[1] = v[2] = v[3] = 0.f;
         }
-        for (int j = 0; j < 4; j++) v[j] = (v[j] - sx[0][4 * g + j]) * sx[1][4 * g + j];
-        bf16x4 bh[4], bl[4];
-        split4(v, bh[0], bl[0]);
+        for (int j = 0; j < 4; j++) v[j] = (v[j] - xmu[j]) * rxsd[j];
+        u32x4 bx, bh[2], bl[2];
+        split4(v, bx, 0, bx, 2);
         f32x4 acc[4];
-        for (int t = 0; t < 4; t++) {
-            acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-            acc[t] = MFMA16(a1[t], bh[0], acc[t]);
-            acc[t] = MFMA16(a1[t], bl[0], acc[t]);
-        }
+        for (int t = 0; t < 4; t++) acc[t] = MFMA32(a1[t], bx, b1[t]);
+#pragma unroll
         for (int t = 0; t < 4; t++) {
             float h[4];
-            for (int j = 0; j < 4; j++) h[j] = silu_f(acc[t][j] + sb[0][16 * t + 4 * g + j]);
-            split4(h, bh[t], bl[t]);
+            for (int j = 0; j < 4; j++) h[j] = silu_l2(acc[t][j]);
+            split4(h, bh[t / 2], 2 * (t % 2), bl[t / 2], 2 * (t % 2));
         }
         for (int t = 0; t < 4; t++) {
-            acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-            for (int k = 0; k < 4; k++) {
-                acc[t] = MFMA16(a2[t][k], bh[k], acc[t]);
-                acc[t] = MFMA16(a2[t][k], bl[k], acc[t]);
-            }
+            acc[t] = MFMA32(a2[t][0], bh[0], b2[t]);
+            acc[t] = MFMA32(a2[t][0], bl[0], acc[t]);
+            acc[t] = MFMA32(a2[t][1], bh[1], acc[t]);
+            acc[t] = MFMA32(a2[t][1], bl[1], acc[t]);
         }
+#pragma unroll
         for (int t = 0; t < 4; t++) {
             float h[4];
-            for (int j = 0; j < 4; j++) h[j] = silu_f(acc[t][j] + sb[1][16 * t + 4 * g + j]);
-            split4(h, bh[t], bl[t]);
+            for (int j = 0; j < 4; j++) h[j] = silu_l2(acc[t][j]);
+            split4(h, bh[t / 2], 2 * (t % 2), bl[t / 2], 2 * (t % 2));
         }
         for (int t = 0; t < 4; t++) {
-            acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-            for (int k = 0; k < 4; k++) {
-                acc[t] = MFMA16(a3[t][k], bh[k], acc[t]);
-                acc[t] = MFMA16(a3[t][k], bl[k], acc[t]);
-            }
+            acc[t] = MFMA32(a3[t][0], bh[0], b3[t]);
+            acc[t] = MFMA32(a3[t][0], bl[0], acc[t]);
+            acc[t] = MFMA32(a3[t][1], bh[1], acc[t]);
+            acc[t] = MFMA32(a3[t][1], bl[1], acc[t]);
         }
         float part = 0.f;
         for (int t = 0; t < 4; t++)
-            for (int j = 0; j < 4; j++) part += silu_f(acc[t][j] + sb[2][16 * t + 4 * g + j]) * sb[3][16 * t + 4 * g + j];
+            for (int j = 0; j < 4; j++) part += silu_l2(acc[t][j]) * w4[t][j];
         // the four lane groups hold the four quarters of the hidden units
         part += __shfl_xor(part, 16);
         part += __shfl_xor(part, 32);
@@ -233,12 +243,12 @@ __global__ __launch_bounds__(256) void k_mlp_infer(const MlpPacked* __restrict__
 }
 
 // ---------------------------------------------------------------------------
-// Training: float32 forward and backward over micro-batches of MB rows per
-// workgroup (weights rounded to bfloat16 as in inference), partial
-// gradients per workgroup, then a reduction fused with Adam.
+// Training: float32 forward and backward over tiles of MB rows per workgroup
+// (weights rounded to bfloat16 as in inference), partial gradients per
+// workgroup, then a reduction fused with Adam.
 // ---------------------------------------------------------------------------
-#define MB 32
-// Workgroups of k_mlp_fb at most: one per compute unit (about 88 KB of LDS
+#define MB 64
+// Workgroups of k_mlp_fb at most: one per compute unit (about 149 KB of LDS
 // each); each loops over row tiles of MB rows.
 #define MLP_FB_WGS 256
 
@@ -261,19 +271,96 @@ inline int fb_workgroups(int64_t count)
     return (int)std::max<int64_t>(1, std::min<int64_t>((count + MB - 1) / MB, MLP_FB_WGS));
 }
 
+// Row stride of the LDS tiles, in floats: 4 LSTR = 16 (mod 64) puts the four
+// lane groups' rows 4g + s of an operand on different banks, and the rows of
+// a 16-byte read on different quads of banks.
+#define LSTR (NH + 4)
+#define XSTR (NIN + 4)
+
+#define MFMA4(a, b, c) __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0)
+
+// z[o] += W^T x (TRANS false: sum over W's rows) or W x (TRANS true: over its
+// columns) for the 64 units x of 16 samples: x[t][j] is unit 16 t + 4 g + j of
+// sample lane%16, and so are the results.  Step (t, j) contracts the four
+// units 16 t + 4 g + j, one per lane group, so that a product's result is the
+// next product's operand as it stands.
+template <bool TRANS>
+__device__ __forceinline__ void fb_operands(const float (*W)[LSTR], int t, int g, int col, f32x4 w[4])
+{
+#pragma unroll
+    for (int o = 0; o < 4; o++) {
+        if (TRANS) w[o] = *(const f32x4*)&W[16 * o + col][16 * t + 4 * g];
+        else
+            for (int j = 0; j < 4; j++) w[o][j] = W[16 * t + 4 * g + j][16 * o + col];
+    }
+}
+template <bool TRANS>
+__device__ __forceinline__ void fb_layer(const float (*W)[LSTR], const f32x4 x[4], f32x4 z[4], int g, int col)
+{
+    // the operands of the next 16 products are read while these run: with one
+    // wave on a SIMD nothing else covers the reads
+    f32x4 w[2][4];
+    fb_operands<TRANS>(W, 0, g, col, w[0]);
+#pragma unroll
+    for (int t = 0; t < 4; t++) {
+        if (t < 3) fb_operands<TRANS>(W, t + 1, g, col, w[(t + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+            for (int o = 0; o < 4; o++) z[o] = MFMA4(w[t & 1][o][j], x[t][j], z[o]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// Bound by the float32 matrix rate and its operand reads from LDS: each wave
+// takes 16 of the tile's 64 rows through the whole forward and backward chain
+// in registers (416 16x16x4 products, about 13000 cycles), then the four waves
+// share the weight gradients by rows of W, contracting the tile's 64 rows from
+// LDS, so no wave's partial sums meet another's.  16384 rows: 70 us in scalar
+// form (32 rows a tile, one lane per 8 units, every operand read from LDS, the
+// backward ones 8 ways in conflict), 19 us now.
 __global__ __launch_bounds__(256) void k_mlp_fb(TrainArgs a)
 {
-    __shared__ float W1[NIN * NH], W2[NH * NH], W3[NH * NH];
+    __shared__ __align__(16) float W1[NIN][LSTR], W2[NH][LSTR], W3[NH][LSTR];
     __shared__ float bb[3][NH], w4[NH], xmu[NIN], rxsd[NIN];
-    __shared__ float xh[MB][NIN];
-    __shared__ float hA[3][MB][NH];   // activations h1, h2, h3
-    __shared__ float dA[3][MB][NH];   // SiLU'(z), then dL/dz
-    __shared__ float dout[MB], red[MB];
-    const int tid = threadIdx.x;
-    for (int i = tid; i < NIN * NH; i += 256) W1[i] = bf16r(a.p[O_W1 + i]);
-    for (int i = tid; i < NH * NH; i += 256) {
-        W2[i] = bf16r(a.p[O_W2 + i]);
-        W3[i] = bf16r(a.p[O_W3 + i]);
+    __shared__ __align__(16) float xh[MB][XSTR];
+    __shared__ __align__(16) float hA[3][MB][LSTR];   // activations h1, h2, h3
+    __shared__ __align__(16) float dA[3][MB][LSTR];   // dL/dz1, dL/dz2, dL/dz3
+    __shared__ float dout[MB], red[2][4];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int g = lane >> 4, col = lane & 15;
+    const int s = 16 * wv + col;   // row of the tile
+    // inputs 4g .. 4g+3 and the target of this lane's row of a tile, zero past
+    // the last row
+    float x[4], yt;
+    auto load_row = [&](int64_t tile) __attribute__((always_inline)) {
+        const int64_t pos = tile * MB + s;
+        x[0] = x[1] = x[2] = x[3] = yt = 0.f;
+        if (pos < a.count) {
+            // N < 2^31, so the product stays below 2^62
+            const uint64_t k = (uint64_t)(a.row0 + pos) % (uint64_t)a.N;
+            const int64_t row = (int64_t)((a.pa * k + a.pb) % (uint64_t)a.N);
+            if (4 * g < XS)
+                for (int j = 0; j < 4; j++) x[j] = a.X[row * XS + 4 * g + j];
+            yt = a.y[row];
+        }
+    };
+    load_row(blockIdx.x);
+    {
+        // all of the weights' reads in flight at once
+        float v1[NIN * NH / 256], v2[NH * NH / 256], v3[NH * NH / 256];
+#pragma unroll
+        for (int i = 0; i < NIN * NH / 256; i++) v1[i] = a.p[O_W1 + 256 * i + tid];
+#pragma unroll
+        for (int i = 0; i < NH * NH / 256; i++) v2[i] = a.p[O_W2 + 256 * i + tid];
+#pragma unroll
+        for (int i = 0; i < NH * NH / 256; i++) v3[i] = a.p[O_W3 + 256 * i + tid];
+#pragma unroll
+        for (int i = 0; i < NIN * NH / 256; i++) W1[4 * i + wv][lane] = bf16r(v1[i]);
+#pragma unroll
+        for (int i = 0; i < NH * NH / 256; i++) W2[4 * i + wv][lane] = bf16r(v2[i]);
+#pragma unroll
+        for (int i = 0; i < NH * NH / 256; i++) W3[4 * i + wv][lane] = bf16r(v3[i]);
     }
     if (tid < NH) {
         bb[0][tid] = a.p[O_B1 + tid];
@@ -286,137 +373,151 @@ __global__ __launch_bounds__(256) void k_mlp_fb(TrainArgs a)
         rxsd[tid] = 1.0f / a.p[O_XSD + tid];
     }
     const float b4 = a.p[O_B4], ymu = a.p[O_YMU], rysd = 1.0f / a.p[O_YSD];
-    const int s = tid >> 3, q = tid & 7;   // sample, eighth of the units
-    // this thread's share of the gradient, summed over the workgroup's tiles:
-    // W2, W3 row kw = tid/4, columns 16 (tid%4) .. +15; W1 row k1 = tid/16,
-    // columns 4 (tid%16) .. +3; unit tid of b1, b2, b3, w4 (tid < NH); b4
-    // and the loss (tid 0)
-    const int kw = tid >> 2, c0 = 16 * (tid & 3);
-    const int k1 = tid >> 4, c1 = 4 * (tid & 15);
-    float accW[2][16], acc1[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int j = 0; j < 16; j++) accW[0][j] = accW[1][j] = 0.f;
-    float g1 = 0.f, g2 = 0.f, g3 = 0.f, g4 = 0.f, gb = 0.f, Lsum = 0.f;
+    // this wave's share of the gradient, summed over the workgroup's tiles:
+    // rows 16 wv .. +15 of W2 and W3, columns 16 wv .. +15 of W1; this lane's
+    // unit of b1, b2, b3 or w4 (wv = 0..3); its rows' share of b4 and the loss
+    f32x4 acc2[4], acc3[4], acc1 = {0.f, 0.f, 0.f, 0.f};
+    for (int o = 0; o < 4; o++) acc2[o] = acc3[o] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float gu = 0.f, gb = 0.f, Lsum = 0.f;
     const int64_t n_tiles = (a.count + MB - 1) / MB;
     for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-        const int64_t pos = tile * MB + s;
-        const bool valid = pos < a.count;
-        int64_t row = 0;
-        if (valid) {
-            // N < 2^31, so the product stays below 2^62
-            const uint64_t k = (uint64_t)(a.row0 + pos) % (uint64_t)a.N;
-            row = (int64_t)((a.pa * k + a.pb) % (uint64_t)a.N);
-        }
+        const bool valid = tile * MB + s < a.count;
         // weights loaded; the previous tile's readers of xh, hA, dA are done
         __syncthreads();
-        // standardised inputs: thread (s, q) loads inputs 2q, 2q+1
-        for (int j = 0; j < 2; j++) {
-            const int k = 2 * q + j;
-            const float raw = (valid && k < XS) ? a.X[row * XS + k] : 0.f;
-            xh[s][k] = valid ? (raw - xmu[k]) * rxsd[k] : 0.f;
-        }
-        __syncthreads();
-        // forward: thread (s, q) computes units 8q..8q+7 of sample s
+        // standardised inputs 4g .. 4g+3 of row s
+        for (int j = 0; j < 4; j++) x[j] = valid ? (x[j] - xmu[4 * g + j]) * rxsd[4 * g + j] : 0.f;
+        *(f32x4*)&xh[s][4 * g] = f32x4{x[0], x[1], x[2], x[3]};
+        // forward
+        f32x4 z[4], h[4], ds[3][4];
         for (int l = 0; l < 3; l++) {
-            float z[8];
-            for (int j = 0; j < 8; j++) z[j] = bb[l][8 * q + j];
+            for (int o = 0; o < 4; o++) z[o] = *(const f32x4*)&bb[l][16 * o + 4 * g];
             if (l == 0) {
-                for (int k = 0; k < NIN; k++) {
-                    const float x = xh[s][k];
-                    for (int j = 0; j < 8; j++) z[j] += x * W1[k * NH + 8 * q + j];
+                for (int j = 0; j < 4; j++)
+                    for (int o = 0; o < 4; o++) z[o] = MFMA4(W1[4 * g + j][16 * o + col], x[j], z[o]);
+            } else
+                fb_layer<false>(l == 1 ? W2 : W3, h, z, g, col);
+            for (int o = 0; o < 4; o++) {
+                for (int j = 0; j < 4; j++) {
+                    const float sg = __builtin_amdgcn_rcpf(1.0f + __expf(-z[o][j]));
+                    h[o][j] = z[o][j] * sg;
+                    ds[l][o][j] = sg * (1.0f + z[o][j] * (1.0f - sg));
                 }
-            } else {
-                const float* Wl = l == 1 ? W2 : W3;
-                for (int k = 0; k < NH; k++) {
-                    const float x = hA[l - 1][s][k];
-                    for (int j = 0; j < 8; j++) z[j] += x * Wl[k * NH + 8 * q + j];
-                }
+                *(f32x4*)&hA[l][s][16 * o + 4 * g] = h[o];
             }
-            for (int j = 0; j < 8; j++) {
-                hA[l][s][8 * q + j] = silu_f(z[j]);
-                dA[l][s][8 * q + j] = dsilu_f(z[j]);
-            }
-            __syncthreads();
         }
         // output and dL/do
         float part = 0.f;
-        for (int j = 0; j < 8; j++) part += hA[2][s][8 * q + j] * w4[8 * q + j];
-        part += __shfl_xor(part, 1);
-        part += __shfl_xor(part, 2);
-        part += __shfl_xor(part, 4);
-        if (q == 0) {
-            float r = 0.f;
-            if (valid) r = part + b4 - (a.y[row] - ymu) * rysd;
-            dout[s] = r * a.inv_count;
-            red[s] = 0.5f * r * r;
+        for (int o = 0; o < 4; o++)
+            for (int j = 0; j < 4; j++) part += h[o][j] * w4[16 * o + 4 * g + j];
+        part += __shfl_xor(part, 16);
+        part += __shfl_xor(part, 32);
+        const float r = valid ? part + b4 - (yt - ymu) * rysd : 0.f;
+        const float dr = r * a.inv_count;
+        if (g == 0) {
+            dout[s] = dr;
+            gb += dr;
+            Lsum += 0.5f * r * r;
         }
+        // backward through the layers: z becomes dL/dz_l
+        for (int o = 0; o < 4; o++)
+            for (int j = 0; j < 4; j++) z[o][j] = ds[2][o][j] * (dr * w4[16 * o + 4 * g + j]);
+        for (int l = 2; l >= 0; l--) {
+            for (int o = 0; o < 4; o++) *(f32x4*)&dA[l][s][16 * o + 4 * g] = z[o];
+            if (l == 0) break;
+            f32x4 dh[4];
+            for (int o = 0; o < 4; o++) dh[o] = f32x4{0.f, 0.f, 0.f, 0.f};
+            fb_layer<true>(l == 2 ? W3 : W2, z, dh, g, col);
+            for (int o = 0; o < 4; o++) z[o] = ds[l - 1][o] * dh[o];
+        }
+        if (tile + gridDim.x < n_tiles) load_row(tile + gridDim.x);
         __syncthreads();
-        // backward through the layers: dA[l] becomes dL/dz_l
-        for (int j = 0; j < 8; j++) dA[2][s][8 * q + j] *= dout[s] * w4[8 * q + j];
-        __syncthreads();
-        for (int l = 2; l >= 1; l--) {
-            const float* Wl = l == 2 ? W3 : W2;
-            float dh[8];
-            for (int j = 0; j < 8; j++) dh[j] = 0.f;
-            for (int k = 0; k < NH; k++) {
-                const float d = dA[l][s][k];
-                for (int j = 0; j < 8; j++) dh[j] += d * Wl[(8 * q + j) * NH + k];
+        // this tile's contribution to the gradient: step (k, j) contracts the
+        // rows 16 k + 4 g + j
+        float va[2][3], vb[2][9];
+        auto rows = [&](int i, float* pa, float* pb) __attribute__((always_inline)) {
+            const int r0 = 16 * (i / 4) + 4 * g + i % 4;
+            pa[0] = xh[r0][col];
+            pa[1] = hA[0][r0][16 * wv + col];
+            pa[2] = hA[1][r0][16 * wv + col];
+            pb[8] = dA[0][r0][16 * wv + col];
+#pragma unroll
+            for (int o = 0; o < 4; o++) {
+                pb[o] = dA[1][r0][16 * o + col];
+                pb[4 + o] = dA[2][r0][16 * o + col];
             }
-            for (int j = 0; j < 8; j++) dA[l - 1][s][8 * q + j] *= dh[j];
-            __syncthreads();
+        };
+        rows(0, va[0], vb[0]);
+#pragma unroll
+        for (int i = 0; i < MB / 4; i++) {
+            if (i + 1 < MB / 4) rows(i + 1, va[(i + 1) & 1], vb[(i + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+            const float *pa = va[i & 1], *pb = vb[i & 1];
+            acc1 = MFMA4(pa[0], pb[8], acc1);
+#pragma unroll
+            for (int o = 0; o < 4; o++) {
+                acc2[o] = MFMA4(pa[1], pb[o], acc2[o]);
+                acc3[o] = MFMA4(pa[2], pb[4 + o], acc3[o]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
-        // this tile's contribution to the gradient
-        for (int l = 1; l <= 2; l++)
-            for (int r = 0; r < MB; r++) {
-                const float hv = hA[l - 1][r][kw];
-                for (int j = 0; j < 16; j++) accW[l - 1][j] += hv * dA[l][r][c0 + j];
-            }
-        for (int r = 0; r < MB; r++) {
-            const float xv = xh[r][k1];
-            for (int j = 0; j < 4; j++) acc1[j] += xv * dA[0][r][c1 + j];
-        }
-        if (tid < NH)
-            for (int r = 0; r < MB; r++) {
-                g1 += dA[0][r][tid];
-                g2 += dA[1][r][tid];
-                g3 += dA[2][r][tid];
-                g4 += hA[2][r][tid] * dout[r];
-            }
-        if (tid == 0)
-            for (int r = 0; r < MB; r++) {
-                gb += dout[r];
-                Lsum += red[r];
-            }
+        if (wv < 3)
+#pragma unroll 16
+            for (int k = 0; k < MB; k++) gu += dA[wv][k][lane];
+        else
+#pragma unroll 16
+            for (int k = 0; k < MB; k++) gu += hA[2][k][lane] * dout[k];
     }
     // partial gradients of this workgroup (every one of the NT entries)
     float* G = a.part + (size_t)blockIdx.x * NT;
-    for (int j = 0; j < 16; j++) {
-        G[O_W2 + kw * NH + c0 + j] = accW[0][j];
-        G[O_W3 + kw * NH + c0 + j] = accW[1][j];
+    for (int j = 0; j < 4; j++) {
+        const int row = 16 * wv + 4 * g + j;
+        for (int o = 0; o < 4; o++) {
+            G[O_W2 + row * NH + 16 * o + col] = acc2[o][j];
+            G[O_W3 + row * NH + 16 * o + col] = acc3[o][j];
+        }
+        G[O_W1 + (4 * g + j) * NH + 16 * wv + col] = acc1[j];
     }
-    for (int j = 0; j < 4; j++) G[O_W1 + k1 * NH + c1 + j] = acc1[j];
-    if (tid < NH) {
-        G[O_B1 + tid] = g1;
-        G[O_B2 + tid] = g2;
-        G[O_B3 + tid] = g3;
-        G[O_W4 + tid] = g4;
+    G[(wv == 0 ? O_B1 : wv == 1 ? O_B2 : wv == 2 ? O_B3 : O_W4) + lane] = gu;
+    for (int off = 8; off > 0; off >>= 1) {
+        gb += __shfl_xor(gb, off);
+        Lsum += __shfl_xor(Lsum, off);
     }
+    if (lane == 0) {
+        red[0][wv] = gb;
+        red[1][wv] = Lsum;
+    }
+    __syncthreads();
     if (tid == 0) {
-        G[O_B4] = gb;
-        a.part_loss[blockIdx.x] = Lsum;
+        G[O_B4] = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
+        a.part_loss[blockIdx.x] = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
     }
 }
 
 // Sum of the workgroup partials; then either store the gradient or apply
-// one Adam step (adam != 0).  Thread 0 also sums the loss.
-__global__ __launch_bounds__(256) void k_mlp_reduce(const float* __restrict__ part, const float* __restrict__ part_loss,
-                                                    int nwg, float inv_count, float* grad, float* p, float* m, float* v,
-                                                    int adam, float lr, float b1, float b2, float eps, float c1,
-                                                    float c2, float* loss_out)
+// one Adam step (adam != 0).  The first workgroup also sums the loss.
+// Latency bound: one entry per lane, and the RED_WAVES waves of a workgroup
+// each sum every RED_WAVES-th partial, so that a wave has all its reads in
+// flight at once (256 partials of 9473 entries: 71 us by one thread per entry
+// in turn, 5 us now).
+#define RED_WAVES 16
+__global__ __launch_bounds__(64 * RED_WAVES) void k_mlp_reduce(const float* __restrict__ part,
+                                                               const float* __restrict__ part_loss, int nwg,
+                                                               float inv_count, float* grad, float* p, float* m,
+                                                               float* v, int adam, float lr, float b1, float b2,
+                                                               float eps, float c1, float c2, float* loss_out)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ float sums[RED_WAVES][64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int i = blockIdx.x * 64 + lane;
+    float g = 0.f;
     if (i < NT) {
-        float g = 0.f;
-        for (int w = 0; w < nwg; w++) g += part[(size_t)w * NT + i];
+#pragma unroll 16
+        for (int w = wv; w < nwg; w += RED_WAVES) g += part[(size_t)w * NT + i];
+    }
+    sums[wv][lane] = g;
+    __syncthreads();
+    if (wv == 0 && i < NT) {
+        for (int w = 1; w < RED_WAVES; w++) g += sums[w][lane];
         if (grad) grad[i] = g;
         if (adam) {
             const float mi = b1 * m[i] + (1.f - b1) * g;
@@ -426,10 +527,11 @@ __global__ __launch_bounds__(256) void k_mlp_reduce(const float* __restrict__ pa
             p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
         }
     }
-    if (i == 0 && loss_out) {
+    if (blockIdx.x == 0 && wv == 1 && loss_out) {
         double L = 0.0;
-        for (int w = 0; w < nwg; w++) L += part_loss[w];
-        *loss_out = (float)(L * inv_count);
+        for (int w = lane; w < nwg; w += 64) L += part_loss[w];
+        for (int off = 32; off > 0; off >>= 1) L += __shfl_xor(L, off);
+        if (lane == 0) *loss_out = (float)(L * inv_count);
     }
 }
 
@@ -614,7 +716,7 @@ __global__ __launch_bounds__(256) void k_record(int64_t n, const float* __restri
 // ---------------------------------------------------------------------------
 static sph_status pack(const float* p, MlpPacked* w, hipStream_t s)
 {
-    k_mlp_pack<<<nblocks(4 * 64 + 2 * 16 * 64, 256), 256, 0, s>>>(p, w);
+    k_mlp_pack<<<nblocks(4 * 64 + 2 * 8 * 64, 256), 256, 0, s>>>(p, w);
     SPH_CHECK_LAUNCH();
     return SPH_OK;
 }
@@ -655,7 +757,7 @@ static sph_status fb_reduce(float* part, float* part_loss, const float* p, const
     SPH_CHECK_LAUNCH();
     const float c1 = adam ? (float)(1.0 - pow((double)b1, t)) : 1.f;
     const float c2 = adam ? (float)(1.0 - pow((double)b2, t)) : 1.f;
-    k_mlp_reduce<<<nblocks(NT, 256), 256, 0, s>>>(part, part_loss, nwg, 1.0f / (float)count, grad, pw, m, v,
+    k_mlp_reduce<<<nblocks(NT, 64), 64 * RED_WAVES, 0, s>>>(part, part_loss, nwg, 1.0f / (float)count, grad, pw, m, v,
                                                    adam ? 1 : 0, lr, b1, b2, eps, c1, c2, loss_slot);
     SPH_CHECK_LAUNCH();
     return SPH_OK;
