@@ -2,15 +2,14 @@
 // Sec. 2, eq. (interp)): Q(r) = sum_i m_i Q_i / rho_i W(|r - r_i|, H_i), each
 // particle contributing within its own support H_i.
 //
-// The points are first ordered by box and Morton code of their position, so
-// that the 64 points of a wave lie close together.  A wave whose points share
-// a box and fit in a top cell (point sets dense against H) walks the octree of
-// the last build once for all of them: cells farther from the wave's point box
-// than their largest H are pruned, a leaf's particles are loaded one per lane
-// and broadcast to the points with readlane, and only the particles that can
-// reach the point box are visited.  Other waves (points sparse against H,
-// several boxes, invalid points) walk the tree point by point, on nearby
-// paths thanks to the order.
+// The points are first ordered by box and Morton code of their position and
+// cut into blocks of up to 64 that share a box and fit in a top cell.  A wave
+// walks the octree of the last build once for a block, 64 cells at a time:
+// cells farther from the block's bounding box than their largest H are
+// pruned, the leaves left are listed.  The leaves of the blocks of a workgroup
+// are then shared out evenly between its waves, whichever block they belong
+// to; their particles are tested against the points on the matrix units and
+// the pairs in range summed one per lane (sph_device.h).
 //
 // Distances are minimum-image: every H is below half the box (the top cells
 // are at least H wide and there are at least three per axis), so at most one
@@ -20,6 +19,7 @@
 #include <math.h>
 
 #include "sph_ctx.h"
+#include "sph_device.h"
 
 #define INTERP_INV_PI_8 2.5464790894703255  // 8/pi
 #define INTERP_MBITS 10                    // Morton bits per axis of the sort key
@@ -40,33 +40,29 @@ struct InterpArgs {
     const uint32_t* perm;  // sorted position -> point index
 };
 
+// sqrt(x) for 0 <= x <= 4 to an ulp: the hardware's estimate of 1/sqrt and two
+// coupled Newton steps, without the scaling that other arguments need.
+__device__ inline double interp_sqrt(double x)
+{
+    x = fmax(x, 1e-290);
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double e = fma(-h, g, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+    return fma(fma(-g, g, x), h, g);
+}
+
+// Kernel of q >= 0 without 8 / (pi H^3)
 __device__ inline double interp_w(double q)
 {
-    if (!(q < 1.0)) return 0.0;
-    return q <= 0.5 ? 1.0 + q * q * (6.0 * q - 6.0) : 2.0 * (1.0 - q) * (1.0 - q) * (1.0 - q);
+    const double t = 1.0 - q;
+    const double in = fma(q * q, fma(6.0, q, -6.0), 1.0), out = 2.0 * t * t * t;
+    return q <= 0.5 ? in : out;
 }
 
-__device__ inline double min_image(double d, double L) { return d - L * rint(d / L); }
-
-__device__ inline double wave_min_d(double v)
-{
-    for (int off = 32; off > 0; off >>= 1) v = fmin(v, __shfl_xor(v, off));
-    return v;
-}
-
-__device__ inline double wave_max_d(double v)
-{
-    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off));
-    return v;
-}
-
-__device__ inline double readlane_d(double v, int l)
-{
-    const unsigned long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)(uint32_t)b, l);
-    const int hi = __builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l);
-    return __longlong_as_double(((long long)(uint32_t)hi << 32) | (uint32_t)lo);
-}
+// Offset d along an axis of length L = 1 / iL as that of the nearest image.
+__device__ inline double min_image(double d, double L, double iL) { return fma(-L, rint(d * iL), d); }
 
 // Validated point k wrapped into its box; false for a bad box index or a
 // non-finite coordinate.
@@ -102,62 +98,9 @@ __device__ inline void top_range(const DomainInfo& I, const double lo[3], const 
 __device__ inline int top_index(const DomainInfo& I, const int t0[3], int ix, int iy, int iz)
 {
     int c[3] = {t0[0] + ix, t0[1] + iy, t0[2] + iz};
-    for (int q = 0; q < 3; q++) c[q] = ((c[q] % I.n_top[q]) + I.n_top[q]) % I.n_top[q];
+    // (a range that is not the whole axis begins above -n_top and ends below 2 n_top)
+    for (int q = 0; q < 3; q++) c[q] += c[q] < 0 ? I.n_top[q] : c[q] >= I.n_top[q] ? -I.n_top[q] : 0;
     return I.top_offset + (c[0] * I.n_top[1] + c[1]) * I.n_top[2] + c[2];
-}
-
-// Squared minimum-image gap between a node's box and the box of centre c,
-// half-widths hw.
-__device__ inline double node_gap2(const Node& nd, const DomainInfo& I, const double c[3], const double hw[3])
-{
-    double d2 = 0.0;
-    for (int q = 0; q < 3; q++) {
-        const double half = 0.5 * (nd.hi[q] - nd.lo[q]);
-        const double g = fmax(fabs(min_image(c[q] - 0.5 * (nd.lo[q] + nd.hi[q]), I.L[q])) - half - hw[q], 0.0);
-        d2 += g * g;
-    }
-    return d2;
-}
-
-// One point, its own walk.
-__device__ double interp_point(const InterpArgs& a, const DomainInfo& I, const double p[3])
-{
-    int t0[3], nt[3];
-    top_range(I, p, p, a.margin, t0, nt);
-    const double hw[3] = {0.0, 0.0, 0.0};
-    double sum = 0.0;
-    for (int ix = 0; ix < nt[0]; ix++)
-    for (int iy = 0; iy < nt[1]; iy++)
-    for (int iz = 0; iz < nt[2]; iz++) {
-        int kk = top_index(I, t0, ix, iy, iz);
-        while (kk >= 0) {
-            const WNode w = a.wn[kk];
-            if (w.count == 0) {
-                kk = w.next;
-                continue;
-            }
-            const Node& nd = a.nodes[kk];
-            const double reach = nd.hmax + a.margin;
-            if (node_gap2(nd, I, p, hw) >= reach * reach) {
-                kk = w.next;
-                continue;
-            }
-            if (w.first_child >= 0) {
-                kk = w.first_child;
-                continue;
-            }
-            kk = w.next;
-            for (int i = nd.begin; i < nd.begin + nd.count; i++) {
-                const double dx = min_image(p[0] - a.x[i], I.L[0]);
-                const double dy = min_image(p[1] - a.y[i], I.L[1]);
-                const double dz = min_image(p[2] - a.z[i], I.L[2]);
-                const double r = sqrt(dx * dx + dy * dy + dz * dz);
-                const double h = a.H[i];
-                if (r < h) sum += a.m[i] * a.Q[i] / a.rho[i] * INTERP_INV_PI_8 / (h * h * h) * interp_w(r / h);
-            }
-        }
-    }
-    return sum;
 }
 
 // Sort keys: box index in the high bits, Morton code of the position
@@ -185,89 +128,314 @@ __global__ __launch_bounds__(256) void k_interp_keys(InterpArgs a, uint64_t* key
     vals[k] = (uint32_t)k;
 }
 
-// One wave per 64 consecutive points of the sorted order.
-__global__ __launch_bounds__(256) void k_interp_wave(InterpArgs a)
+// Waves of a workgroup, leaves a wave lists at a time, cells its walk holds.
+#define IW 8
+#define ILEAF 192
+#define ISTACK 512
+#define IROW 16  // candidates per 16-lane row of a tile
+
+// Candidates of one wave: up to 4 IROW particles that can reach the block.
+struct ITile {
+    double4 cand[4 * IROW];       // relative to the block's centre, scaled; w: H, then 1/H^2
+    double cf[4 * IROW];          // particle index, then m Q / rho 8 / (pi H^3)
+    union {
+        float c1[4 * IROW];       // row constants of the range tests
+        uint16_t list[PAIR_CAP];  // then the pairs
+    };
+};
+struct ILeaf { int begin, count; };
+struct IBlock {
+    double p[3][64];    // points relative to the centre, scaled
+    double c[3], hw[3]; // bounding box: centre, half-widths
+    double sc, isc;     // power of two that makes the box's top cells of order 1, its inverse
+    double L[3], iL[3]; // edges of the box, their inverses
+    unsigned long long sel;  // lanes with a point of the block
+    int dom, n_leaf;
+};
+
+// One workgroup per IW groups of G consecutive points of the sorted order, a
+// wave per group.  Rounds: each wave takes the next block of its group (or
+// goes on with one that filled its list) and lists leaves; then all waves
+// share all leaves; then each wave adds up its block's sums.  Sums are made in
+// the same order whatever the timing.
+//
+// Was bound by the few waves with a halo in their block (one wave per 64
+// points, cells and leaves one after another: the fullest of 128^3 mesh points
+// over 96^3 clustered particles visits 11373 particles, the mean 154) and by
+// 65 FP64 instructions per particle visited with 22% of the lanes in range.
+// That mesh: 2.87 ms before, 0.73 ms now (VALU active 63% of the time; the rest is
+// the walk's latency, with 4 waves a SIMD in 79 KB of LDS and 128 registers).
+// 4 waves a workgroup: 2% less time there, but twice the longest share; 16: 9%
+// more.
+__global__ __launch_bounds__(64 * IW, 4) void k_interp_blocks(InterpArgs a, int G)
 {
-    const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (w * 64 >= a.m_pts) return;
-    const int64_t s = w * 64 + lane;
-    const bool inr = s < a.m_pts;
+    __shared__ ITile tile[IW];
+    __shared__ IBlock blk[IW];
+    __shared__ ILeaf leaf[IW][ILEAF];
+    __shared__ int stack[IW][ISTACK];
+    __shared__ double S0[IW][64], S1[IW][64];
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    ITile& L = tile[wv];
+    const int64_t s = ((int64_t)blockIdx.x * IW + wv) * G + lane;
+    const bool inr = lane < G && s < a.m_pts;
     const int64_t k = inr ? (int64_t)a.perm[s] : 0;
     double p[3] = {0.0, 0.0, 0.0};
     int d = -1;
     const bool ok = inr && load_point(a, k, p, d);
     if (inr && !ok) a.out[k] = NAN;
-    const unsigned long long okm = __ballot(ok);
-    if (okm == 0ull) return;
-    const int d0 = __builtin_amdgcn_readlane(d, __ffsll((long long)okm) - 1);
-    const DomainInfo& I = a.di[d0];
-    const double big = 1e300;
-    double lo[3], hi[3], c[3], hw[3];
-    double ext = 0.0;
-    for (int q = 0; q < 3; q++) {
-        lo[q] = wave_min_d(ok ? p[q] : big);
-        hi[q] = wave_max_d(ok ? p[q] : -big);
-        c[q] = 0.5 * (lo[q] + hi[q]);
-        hw[q] = 0.5 * (hi[q] - lo[q]);
-        ext = fmax(ext, hi[q] - lo[q]);
-    }
-    const double s0min = fmin(fmin(I.s0[0], I.s0[1]), I.s0[2]);
-    if (__ballot(ok && d != d0) != 0ull || !(ext <= s0min)) {
-        if (ok) a.out[k] = interp_point(a, a.di[d], p);
-        return;
-    }
-    int t0[3], nt[3];
-    top_range(I, lo, hi, a.margin, t0, nt);
+    unsigned long long rest = __ballot(ok);  // points in no block yet
+    bool open = false;                       // the block's walk is under way
+    unsigned long long sel = 0ull;
+    int size = 0, tcur = 0, ntop = 0, t0[3] = {0, 0, 0}, nt[3] = {0, 0, 0};
     double sum = 0.0;
-    for (int ix = 0; ix < nt[0]; ix++)
-    for (int iy = 0; iy < nt[1]; iy++)
-    for (int iz = 0; iz < nt[2]; iz++) {
-        int kk = __builtin_amdgcn_readfirstlane(top_index(I, t0, ix, iy, iz));
-        while (kk >= 0) {
-            const WNode wv = a.wn[kk];
-            if (wv.count == 0) {
-                kk = __builtin_amdgcn_readfirstlane(wv.next);
-                continue;
-            }
-            const Node& nd = a.nodes[kk];
-            const double reach = nd.hmax + a.margin;
-            if (node_gap2(nd, I, c, hw) >= reach * reach) {
-                kk = __builtin_amdgcn_readfirstlane(wv.next);
-                continue;
-            }
-            if (wv.first_child >= 0) {
-                kk = __builtin_amdgcn_readfirstlane(wv.first_child);
-                continue;
-            }
-            kk = __builtin_amdgcn_readfirstlane(wv.next);
-            const int b = nd.begin, n = nd.count;
-            for (int p0 = 0; p0 < n; p0 += 64) {
-                const bool has = p0 + lane < n;
-                const int j = b + p0 + (has ? lane : 0);
-                // the particle's image nearest the point box, its gap to that box
-                double xj[3], g2 = 0.0;
-                const double hj = a.H[j];
-                {
-                    const double r[3] = {a.x[j], a.y[j], a.z[j]};
+    while (__syncthreads_or(open || rest != 0ull)) {
+        IBlock& B = blk[wv];
+        if (!open) {
+            // the largest aligned run of 64, 32, .. 1 lanes from the next point
+            // on whose points share a box and fit in a top cell
+            sel = 0ull;
+            size = tcur = ntop = 0;
+            if (rest) {
+                const int l0 = __builtin_ctzll(rest);
+                const int d0 = __builtin_amdgcn_readlane(d, l0);
+                const DomainInfo& I = a.di[d0];
+                const double s0min = fmin(fmin(I.s0[0], I.s0[1]), I.s0[2]);
+                double lo[3], hi[3];
+                for (int g = 64; g > 0; g >>= 1) {
+                    sel = rest & ((g == 64 ? ~0ull : (1ull << g) - 1ull) << (l0 & ~(g - 1)));
+                    const bool in = (sel >> lane) & 1ull;
+                    double ext = 0.0;
                     for (int q = 0; q < 3; q++) {
-                        xj[q] = c[q] + min_image(r[q] - c[q], I.L[q]);
-                        const double g = fmax(fabs(xj[q] - c[q]) - hw[q], 0.0);
-                        g2 += g * g;
+                        lo[q] = wave_min_t(in ? p[q] : 1e300);
+                        hi[q] = wave_max_t(in ? p[q] : -1e300);
+                        ext = fmax(ext, hi[q] - lo[q]);
+                    }
+                    if (__ballot(in && d != d0) == 0ull && ext <= s0min) break;
+                }
+                top_range(I, lo, hi, a.margin, t0, nt);
+                ntop = nt[0] * nt[1] * nt[2];
+                const double sc = pow2_scale(s0min);
+                const bool in = (sel >> lane) & 1ull;
+                for (int q = 0; q < 3; q++) {
+                    const double c = 0.5 * (lo[q] + hi[q]);
+                    B.p[q][lane] = in ? (p[q] - c) * sc : 0.0;
+                    if (lane == 0) {
+                        B.c[q] = c;
+                        B.hw[q] = 0.5 * (hi[q] - lo[q]);
+                        B.L[q] = I.L[q];
+                        B.iL[q] = 1.0 / I.L[q];
                     }
                 }
-                const double cf = has ? a.m[j] * a.Q[j] / a.rho[j] * INTERP_INV_PI_8 / (hj * hj * hj) : 0.0;
-                const double ih = 1.0 / hj, h2 = hj * hj;
-                for (unsigned long long mk = __ballot(has && g2 < h2); mk; mk &= mk - 1ull) {
-                    const int l = __ffsll((long long)mk) - 1;
-                    const double jx = readlane_d(xj[0], l), jy = readlane_d(xj[1], l), jz = readlane_d(xj[2], l);
-                    const double jh2 = readlane_d(h2, l);
-                    const double dx = p[0] - jx, dy = p[1] - jy, dz = p[2] - jz;
-                    const double r2 = dx * dx + dy * dy + dz * dz;
-                    if (ok && r2 < jh2) sum += readlane_d(cf, l) * interp_w(sqrt(r2) * readlane_d(ih, l));
+                if (lane == 0) {
+                    B.sc = sc;
+                    B.isc = 1.0 / sc;
+                    B.sel = sel;
+                    B.dom = d0;
                 }
+                rest &= ~sel;
+                open = true;
+                wave_sync();
             }
         }
+        // list leaves until the walk ends or the list is full
+        int nl = 0;
+        if (open) {
+            const DomainInfo& I = a.di[B.dom];
+            const double bc[3] = {B.c[0], B.c[1], B.c[2]}, bw[3] = {B.hw[0], B.hw[1], B.hw[2]};
+            while (nl <= ILEAF - 64) {
+                int kk = -1;
+                if (size > 0) {
+                    // at most 7 cells more for each taken: even one a time from
+                    // here down all levels stays within the stack
+                    const int t = min(min(64, size), max(1, (ISTACK - 8 * 24 - size) / 7));
+                    if (lane < t) kk = stack[wv][size - t + lane];
+                    size -= t;
+                } else if (tcur < ntop) {
+                    const int t = min(min(64, ntop - tcur), (ISTACK - 8 * 24) / 8);
+                    if (lane < t) {
+                        // (exact: the quotients are far below 2^20)
+                        const int id = tcur + lane;
+                        const int r = (int)((id + 0.5f) * __builtin_amdgcn_rcpf((float)nt[2]));
+                        const int ix = (int)((r + 0.5f) * __builtin_amdgcn_rcpf((float)nt[1]));
+                        kk = top_index(I, t0, ix, r - ix * nt[1], id - r * nt[2]);
+                    }
+                    tcur += t;
+                } else {
+                    open = false;
+                    break;
+                }
+                wave_sync();
+                int fc = -1, nc = 0;
+                ILeaf lf = {0, 0};
+                bool keep = false;
+                if (kk >= 0) {
+                    const Node& nd = a.nodes[kk];
+                    fc = nd.first_child;
+                    nc = nd.n_child;
+                    lf.begin = nd.begin;
+                    lf.count = nd.count;
+                    // squared gap between the cell's box and the block's
+                    double d2 = 0.0;
+                    for (int q = 0; q < 3; q++) {
+                        const double nlo = nd.lo[q], nhi = nd.hi[q];
+                        const double g = fmax(fabs(min_image(bc[q] - 0.5 * (nlo + nhi), B.L[q], B.iL[q])) -
+                                                  0.5 * (nhi - nlo) - bw[q], 0.0);
+                        d2 += g * g;
+                    }
+                    const double reach = nd.hmax + a.margin;
+                    keep = lf.count > 0 && d2 < reach * reach;
+                }
+                const bool is_leaf = keep && fc < 0;
+                const unsigned long long lm = __ballot(is_leaf);
+                if (is_leaf) leaf[wv][nl + lane_rank(lm)] = lf;
+                nl += __popcll(lm);
+                if (!keep || is_leaf) nc = 0;
+                for (int q = 0; __ballot(q < nc) != 0ull; q++) {
+                    const unsigned long long cm = __ballot(q < nc);
+                    if (q < nc) stack[wv][size + lane_rank(cm)] = fc + q;
+                    size += __popcll(cm);
+                }
+                wave_sync();
+            }
+        }
+        if (lane == 0) B.n_leaf = nl;
+        S0[wv][lane] = S1[wv][lane] = 0.0;
+        __syncthreads();
+        // share of wave w: leaves [N w / IW, N (w + 1) / IW) of all blocks'
+        int N = 0, own = 0;  // leaves of all blocks, of those before this wave's
+#pragma unroll
+        for (int w = 0; w < IW; w++) {
+            if (w == wv) own = N;
+            N += __builtin_amdgcn_readfirstlane(blk[w].n_leaf);
+        }
+        const int end = N * (wv + 1) / IW;
+        for (int b = 0, pb = 0, pe = 0, at = N * wv / IW; at < end; b++, pb = pe) {
+            pe = pb + __builtin_amdgcn_readfirstlane(blk[b].n_leaf);
+            if (at >= pe) continue;
+            const int e = min(end, pe);
+            const IBlock& Q = blk[b];
+            // sums of the wave that begins a block, and of those that go on
+            double* acc = at == pb ? S0[b] : S1[wv];
+            const double sc = Q.sc, isc = Q.isc;
+            float b1[4];
+            {
+                const float x = (float)Q.p[0][lane], y = (float)Q.p[1][lane], z = (float)Q.p[2][lane];
+                const bool on = (Q.sel >> lane) & 1ull;
+                test_operand(x, y, z, on ? (x * x + y * y + z * z) * (1.0f - PAIR_EPS) - 1e-30f : 1e30f,
+                             (float4*)L.cand, lane, b1);
+            }
+            const int nb = 4 - (__builtin_clzll(Q.sel) >> 4);
+            auto eval = [&](const uint16_t* list, int n) __attribute__((always_inline)) {
+                const int K = (n + 63) >> 6;
+                int cur = -1;
+                double v = 0.0, x = 0.0, y = 0.0, z = 0.0;
+                for (int i = lane * K; i < min(lane * K + K, n); i++) {
+                    const int code = list[i], ii = code >> 7;
+                    if (ii != cur) {
+                        if (cur >= 0) lds_add(&acc[cur], v);
+                        cur = ii;
+                        x = Q.p[0][ii];
+                        y = Q.p[1][ii];
+                        z = Q.p[2][ii];
+                        v = 0.0;
+                    }
+                    const double4 c = L.cand[code & 127];
+                    const double dx = c.x - x, dy = c.y - y, dz = c.z - z;
+                    const double q2 = fma(dx, dx, fma(dy, dy, dz * dz)) * c.w;
+                    const double w = L.cf[code & 127] * interp_w(interp_sqrt(q2));
+                    v += q2 < 1.0 ? w : 0.0;
+                }
+                if (cur >= 0) lds_add(&acc[cur], v);
+            };
+            auto run_tile = [&](int len) __attribute__((always_inline)) {
+                for (int j = len + lane; j < 4 * IROW; j += 64) {
+                    L.cand[j] = make_double4(0.0, 0.0, 0.0, 1.0);
+                    L.c1[test_slot<IROW>(j)] = 1e30f;
+                }
+                wave_sync();
+                // the weights, while the tests run
+                const bool has = lane < len;
+                const int j = has ? (int)L.cf[lane] : 0;
+                const double hs = L.cand[lane].w, h = hs * isc;
+                const double mj = a.m[j], qj = a.Q[j], rj = a.rho[j];
+                uint32_t M[4] = {0u, 0u, 0u, 0u};
+                tile_masks<false, IROW>(L.c1, nullptr, [&](int t) {
+                    const float v = (float)((const double*)&L.cand[t])[lane >> 4];
+                    return lane < 48 ? v : 1.0f;
+                }, b1, b1, nb, lane, M);
+                // (a row of IROW bits, the first candidate's at bit IROW - 1)
+                for_pairs<IROW>(M, L.list, lane, [&]() {
+                    wave_sync();
+                    L.cf[lane] = mj * qj / rj * INTERP_INV_PI_8 / (h * h * h);
+                    L.cand[lane].w = 1.0 / (hs * hs);
+                }, eval);
+                wave_sync();
+            };
+            int ncand = 0, li = at - pb, p0 = 0;
+            const int le = e - pb;
+            ILeaf lf = {0, 0};
+            double r[3] = {0.0, 0.0, 0.0}, hj = 0.0;
+            auto load = [&]() __attribute__((always_inline)) {
+                lf = leaf[b][li];
+                const int j = lf.begin + min(p0 + lane, lf.count - 1);
+                r[0] = a.x[j];
+                r[1] = a.y[j];
+                r[2] = a.z[j];
+                hj = a.H[j];
+            };
+            load();
+            while (true) {
+                bool in = false;
+                int j = 0;
+                double x[3] = {0.0, 0.0, 0.0}, h = 0.0;
+                const bool more = li < le;
+                if (more) {
+                    // the particle's image nearest the block, its gap to the block
+                    double g2 = 0.0;
+                    for (int q = 0; q < 3; q++) {
+                        x[q] = min_image(r[q] - Q.c[q], Q.L[q], Q.iL[q]);
+                        const double g = fmax(fabs(x[q]) - Q.hw[q], 0.0);
+                        g2 += g * g;
+                    }
+                    h = hj;
+                    j = lf.begin + p0 + lane;
+                    in = p0 + lane < lf.count && g2 < h * h;
+                    p0 += 64;
+                    if (p0 >= lf.count) {
+                        li++;
+                        p0 = 0;
+                    }
+                    if (li < le) load();
+                }
+                const unsigned long long mk = __ballot(in);
+                const int nk = __popcll(mk);
+                if (ncand + nk > 4 * IROW || !more) {
+                    if (ncand > 0) run_tile(ncand);
+                    if (!more) break;
+                    ncand = 0;
+                }
+                if (in) {
+                    const int slot = ncand + lane_rank(mk);
+                    const double4 o = make_double4(x[0] * sc, x[1] * sc, x[2] * sc, h * sc);
+                    L.cand[slot] = o;
+                    L.cf[slot] = (double)j;
+                    const float fx = (float)o.x, fy = (float)o.y, fz = (float)o.z, fh = (float)o.w;
+                    L.c1[test_slot<IROW>(slot)] = (fx * fx + fy * fy + fz * fz) * (1.0f - PAIR_EPS) -
+                                                  fh * fh * (1.0f + PAIR_EPS);
+                }
+                ncand += nk;
+            }
+            at = e;
+        }
+        __syncthreads();
+        // the block's sum: its first wave's, then the later ones' in turn
+        double v = S0[wv][lane];
+#pragma unroll
+        for (int w = 1; w < IW; w++) {
+            const int f = N * w / IW;
+            if (f < N * (w + 1) / IW && f > own && f < own + nl) v += S1[w][lane];
+        }
+        if ((sel >> lane) & 1ull) sum += v;
     }
     if (ok) a.out[k] = sum;
 }
@@ -320,8 +488,11 @@ extern "C" sph_status sph_interpolate(sph_ctx* c, const double* Q, const double*
     int res = 0;
     SPH_TRY(radix_sort(c, (int)m_pts, bits, c->ikeys, c->ivals, &res));
     a.perm = (const uint32_t*)c->ivals[res].p;
-    const unsigned nw = (unsigned)((m_pts + 255) / 256);  // four waves of 64 points per workgroup
-    k_interp_wave<<<nw, 256, 0, c->stream>>>(a);
+    // points per wave: 64, fewer while that leaves less than 4096 waves (half
+    // of what the chip holds): few points wait on the longest walk
+    int G = 64;
+    while (G > 1 && m_pts < (int64_t)G * 4096) G >>= 1;
+    k_interp_blocks<<<(unsigned)((m_pts + IW * G - 1) / (IW * G)), 64 * IW, 0, c->stream>>>(a, G);
     SPH_CHECK_LAUNCH();
     return SPH_OK;
 }
