@@ -256,21 +256,65 @@ __device__ inline int lower_bound_u64(const uint64_t* a, int lo, int hi, uint64_
     return lo;
 }
 
-// Level-0 cells: the top grid of every box.
-__global__ __launch_bounds__(256) void k_top_nodes(int n_top_total, int ndom, const DomainInfo* __restrict__ di,
-                                                   const uint64_t* __restrict__ keys, int n, int D, Node* nodes)
+// ---------------------------------------------------------------------------
+// Octree levels.  Level l is nodes [FI_LEVEL + l, FI_LEVEL + l + 1) of the
+// offsets in the flags; each of its three launches reads them there, so that
+// several levels are enqueued before the host looks at any (a level beyond the
+// last finds no cells).  With a host read of the children's total and separate
+// launches for chunk counts, scans and chunk map, a level took nine launches
+// and 45 us of waiting: the build of 128^3 clustered particles (9 levels) 1.84
+// ms, 1.49 ms now.
+// ---------------------------------------------------------------------------
+
+// Statistics are gathered in chunks of up to STATS_CHUNK particles of one
+// cell: (cell, first particle) per chunk of the level, in any order.
+#define STATS_CHUNK 1024
+
+// Append the chunks of the lane's cell (count 0: none).  Every lane of the
+// wave takes part.
+__device__ inline void add_chunks(int node, int count, int2* cmap, int* n_chunks)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n_top_total) return;
+    const int lane = threadIdx.x & 63;
+    const int nc = (count + STATS_CHUNK - 1) / STATS_CHUNK;
+    int incl = nc;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int t = __shfl_up(incl, off);
+        if (lane >= off) incl += t;
+    }
+    const int all = __shfl(incl, 63);
+    if (all == 0) return;
+    int base = 0;
+    if (lane == 0) base = atomicAdd(n_chunks, all);
+    base = __shfl(base, 0) + incl - nc;
+    for (int j = 0; j < nc; j++) cmap[base + j] = make_int2(node, j);
+}
+
+// Level-0 cells: the top grid of every box.
+#define TOP_CELLS 255
+__global__ __launch_bounds__(256) void k_top_nodes(int n_top_total, int ndom, const DomainInfo* __restrict__ di,
+                                                   const uint64_t* __restrict__ keys, int n, int D, Node* nodes,
+                                                   int2* cmap, int* flags)
+{
+    // (a workgroup searches the first particles of 256 cells and one cell's end
+    // is the next one's begin: one chain of dependent reads, not two)
+    __shared__ int begin[256];
+    const int t = blockIdx.x * TOP_CELLS + threadIdx.x;
+    begin[threadIdx.x] = t <= n_top_total ? lower_bound_u64(keys, 0, n, (uint64_t)t << (3 * D)) : n;
+    __syncthreads();
+    if (t == 0) {
+        flags[FI_LEVEL] = 0;
+        flags[FI_LEVEL + 1] = n_top_total;
+    }
+    const bool has = threadIdx.x < TOP_CELLS && t < n_top_total;
     int d = 0;
-    while (d + 1 < ndom && di[d + 1].top_offset <= t) d++;
+    while (has && d + 1 < ndom && di[d + 1].top_offset <= t) d++;
     const DomainInfo& I = di[d];
     const int loc = t - I.top_offset;
     const int tz = loc % I.n_top[2], ty = (loc / I.n_top[2]) % I.n_top[1], tx = loc / (I.n_top[2] * I.n_top[1]);
     Node nd;
     nd.key_lo = (uint64_t)t << (3 * D);
-    nd.begin = lower_bound_u64(keys, 0, n, nd.key_lo);
-    nd.count = lower_bound_u64(keys, nd.begin, n, (uint64_t)(t + 1) << (3 * D)) - nd.begin;
+    nd.begin = begin[threadIdx.x];
+    nd.count = has ? begin[threadIdx.x + 1] - nd.begin : 0;
     nd.first_child = -1;
     nd.n_child = 0;
     nd.level = 0;
@@ -286,8 +330,9 @@ __global__ __launch_bounds__(256) void k_top_nodes(int n_top_total, int ndom, co
     nd.hmax = 0.0;
     nd.hmin = INFINITY;
     nd.merged = 0;
-    nd.pad = 0;
-    nodes[t] = nd;
+    nd.next = -1;
+    if (has) nodes[t] = nd;
+    add_chunks(t, nd.count, cmap, flags + FI_NCHUNK);
 }
 
 // Children of a split cell: octants holding more than n_split particles
@@ -332,15 +377,12 @@ __device__ inline bool extent_too_large(const Node& nd, double h_ratio)
 }
 
 // Statistics of the cells of one level (bounding box, largest and smallest
-// H) and the particle bounds of their octants, from chunks of up to
-// STATS_CHUNK particles of one cell, one wave per chunk.  Box corners and H
+// H) and the particle bounds of their octants, one wave per chunk.  Box corners and H
 // are >= 0 (validated), so their doubles order like their bit patterns as
 // signed 64-bit integers (and so do the -inf / +inf starting values): the
 // chunks meet in 64-bit integer atomics min / max, which give exactly the
 // minima and maxima of the doubles.  A -0 (which passes the validation)
 // enters as +0: its bit pattern would order below -inf.
-#define STATS_CHUNK 1024
-
 __device__ inline long long stats_bits(double v)
 {
     return __double_as_longlong(v == 0.0 ? 0.0 : v);
@@ -354,45 +396,27 @@ __device__ inline void atomic_max_d(double* p, double v)
     atomicMax((long long*)p, stats_bits(v));
 }
 
-// Chunks of each cell, and the octant bounds [bnd[0..8]] of each cell set to
-// its end (the stats pass writes every bound up to the last octant present).
-__global__ __launch_bounds__(256) void k_level_chunks(const Node* __restrict__ nodes, int level_start, int n_level,
-                                                      int* nchunk, int* bnd)
-{
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n_level) return;
-    const Node& nd = nodes[level_start + k];
-    nchunk[k] = (nd.count + STATS_CHUNK - 1) / STATS_CHUNK;
-    for (int q = 0; q < 9; q++) bnd[9 * k + q] = nd.begin + nd.count;
-}
-
-__global__ __launch_bounds__(256) void k_chunk_map(const int* __restrict__ nchunk, const int* __restrict__ coff,
-                                                   int n_level, int* cmap)
-{
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n_level) return;
-    for (int j = 0; j < nchunk[k]; j++) cmap[coff[k] + j] = k;
-}
-
-// One wave per chunk (grid-stride over the n_chunks[0] chunks).  Octant of a
-// particle in a cell of level `level`: key bits 3 (D - level - 1) and up; the
-// first particle of each octant present sets the bounds from the previous
-// octant present (exclusive) to its own (inclusive).
-__global__ __launch_bounds__(256) void k_level_stats(Node* nodes, int level_start, int level, const int* __restrict__ coff,
-                                                     const int* __restrict__ cmap, const int* __restrict__ n_chunks,
-                                                     const uint64_t* __restrict__ keys, const double* __restrict__ x,
-                                                     const double* __restrict__ y, const double* __restrict__ z,
-                                                     const double* __restrict__ H, int D, int* bnd)
+// One wave per chunk (grid-stride over them).  Octant of a particle in a cell
+// of level `level`: key bits 3 (D - level - 1) and up; the first particle of
+// each octant present sets the bounds from the previous octant present
+// (exclusive) to its own (inclusive), the cell's last those that remain.
+__global__ __launch_bounds__(256) void k_level_stats(Node* nodes, int level, const int2* __restrict__ cmap,
+                                                     const int* __restrict__ flags, const uint64_t* __restrict__ keys,
+                                                     const double* __restrict__ x, const double* __restrict__ y,
+                                                     const double* __restrict__ z, const double* __restrict__ H, int D,
+                                                     int* bnd)
 {
     const int lane = threadIdx.x & 63;
-    const int T = __builtin_amdgcn_readfirstlane(*n_chunks);
+    const int level_start = flags[FI_LEVEL + level];
+    const int T = flags[FI_LEVEL + level + 1] > level_start ? __builtin_amdgcn_readfirstlane(flags[FI_NCHUNK]) : 0;
     const int shift = 3 * (D - level - 1);
     for (int q = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)); q < T; q += gridDim.x * 4) {
-        const int k = __builtin_amdgcn_readfirstlane(cmap[q]);
-        Node* nd = &nodes[level_start + k];
+        const int2 ch = cmap[q];
+        Node* nd = &nodes[__builtin_amdgcn_readfirstlane(ch.x)];
+        const int k = __builtin_amdgcn_readfirstlane(ch.x) - level_start;
         const int b = nd->begin, c = nd->count;
         const bool octants = level < D && !nd->merged;
-        const int i0 = b + (q - coff[k]) * STATS_CHUNK, i1 = min(b + c, i0 + STATS_CHUNK);
+        const int i0 = b + __builtin_amdgcn_readfirstlane(ch.y) * STATS_CHUNK, i1 = min(b + c, i0 + STATS_CHUNK);
         double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
         double hm = 0.0, hn = INFINITY;
         for (int i = i0 + lane; i < i1; i += 64) {
@@ -407,6 +431,8 @@ __global__ __launch_bounds__(256) void k_level_stats(Node* nodes, int level_star
                 const int o = (int)((keys[i] >> shift) & 7);
                 const int op = i > b ? (int)((keys[i - 1] >> shift) & 7) : -1;
                 for (int r = op + 1; r <= o; r++) bnd[9 * k + r] = i;
+                if (i == b + c - 1)
+                    for (int r = o + 1; r < 9; r++) bnd[9 * k + r] = b + c;
             }
         }
         for (int off = 32; off > 0; off >>= 1) {
@@ -444,13 +470,50 @@ __device__ inline int split_cell(Node* nd, int k, int D, int n_split, double h_r
     return nc;
 }
 
-// ... one thread per cell.
-__global__ __launch_bounds__(256) void k_level_split(Node* nodes, int level_start, int n_level, int D, int n_split,
-                                                     double h_ratio, const int* __restrict__ bnd, int* nchild)
+// Exclusive scan over the 256 threads of the workgroup; `all`: the total.
+__device__ inline int wg_scan(int v, int* wsum, int& all)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n_level) return;
-    nchild[k] = split_cell(&nodes[level_start + k], k, D, n_split, h_ratio, bnd);
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int incl = v;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int t = __shfl_up(incl, off);
+        if (lane >= off) incl += t;
+    }
+    __syncthreads();
+    if (lane == 63) wsum[w] = incl;
+    __syncthreads();
+    int ex = incl - v;
+    all = 0;
+    for (int q = 0; q < 4; q++) {
+        if (q < w) ex += wsum[q];
+        all += wsum[q];
+    }
+    return ex;
+}
+
+// The children of each cell of a level are counted, and summed over tiles of
+// 256 cells; cells that stay leaves are counted in FI_NLEAVES (count_leaves).
+__global__ __launch_bounds__(256) void k_level_split(Node* nodes, int level, int D, int n_split, double h_ratio,
+                                                     const int* __restrict__ bnd, int* tile_sum, int* flags,
+                                                     int count_leaves)
+{
+    __shared__ int wsum[4];
+    const int start = flags[FI_LEVEL + level], n = flags[FI_LEVEL + level + 1] - start;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        flags[FI_NCHUNK] = 0;  // for the next level's
+        if (n > 0) flags[FI_LEVELFULL] = 0;
+    }
+    for (int t = blockIdx.x; t * 256 < n; t += gridDim.x) {
+        const int k = t * 256 + threadIdx.x;
+        const bool has = k < n;
+        const int nc = has ? split_cell(&nodes[start + k], k, D, n_split, h_ratio, bnd) : 0;
+        const bool leaf = has && nc == 0 && nodes[start + k].count > 0;
+        const int nl = __popcll(__ballot(leaf));
+        int all;
+        wg_scan(nc, wsum, all);
+        if (threadIdx.x == 0) tile_sum[t] = all;
+        if (count_leaves && nl && (threadIdx.x & 63) == 0) atomicAdd(&flags[FI_NLEAVES], nl);
+    }
 }
 
 // The children of a split cell, from node `out`; bnd: its octant bounds.
@@ -484,89 +547,45 @@ __device__ inline void emit_cell(Node* nodes, int node, int out, int D, int n_sp
         ch.hmax = 0.0;
         ch.hmin = INFINITY;
         ch.merged = (q + 1 < 8 && gb[g] + gc[g] > bq[q + 1]) ? 1 : 0;
-        ch.pad = 0;
+        // escape link: the next sibling, the last child inherits its parent's
+        ch.next = g + 1 < ng ? out + g + 1 : nd->next;
         nodes[out + g] = ch;
     }
 }
 
-// ... of a level, at the scanned offsets.  One thread per cell.
-__global__ __launch_bounds__(256) void k_emit_children(Node* nodes, int level_start, int n_level, const int* __restrict__ coff,
-                                                       int child_base, int D, int n_split, double h_ratio,
-                                                       const int* __restrict__ bnd)
+// ... of a level, in the order of the cells, with their chunks: each workgroup
+// adds up the tiles before its own.  If they do not fit in the node buffer
+// nothing is written but their number.
+__global__ __launch_bounds__(256) void k_emit_children(Node* nodes, int level, int cap, int D, int n_split, double h_ratio,
+                                                       const int* __restrict__ bnd, const int* __restrict__ tile_sum,
+                                                       int2* cmap, int* flags)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n_level || nodes[level_start + k].n_child == 0) return;
-    emit_cell(nodes, level_start + k, child_base + coff[k], D, n_split, h_ratio, bnd + 9 * k);
-}
-
-// Levels of few cells by one workgroup: k_level_chunks, its scan and
-// k_chunk_map in one launch, k_level_split, its scan and k_emit_children in
-// another.  The latter writes every child from one compute unit, so its limit
-// lies lower: 780 cells take it 161 us, the three launches 30 us; 64 cells
-// 12 us against 18 us.
-#define LEVEL_ONE 4096
-#ifndef SPLIT_ONE
-#define SPLIT_ONE 128
-#endif
-// Exclusive scan over the 1024 threads of the workgroup; `all`: the total.
-__device__ inline int wg_scan(int v, int* wsum, int& all)
-{
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int incl = v;
-    for (int off = 1; off < 64; off <<= 1) {
-        const int t = __shfl_up(incl, off);
-        if (lane >= off) incl += t;
-    }
-    __syncthreads();
-    if (lane == 63) wsum[w] = incl;
-    __syncthreads();
-    int ex = incl - v;
-    all = 0;
-    for (int q = 0; q < 16; q++) {
-        if (q < w) ex += wsum[q];
-        all += wsum[q];
-    }
-    return ex;
-}
-
-__global__ __launch_bounds__(1024) void k_level_chunks_one(const Node* __restrict__ nodes, int level_start, int n_level,
-                                                           int* coff, int* cmap, int* bnd, int* n_chunks)
-{
-    __shared__ int wsum[16];
-    int base = 0;
-    for (int k0 = 0; k0 < n_level; k0 += 1024) {
-        const int k = k0 + threadIdx.x;
-        int b = 0, c = 0;
-        if (k < n_level) {
-            b = nodes[level_start + k].begin;
-            c = nodes[level_start + k].count;
-            for (int q = 0; q < 9; q++) bnd[9 * k + q] = b + c;
+    __shared__ int wsum[4];
+    const int start = flags[FI_LEVEL + level], next = flags[FI_LEVEL + level + 1];
+    const int n = next - start, n_tiles = (n + 255) / 256;
+    for (int t = blockIdx.x; t < n_tiles || t == 0; t += gridDim.x) {
+        int before = 0, total = 0;
+        for (int q = threadIdx.x; q < n_tiles; q += 256) {
+            const int v = tile_sum[q];
+            total += v;
+            if (q < t) before += v;
         }
-        const int nc = (c + STATS_CHUNK - 1) / STATS_CHUNK;
-        int all;
-        const int o = base + wg_scan(nc, wsum, all);
-        if (k < n_level) coff[k] = o;
-        for (int j = 0; j < nc; j++) cmap[o + j] = k;
-        base += all;
+        int base, all;
+        wg_scan(before, wsum, base);
+        wg_scan(total, wsum, all);
+        const bool fits = all <= cap - next;
+        if (t == 0 && threadIdx.x == 0) {
+            flags[FI_LEVEL + level + 2] = next + (fits ? all : 0);
+            if (!fits) flags[FI_LEVELFULL] = all;
+        }
+        if (!fits) return;
+        const int k = t * 256 + threadIdx.x;
+        const int nc = k < n ? nodes[start + k].n_child : 0;
+        const int out = next + base + wg_scan(nc, wsum, all);
+        if (nc > 0) emit_cell(nodes, start + k, out, D, n_split, h_ratio, bnd + 9 * k);
+        for (int g = 0; __ballot(g < nc) != 0ull; g++)
+            add_chunks(out + g, g < nc ? nodes[out + g].count : 0, cmap, flags + FI_NCHUNK);
     }
-    if (threadIdx.x == 0) *n_chunks = base;
-}
-
-__global__ __launch_bounds__(1024) void k_level_split_one(Node* nodes, int level_start, int n_level, int child_base,
-                                                          int D, int n_split, double h_ratio,
-                                                          const int* __restrict__ bnd, int* n_children)
-{
-    __shared__ int wsum[16];
-    int base = 0;
-    for (int k0 = 0; k0 < n_level; k0 += 1024) {
-        const int k = k0 + threadIdx.x;
-        const int nc = k < n_level ? split_cell(&nodes[level_start + k], k, D, n_split, h_ratio, bnd) : 0;
-        int all;
-        const int o = base + wg_scan(nc, wsum, all);
-        if (nc > 0) emit_cell(nodes, level_start + k, child_base + o, D, n_split, h_ratio, bnd + 9 * k);
-        base += all;
-    }
-    if (threadIdx.x == 0) *n_children = base;
 }
 
 __global__ __launch_bounds__(256) void k_mark_leaves(const Node* __restrict__ nodes, int n_nodes, int* leafmark)
@@ -738,46 +757,13 @@ __global__ __launch_bounds__(256) void k_wnodes(const Node* __restrict__ nodes, 
         o.hi[a] = __double2float_ru(nd.hi[a]);
     }
     o.first_child = nd.n_child > 0 ? nd.first_child : -1;
-    o.next = -1;
+    o.next = nd.next;
     o.count = nd.count;
     o.leaf = nd.leaf;
     // float bound of the subtree's list radii (as k_node_hmax sets it)
     o.hl = __double2float_ru((nd.hmax * (1.0 + SPH_LIST_SKIN) + skin_abs) * (1.0 + 1e-6));
     o.pad = nd.n_child;
     w[k] = o;
-}
-
-// Escape links, one level at a time from the top: a child's next node is its
-// next sibling, the last child inherits its parent's next node.
-__global__ __launch_bounds__(256) void k_wnext(const Node* __restrict__ nodes, int level_start, int n_level,
-                                               WNode* __restrict__ w)
-{
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n_level) return;
-    const int p = level_start + k;
-    const Node& nd = nodes[p];
-    if (nd.n_child == 0) return;
-    const int pn = w[p].next;
-    for (int q = 0; q < nd.n_child; q++) w[nd.first_child + q].next = (q + 1 < nd.n_child) ? nd.first_child + q + 1 : pn;
-}
-
-// All levels by one workgroup (few cells); level l is [off[l], off[l + 1]).
-struct LevelOffsets {
-    int n, off[SPH_MAX_DEPTH + 3];
-};
-__global__ __launch_bounds__(1024) void k_wnext_all(const Node* __restrict__ nodes, LevelOffsets L, WNode* w)
-{
-    for (int l = 0; l < L.n; l++) {
-        for (int p = L.off[l] + threadIdx.x; p < L.off[l + 1]; p += blockDim.x) {
-            const Node& nd = nodes[p];
-            if (nd.n_child == 0) continue;
-            const int pn = w[p].next;
-            for (int q = 0; q < nd.n_child; q++)
-                w[nd.first_child + q].next = (q + 1 < nd.n_child) ? nd.first_child + q + 1 : pn;
-        }
-        __threadfence_block();
-        __syncthreads();
-    }
 }
 
 __device__ inline float box_dist_f(const float* alo, const float* ahi, const float* blo, const float* bhi,
@@ -1255,12 +1241,13 @@ __global__ __launch_bounds__(256) void k_sort_cells(int n_leaves, int64_t n, con
 // ---------------------------------------------------------------------------
 static inline int blocks_for(int64_t n, int t) { return (int)((n + t - 1) / t); }
 
-static sph_status read_int(sph_ctx* c, const int* dptr, int* out)
+static sph_status read_ints(sph_ctx* c, const int* dptr, int* out, int n)
 {
-    SPH_CHECK_HIP(hipMemcpyAsync(out, dptr, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+    SPH_CHECK_HIP(hipMemcpyAsync(out, dptr, (size_t)n * sizeof(int), hipMemcpyDeviceToHost, c->stream));
     SPH_CHECK_HIP(hipStreamSynchronize(c->stream));
     return SPH_OK;
 }
+static sph_status read_int(sph_ctx* c, const int* dptr, int* out) { return read_ints(c, dptr, out, 1); }
 
 // Permutes the caller's arrays by perm.  x, y, z and H, which the octree
 // reads next, on the context's stream; the other arrays, when the context
@@ -1711,91 +1698,100 @@ sph_status build_all(sph_ctx* c)
     SPH_TRY(permute_all(c, (const uint32_t*)c->vals[res].p, c->keys[res ^ 1].p));
     if (nd > 1) SPH_TRY(domain_ranges(c));
 
-    // 4. octree, level by level
+    // 4. octree, several levels between looks at them
+    const int old_depth = c->depth;
     size_t cap = std::max<size_t>((size_t)top * 2 + 1024, (size_t)(n / 8) + 1024);
+    auto level_buffers = [&]() -> sph_status {
+        // chunks of a level: one per STATS_CHUNK particles, at most one more per cell
+        SPH_TRY(buf_ensure(c->lvl_cmap, ((size_t)n / STATS_CHUNK + cap) * sizeof(int2)));
+        SPH_TRY(buf_ensure(c->lvl_sum, (cap / 256 + 1) * sizeof(int)));
+        return SPH_OK;
+    };
+    // (the buffers of an earlier build that needed more)
+    cap = std::max(cap, std::min({c->nodes.cap / sizeof(Node), c->lvl_bnd.cap / (9 * sizeof(int)), (size_t)INT32_MAX / 9}));
     SPH_TRY(buf_ensure(c->nodes, cap * sizeof(Node)));
-    SPH_TRY(buf_ensure(c->nchild, (size_t)(top + 1) * sizeof(int)));
-    k_top_nodes<<<blocks_for(top, 256), 256, 0, c->stream>>>(top, nd, (const DomainInfo*)c->dom_d.p, keys, (int)n, D,
-                                                           (Node*)c->nodes.p);
+    SPH_TRY(buf_ensure(c->lvl_bnd, cap * 9 * sizeof(int)));
+    SPH_TRY(level_buffers());
+    k_top_nodes<<<blocks_for(top, TOP_CELLS), 256, 0, c->stream>>>(top, nd, (const DomainInfo*)c->dom_d.p, keys, (int)n, D,
+                                                           (Node*)c->nodes.p, (int2*)c->lvl_cmap.p, flags);
     SPH_CHECK_LAUNCH();
     // FP32 cell-relative coordinates: keep every leaf's extent within
     // SPH_FP32_EXTENT_RATIO of its smallest smoothing length
     const double h_ratio = c->prm.precision == SPH_FP64 ? 0.0 : SPH_FP32_EXTENT_RATIO;
-    c->level_off.clear();
-    c->level_off.push_back(0);
-    int level_start = 0, n_level = top, n_nodes = top;
+    // levels enqueued at first: those of the last build, else what an even
+    // distribution of the particles would need and one more
+    int last = old_depth;
+    if (last == 0)
+        for (double per = (double)n / top; per > c->prm.n_split && last < D; per /= 8.0) last++;
+    last = std::min(last + (old_depth == 0 ? 1 : 0), D);
+    c->level_off.assign(1, 0);
     c->depth = 0;
-    for (int level = 0; level <= D; level++) {
-        // chunks of the level: one per STATS_CHUNK particles of each cell, at
-        // most n / STATS_CHUNK + the level's cells
-        SPH_TRY(buf_ensure(c->lvl_cmap, ((size_t)n / STATS_CHUNK + n_level + 1) * sizeof(int)));
-        SPH_TRY(buf_ensure(c->nchild, (size_t)(n_level + 1) * sizeof(int)));
-        SPH_TRY(buf_ensure(c->coff, (size_t)(n_level + 1) * sizeof(int)));
-        SPH_TRY(buf_ensure(c->lvl_bnd, (size_t)n_level * 9 * sizeof(int)));
-        int* nchild = (int*)c->nchild.p;
-        int* ccoff = (int*)c->coff.p;
-        int* bnd = (int*)c->lvl_bnd.p;
-        const int nbl = blocks_for(n_level, 256);
-        const bool one = n_level <= LEVEL_ONE;
-        if (one) {
-            k_level_chunks_one<<<1, 1024, 0, c->stream>>>((const Node*)c->nodes.p, level_start, n_level, ccoff,
-                                                          (int*)c->lvl_cmap.p, bnd, flags + FI_NCHUNK);
-        } else {
-            k_level_chunks<<<nbl, 256, 0, c->stream>>>((const Node*)c->nodes.p, level_start, n_level, nchild, bnd);
-            SPH_CHECK_LAUNCH();
-            SPH_TRY(scan_exclusive(c, nchild, ccoff, n_level, flags + FI_NCHUNK));
-            k_chunk_map<<<nbl, 256, 0, c->stream>>>(nchild, ccoff, n_level, (int*)c->lvl_cmap.p);
-        }
-        SPH_CHECK_LAUNCH();
-        const int nstat = (int)std::min<int64_t>(2048, (n / STATS_CHUNK + n_level + 3) / 4);
-        k_level_stats<<<nstat, 256, 0, c->stream>>>((Node*)c->nodes.p, level_start, level, ccoff,
-                                                   (const int*)c->lvl_cmap.p, flags + FI_NCHUNK, keys, c->P.x, c->P.y,
-                                                   c->P.z, c->P.H, D, bnd);
-        SPH_CHECK_LAUNCH();
-        // the children go at the scanned offsets, whatever their total: when
-        // the node buffer holds 8 per cell of the level (the most a split
-        // makes), they are written while the host reads the total
-        const bool early = (size_t)n_nodes + 8 * (size_t)n_level <= cap;
-        const bool emitted = early && n_level <= SPLIT_ONE;
-        if (emitted) {
-            k_level_split_one<<<1, 1024, 0, c->stream>>>((Node*)c->nodes.p, level_start, n_level, n_nodes, D,
-                                                         c->prm.n_split, h_ratio, bnd, flags + FI_NCHILD);
-            SPH_CHECK_LAUNCH();
-        } else {
-            k_level_split<<<nbl, 256, 0, c->stream>>>((Node*)c->nodes.p, level_start, n_level, D, c->prm.n_split,
-                                                      h_ratio, bnd, nchild);
-            SPH_CHECK_LAUNCH();
-            SPH_TRY(scan_exclusive(c, nchild, nchild, n_level, flags + FI_NCHILD));
-        }
-        if (early && !emitted) {
-            k_emit_children<<<nbl, 256, 0, c->stream>>>((Node*)c->nodes.p, level_start, n_level, nchild, n_nodes, D,
-                                                         c->prm.n_split, h_ratio, bnd);
-            SPH_CHECK_LAUNCH();
-        }
-        int total = 0;
-        SPH_TRY(read_int(c, flags + FI_NCHILD, &total));
-        c->level_off.push_back(n_nodes);
-        if (total == 0) break;
-        if (!early) {
-            if ((size_t)(n_nodes + total) > cap) {
-                size_t ncap = std::max((size_t)(n_nodes + total) * 3 / 2, cap * 2);
-                DevBuf nb2;
-                SPH_TRY(buf_ensure(nb2, ncap * sizeof(Node)));
-                SPH_CHECK_HIP(hipMemcpyAsync(nb2.p, c->nodes.p, (size_t)n_nodes * sizeof(Node),
-                                             hipMemcpyDeviceToDevice, c->stream));
-                SPH_CHECK_HIP(hipStreamSynchronize(c->stream));
-                buf_free(c->nodes);
-                c->nodes = nb2;
-                cap = ncap;
+    int n_nodes = 0, nL = 0;
+    bool again = false;  // the first level enqueued was counted, but its children did not fit
+    for (int level = 0; level <= D;) {
+        const int wg_cells = (int)std::min<size_t>(1024, (std::min<size_t>(cap, (size_t)n) + 255) / 256);
+        const int wg_stats = (int)std::min<size_t>(2048, ((size_t)n / STATS_CHUNK + std::min<size_t>(cap, (size_t)n) + 3) / 4);
+        for (int l = level; l <= last; l++) {
+            if (!(again && l == level)) {
+                k_level_stats<<<wg_stats, 256, 0, c->stream>>>((Node*)c->nodes.p, l, (const int2*)c->lvl_cmap.p, flags,
+                                                              keys, c->P.x, c->P.y, c->P.z, c->P.H, D,
+                                                              (int*)c->lvl_bnd.p);
+                SPH_CHECK_LAUNCH();
             }
-            k_emit_children<<<nbl, 256, 0, c->stream>>>((Node*)c->nodes.p, level_start, n_level, nchild, n_nodes, D,
-                                                         c->prm.n_split, h_ratio, bnd);
+            k_level_split<<<wg_cells, 256, 0, c->stream>>>((Node*)c->nodes.p, l, D, c->prm.n_split, h_ratio,
+                                                           (const int*)c->lvl_bnd.p, (int*)c->lvl_sum.p, flags,
+                                                           !(again && l == level));
+            SPH_CHECK_LAUNCH();
+            k_emit_children<<<wg_cells, 256, 0, c->stream>>>((Node*)c->nodes.p, l, (int)cap, D, c->prm.n_split, h_ratio,
+                                                             (const int*)c->lvl_bnd.p, (const int*)c->lvl_sum.p,
+                                                             (int2*)c->lvl_cmap.p, flags);
             SPH_CHECK_LAUNCH();
         }
-        level_start = n_nodes;
-        n_level = total;
-        n_nodes += total;
-        c->depth = level + 1;
+        again = false;
+        int fl[FI_NFLAGS];
+        SPH_TRY(read_ints(c, flags, fl, FI_NFLAGS));
+        const int* off = fl + FI_LEVEL;
+        bool done = false;
+        for (; level <= last; level++) {
+            n_nodes = off[level + 1];
+            if (off[level + 2] == n_nodes && fl[FI_LEVELFULL] > 0) {
+                again = true;
+                break;
+            }
+            c->level_off.push_back(n_nodes);
+            if (off[level + 2] == n_nodes) {
+                done = true;
+                break;
+            }
+            c->depth = level + 1;
+        }
+        if (again) {
+            const int nl = off[level + 1] - off[level];
+            const size_t ncap = std::max(((size_t)n_nodes + fl[FI_LEVELFULL]) * 3 / 2, cap * 2);
+            DevBuf nb2, bb2;
+            SPH_TRY(buf_ensure(nb2, ncap * sizeof(Node)));
+            const sph_status st = buf_ensure(bb2, ncap * 9 * sizeof(int));
+            if (st != SPH_OK) {
+                buf_free(nb2);
+                return st;
+            }
+            SPH_CHECK_HIP(hipMemcpyAsync(nb2.p, c->nodes.p, (size_t)n_nodes * sizeof(Node), hipMemcpyDeviceToDevice,
+                                         c->stream));
+            SPH_CHECK_HIP(hipMemcpyAsync(bb2.p, c->lvl_bnd.p, (size_t)nl * 9 * sizeof(int), hipMemcpyDeviceToDevice,
+                                         c->stream));
+            SPH_CHECK_HIP(hipStreamSynchronize(c->stream));
+            buf_free(c->nodes);
+            buf_free(c->lvl_bnd);
+            c->nodes = nb2;
+            c->lvl_bnd = bb2;
+            cap = ncap;
+            SPH_TRY(level_buffers());
+        }
+        if (done) {
+            nL = fl[FI_NLEAVES];
+            break;
+        }
+        last = std::min(std::max(last, level) + 2, D);
     }
     c->n_nodes = n_nodes;
 
@@ -1805,9 +1801,7 @@ sph_status build_all(sph_ctx* c)
     k_mark_leaves<<<blocks_for(n_nodes, 256), 256, 0, c->stream>>>((const Node*)c->nodes.p, n_nodes, (int*)c->leafmark.p);
     SPH_CHECK_LAUNCH();
     SPH_TRY(buf_ensure(c->leafscan, (size_t)(n + 1) * sizeof(int)));
-    SPH_TRY(scan_exclusive(c, (const int*)c->leafmark.p, (int*)c->leafscan.p, (int)n, flags + FI_NLEAVES));
-    int nL = 0;
-    SPH_TRY(read_int(c, flags + FI_NLEAVES, &nL));
+    SPH_TRY(scan_exclusive(c, (const int*)c->leafmark.p, (int*)c->leafscan.p, (int)n, flags + FI_SCRATCH));
     c->n_leaves = nL;
     const size_t L1 = (size_t)nL + 1;
     SPH_TRY(buf_ensure(c->leaf_node, L1 * 4));
@@ -1853,20 +1847,6 @@ sph_status build_all(sph_ctx* c)
     k_wnodes<<<blocks_for(n_nodes, 256), 256, 0, c->stream>>>((const Node*)c->nodes.p, n_nodes, c->skin_abs,
                                                                 (WNode*)c->wnodes.p);
     SPH_CHECK_LAUNCH();
-    const int n_lvl = (int)c->level_off.size() - 1;
-    if (n_nodes <= LEVEL_ONE) {
-        LevelOffsets L;
-        L.n = n_lvl;
-        for (int l = 0; l <= n_lvl; l++) L.off[l] = c->level_off[l];
-        k_wnext_all<<<1, 1024, 0, c->stream>>>((const Node*)c->nodes.p, L, (WNode*)c->wnodes.p);
-        SPH_CHECK_LAUNCH();
-    }
-    for (int l = 0; n_nodes > LEVEL_ONE && l < n_lvl; l++) {
-        const int ls = c->level_off[l], nl = c->level_off[l + 1] - ls;
-        if (nl <= 0) continue;
-        k_wnext<<<blocks_for(nl, 256), 256, 0, c->stream>>>((const Node*)c->nodes.p, ls, nl, (WNode*)c->wnodes.p);
-        SPH_CHECK_LAUNCH();
-    }
     // with cell lists the cells' largest H (octree statistics), the leaves'
     // list radii (leaf fill) and the walk nodes' bounds are those of the
     // current H: the relist need not recompute them

@@ -49,7 +49,7 @@ struct Node {
     double hmin;           // smallest H in the cell
     double c_lo[3], c_sz[3];  // geometric cell corner and edge lengths
     int merged;            // 1: run of sibling octants merged into one leaf
-    int pad;
+    int next;              // node after this subtree in depth-first order (-1: end of the top cell)
 };
 
 // Compact copy of a cell for the list walk: bounding box rounded outward to
@@ -123,8 +123,8 @@ enum {
 };
 
 // Slots of the int[64] flags buffer.
-enum { FI_FLAGS = 0, FI_SCRATCH = 8, FI_NCHILD = 9, FI_NLEAVES = 10, FI_NLIST = 11, FI_GATE = 12, FI_MAXLEAF = 13, FI_MAXLIST = 14, FI_PLROWS = 15, FI_WOVF = 16,
-       FI_WINC = 17, FI_NCHUNK = 18, FI_NWIDE = 19, FI_WIDEMIN = 20, FI_NFLAGS = 64 };
+enum { FI_FLAGS = 0, FI_SCRATCH = 8, FI_LEVELFULL = 9, FI_NLEAVES = 10, FI_NLIST = 11, FI_GATE = 12, FI_MAXLEAF = 13, FI_MAXLIST = 14, FI_PLROWS = 15, FI_WOVF = 16,
+       FI_WINC = 17, FI_NCHUNK = 18, FI_NWIDE = 19, FI_WIDEMIN = 20, FI_LEVEL = 32, FI_NFLAGS = 64 };
 
 // Waves that share a leaf with a long list, and the list length from which
 // they do: one wave on the longest lists of a clustered box (800 entries, the
