@@ -501,15 +501,17 @@ __device__ inline bool dens_finish(const DensArgs& a, int i, bool act, int jg, i
 //
 // Range tests (tile_masks).  All 4 ROW x 64 tests of a full tile run on the
 // matrix units: r^2 - H_i^2 = -2 p_j.p_i + |p_j|^2 + (|p_i|^2 - H_i^2) is a
-// product over K = 4 (x, y, z, 1) plus a row constant, one
-// v_mfma_f32_16x16x4_f32 per 16 x 16 tests, and the sign bits are the mask
+// product over (x, y, z, 1) plus a row constant, one
+// v_mfma_f32_16x16x16_bf16 per 16 x 16 tests, and the sign bits are the mask
 // (one v_alignbit per 64 tests instead of the ~11 instructions of a
-// per-particle loop with a ballot).  The expanded form rounds relative to
-// |p|^2, so every constant is shifted by PAIR_EPS towards "in range": with
-// at most 8 roundings of 2^-23 of a sum bounded by 2(|p_i|^2 + |p_j|^2) +
-// H^2 and coordinates rounded to FP32, the shift is at least four times the
-// error.  No pair is lost; the few that are let in wrongly contribute
-// exact zeros below (q >= 1).
+// per-particle loop with a ballot).  Each factor is a sum of two bfloat16, a
+// product x y the three terms xh yh + xh ym + xm yh: a quarter of the float32
+// product's matrix time, and work that VALU instructions of other waves
+// overlap, which float32 products do not.  What the terms leave out is below 3
+// 2^-18 |x y| per coordinate, 2^-16 (|p_i|^2 + |p_j|^2) in all with the
+// roundings of the sum, so every constant is shifted by PAIR_EPS = 2^-14 of it
+// towards "in range", four times the error.  No pair is lost; the 0.2% that
+// are let in wrongly contribute exact zeros below (q >= 1).
 // Coordinates and smoothing lengths are scaled by a power of two (exact) to
 // order 1, so nothing over- or underflows that did not before; the sums only
 // hold r / H and unit vectors, which the scale leaves as they are.
@@ -523,9 +525,20 @@ __device__ inline bool dens_finish(const DensArgs& a, int i, bool act, int jg, i
 // LDS accumulator where the run passes from one particle to the next.
 // ---------------------------------------------------------------------------
 #define PAIR_CAP 512  // pairs listed at a time (a tile usually has ~300)
-#define PAIR_EPS 3.8146973e-6f  // 2^-18
+#define PAIR_EPS 6.1035156e-5f  // 2^-14
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef short bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16v2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+// a (low half) and b rounded to bfloat16 (nearest even)
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b)
+{
+    const bf16v2 v = {(__bf16)a, (__bf16)b};
+    return __builtin_bit_cast(uint32_t, v);
+}
+__device__ __forceinline__ float bf16_high(uint32_t pair) { return __uint_as_float(pair & 0xffff0000u); }
 
 // Batch of up to NE neighbour cells as one stream of candidates.
 template <typename T, int NE>
@@ -599,16 +612,30 @@ __device__ inline int stream_cell(int p0, int start)
 __device__ inline float pow2_scale(float x) { return __builtin_amdgcn_ldexpf(1.0f, -__builtin_amdgcn_frexp_expf(x)); }
 __device__ inline double pow2_scale(double x) { return __builtin_amdgcn_ldexp(1.0, -__builtin_amdgcn_frexp_exp(x)); }
 
-// Test operand of the particles i, one value per lane and block of 16
-// particles: lane l holds component l / 16 of (-2x, -2y, -2z, c) of
-// particle 16 blk + l % 16.  (x, y, z, c): the lane's own particle, scaled;
-// tmp: 64 float4 of LDS.
-__device__ inline void test_operand(float x, float y, float z, float c, float4* tmp, int lane, float b[4])
+// Test operand of the particles i, one value v per lane and block of 16
+// particles: lane l holds component l / 16 of (-2x, -2y, -2z, c) of particle
+// 16 blk + l % 16, as the four slots (vh, vm, vh, .) that meet a candidate's
+// (xh, xh, xm, 1); for c, which meets ones, (ch, cm, 0, cl).  The open slots of
+// x, y and z hold the three terms of `own`, a constant that only the first of
+// two tests takes in (the second has zeros there).  (x, y, z, c), own: the
+// lane's own particle, scaled; tmp: 64 float4 of LDS.
+__device__ inline void test_operand(float x, float y, float z, float c, float own, float4* tmp, int lane, bf16x4 b[4])
 {
     wave_sync();
     tmp[lane] = make_float4(-2.0f * x, -2.0f * y, -2.0f * z, c);
     wave_sync();
-    for (int k = 0; k < 4; k++) b[k] = ((const float*)&tmp[16 * k + (lane & 15)])[lane >> 4];
+    float v[4];
+    for (int k = 0; k < 4; k++) v[k] = ((const float*)&tmp[16 * k + (lane & 15)])[lane >> 4];
+    wave_sync();
+    const float oh = bf16_high(bf16_pair(own, own)), om = bf16_high(bf16_pair(own, own - oh));
+    tmp[lane] = make_float4(oh, om, own - oh - om, 0.0f);
+    wave_sync();
+    for (int k = 0; k < 4; k++) {
+        const float vh = bf16_high(bf16_pair(v[k], v[k])), vm = bf16_high(bf16_pair(v[k], v[k] - vh));
+        const float o = ((const float*)&tmp[16 * k + (lane & 15)])[lane >> 4];
+        const u32x2 s = {bf16_pair(vh, vm), lane < 48 ? bf16_pair(vh, o) : bf16_pair(0.0f, v[k] - vh - vm)};
+        b[k] = __builtin_bit_cast(bf16x4, s);
+    }
     wave_sync();
 }
 
@@ -624,20 +651,24 @@ template <int ROW>
 __device__ inline int test_slot(int j) { return (j & 3) * ROW + (j >> 2); }
 
 template <bool TWO, int ROW, int NB, typename Coord>
-__device__ inline void tile_masks_n(const float* c1, const float* c2, Coord coord, const float b1[4], const float b2[4],
+__device__ inline void tile_masks_n(const float* c1, const float* c2, Coord coord, const bf16x4 b[4],
                                     int lane, uint32_t M[4])
 {
     const int g = lane >> 4;
 #pragma unroll
     for (int t = 0; t < ROW / 4; t++) {
-        const float a = coord(16 * t + 4 * (lane & 3) + ((lane >> 2) & 3));
+        const float v = coord(16 * t + 4 * (lane & 3) + ((lane >> 2) & 3));
+        const uint32_t vh = bf16_pair(v, v);
+        const uint32_t vm = bf16_pair(v - bf16_high(vh), 1.0f);
+        const u32x2 s1 = {vh, vm}, s2 = {vh, lane < 48 ? vm & 0xffffu : vm};
+        const bf16x4 a1 = __builtin_bit_cast(bf16x4, s1), a2 = __builtin_bit_cast(bf16x4, s2);
         const f32x4 r1 = *(const f32x4*)(c1 + ROW * g + 4 * t);
         const f32x4 r2 = TWO ? *(const f32x4*)(c2 + ROW * g + 4 * t) : r1;
         f32x4 d1[NB], d2[NB];
 #pragma unroll
         for (int k = 0; k < NB; k++) {
-            d1[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b1[k], r1, 0, 0, 0);
-            if (TWO) d2[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b2[k], r2, 0, 0, 0);
+            d1[k] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a1, b[k], r1, 0, 0, 0);
+            if (TWO) d2[k] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a2, b[k], r2, 0, 0, 0);
         }
 #pragma unroll
         for (int k = 0; k < NB; k++)
@@ -651,12 +682,12 @@ __device__ inline void tile_masks_n(const float* c1, const float* c2, Coord coor
 }
 // nb: blocks of 16 particles up to the last that holds any (1..4)
 template <bool TWO, int ROW, typename Coord>
-__device__ inline void tile_masks(const float* c1, const float* c2, Coord coord, const float b1[4], const float b2[4],
+__device__ inline void tile_masks(const float* c1, const float* c2, Coord coord, const bf16x4 b[4],
                                   int nb, int lane, uint32_t M[4])
 {
-    if (nb <= 2) tile_masks_n<TWO, ROW, 2>(c1, c2, coord, b1, b2, lane, M);
-    else if (nb == 3) tile_masks_n<TWO, ROW, 3>(c1, c2, coord, b1, b2, lane, M);
-    else tile_masks_n<TWO, ROW, 4>(c1, c2, coord, b1, b2, lane, M);
+    if (nb <= 2) tile_masks_n<TWO, ROW, 2>(c1, c2, coord, b, lane, M);
+    else if (nb == 3) tile_masks_n<TWO, ROW, 3>(c1, c2, coord, b, lane, M);
+    else tile_masks_n<TWO, ROW, 4>(c1, c2, coord, b, lane, M);
 }
 
 // Exclusive prefix sums over (particle, row of 16 lanes) of two 16-bit counts

@@ -129,7 +129,7 @@ __device__ __forceinline__ void density_leaf_packed(const DensArgs& a, int A, ty
     const T hAm = (T)(hA * (1.0 + 1e-5)) * sc;
     const T hA2 = hAm * hAm;
     const int nb = 4 - (__builtin_clzll(amask) >> 4);
-    float b1[4];
+    bf16x4 bt[4];
     {
         V4 q = pi;
         q.x *= sc, q.y *= sc, q.z *= sc;
@@ -137,7 +137,7 @@ __device__ __forceinline__ void density_leaf_packed(const DensArgs& a, int A, ty
         const float p2 = x * x + y * y + z * z;
         const bool on = act && p2 < 1e30f;
         test_operand(on ? x : 0.f, on ? y : 0.f, on ? z : 0.f,
-                     on ? p2 * (1.0f - PAIR_EPS) - h * h * (1.0f + PAIR_EPS) - 1e-30f : 1e30f, (float4*)L.cand, lane, b1);
+                     on ? p2 * (1.0f - PAIR_EPS) - h * h * (1.0f + PAIR_EPS) - 1e-30f : 1e30f, 0.f, (float4*)L.cand, lane, bt);
         q.w = T(1) / ((T)Hd * sc);
         L.si[lane] = q;
         L.sw[lane] = L.sd[lane] = 0.0;
@@ -190,7 +190,7 @@ __device__ __forceinline__ void density_leaf_packed(const DensArgs& a, int A, ty
         }
         wave_sync();
         uint32_t M[4] = {0u, 0u, 0u, 0u};
-        tile_masks<false, DENS_ROW>(L.c1, nullptr, [&](int j) { return get_test<T>(L, j, lane); }, b1, b1, nb, lane, M);
+        tile_masks<false, DENS_ROW>(L.c1, nullptr, [&](int j) { return get_test<T>(L, j, lane); }, bt, nb, lane, M);
         for_pairs<DENS_ROW>(M, L.list, lane, []() {}, eval);
         wave_sync();
     };
@@ -1054,7 +1054,7 @@ __device__ __forceinline__ void force_leaf_gather(const ForceArgs& a, int A, typ
         const T sc = pow2_scale(fmax((T)hA, fmax(fmax(fmax(-bxl, bxh), fmax(-byl, byh)), fmax(-bzl, bzh))));
         bxl *= sc, bxh *= sc, byl *= sc, byh *= sc, bzl *= sc, bzh *= sc;
         const T hAm = (T)(hA * (1.0 + 1e-5)) * sc;
-        float b1[4], b2[4];
+        bf16x4 bt[4];
         int nmax = 0;  // pairs within max(H_i, H_j), self included, of the lane's runs
         {
             V4 q = pi;
@@ -1065,8 +1065,7 @@ __device__ __forceinline__ void force_leaf_gather(const ForceArgs& a, int A, typ
             nself += __popcll(__ballot(on));
             const float xi = on ? x : 0.f, yi = on ? y : 0.f, zi = on ? z : 0.f;
             const float ci = on ? p2 * (1.0f - PAIR_EPS) - 1e-30f : 1e30f;
-            test_operand(xi, yi, zi, on ? ci - h * h * (1.0f + PAIR_EPS) : 1e30f, (float4*)L.cand, lane, b1);
-            test_operand(xi, yi, zi, ci, (float4*)L.cand, lane, b2);
+            test_operand(xi, yi, zi, ci, on ? -h * h * (1.0f + PAIR_EPS) : 0.f, (float4*)L.cand, lane, bt);
             q.w = T(1) / (Hi * sc);
             L.si[lane] = q;
             L.sv[lane] = fv4[i];
@@ -1135,7 +1134,7 @@ __device__ __forceinline__ void force_leaf_gather(const ForceArgs& a, int A, typ
             if (lane < len) v0 = fv4[((const uint32_t*)&L.cv[lane])[0]];
             if (lane + 64 < len) v1 = fv4[((const uint32_t*)&L.cv[lane + 64])[0]];
             uint32_t M[4] = {0u, 0u, 0u, 0u};
-            tile_masks<true, FORCE_ROW>(L.c[0], L.c[1], [&](int j) { return get_test<T>(L, j, lane); }, b1, b2, nb, lane, M);
+            tile_masks<true, FORCE_ROW>(L.c[0], L.c[1], [&](int j) { return get_test<T>(L, j, lane); }, bt, nb, lane, M);
             for_pairs<FORCE_ROW>(M, L.list, lane, [&]() {
                 if (lane < len) L.cv[lane] = v0;
                 if (lane + 64 < len) L.cv[lane + 64] = v1;

@@ -317,12 +317,12 @@ __global__ __launch_bounds__(64 * IW, 4) void k_interp_blocks(InterpArgs a, int 
             // sums of the wave that begins a block, and of those that go on
             double* acc = at == pb ? S0[b] : S1[wv];
             const double sc = Q.sc, isc = Q.isc;
-            float b1[4];
+            bf16x4 bt[4];
             {
                 const float x = (float)Q.p[0][lane], y = (float)Q.p[1][lane], z = (float)Q.p[2][lane];
                 const bool on = (Q.sel >> lane) & 1ull;
-                test_operand(x, y, z, on ? (x * x + y * y + z * z) * (1.0f - PAIR_EPS) - 1e-30f : 1e30f,
-                             (float4*)L.cand, lane, b1);
+                test_operand(x, y, z, on ? (x * x + y * y + z * z) * (1.0f - PAIR_EPS) - 1e-30f : 1e30f, 0.f,
+                             (float4*)L.cand, lane, bt);
             }
             const int nb = 4 - (__builtin_clzll(Q.sel) >> 4);
             auto eval = [&](const uint16_t* list, int n) __attribute__((always_inline)) {
@@ -362,7 +362,7 @@ __global__ __launch_bounds__(64 * IW, 4) void k_interp_blocks(InterpArgs a, int 
                 tile_masks<false, IROW>(L.c1, nullptr, [&](int t) {
                     const float v = (float)((const double*)&L.cand[t])[lane >> 4];
                     return lane < 48 ? v : 1.0f;
-                }, b1, b1, nb, lane, M);
+                }, bt, nb, lane, M);
                 // (a row of IROW bits, the first candidate's at bit IROW - 1)
                 for_pairs<IROW>(M, L.list, lane, [&]() {
                     wave_sync();

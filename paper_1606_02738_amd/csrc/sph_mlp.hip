@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "sph_ctx.h"
+#include "sph_device.h"
 
 namespace {
 
@@ -53,7 +54,6 @@ __device__ __forceinline__ float silu_l2(float u)
 }
 
 typedef short bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // Inference weights arranged for v_mfma_f32_16x16x32_bf16.  The layers are
 // computed transposed, Z^T = W^T X^T: A = 16 output units x 32 input slots,
@@ -128,13 +128,7 @@ __global__ __launch_bounds__(256) void k_mlp_pack(const float* __restrict__ p, M
 
 // split x = hi + lo, both bfloat16 (hardware conversion, nearest even): four
 // values into the pairs at, at+1 of the operands
-typedef __bf16 bf16v2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uint32_t bf16_pair(float a, float b)
-{
-    const bf16v2 v = {(__bf16)a, (__bf16)b};
-    return __builtin_bit_cast(uint32_t, v);
-}
 __device__ __forceinline__ void split4(const float v[4], u32x4& hi, int at_hi, u32x4& lo, int at_lo)
 {
     for (int j = 0; j < 2; j++) {
