@@ -11,7 +11,8 @@ capture of the density, ghost and force stages, and how many steps the
 cells and lists are kept (the list skin).  A second stage sweeps, around
 the fastest of those, the kernel axes: the occupancy target (waves per SIMD)
 the density and the force kernels are compiled for, and the neighbour-cell
-entries they stage per batch.  Every candidate starts from the same saved state, so each is timed
+entries they stage per batch (the packed kernels have one instantiation of
+the last two: they make no difference there).  Every candidate starts from the same saved state, so each is timed
 on identical work; the particle tensors are restored afterwards.  Steps are
 averaged (not the median) so that the occasional rebuild of a candidate
 that keeps its lists is paid for.
@@ -171,6 +172,7 @@ def autotune(boxes, t, precision, dt, steps=8, warmup=1, cands=None, cache=DEFAU
 
     try:
         run(cands or candidates())
+        n_first = len(table)
         if kernel_axes and precision != "fp64":
             stage1 = min(table, key=lambda r: r[1])[0]
             run(kernel_candidates(stage1))
@@ -188,6 +190,9 @@ def autotune(boxes, t, precision, dt, steps=8, warmup=1, cands=None, cache=DEFAU
         del state
         torch.cuda.empty_cache()
     best = min(table, key=lambda r: r[1])[0]
+    if len(table) > n_first:
+        # a first-stage candidate is the one whose kernel axes are the defaults
+        best = dict(dict(waves_density=0, waves_force=0, batch=0), **best)
     if cache:
         db[key] = {"best": best, "table": table}
         try:
