@@ -1432,8 +1432,8 @@ sph_status node_hmax_all(sph_ctx* c, bool set_hlist)
 // Counters of the walk, and the end of its counts (the walks write every leaf's).
 __global__ void k_relist_clear(int* count_end, int* flags)
 {
-    const int f[] = {FI_MAXLIST, FI_WOVF, FI_WINC, FI_NWIDE};
-    if (threadIdx.x < 4) flags[f[threadIdx.x]] = 0;
+    const int f[] = {FI_MAXLIST, FI_WOVF, FI_WINC, FI_NWIDE, FI_WIDECLASS, FI_WIDECLASS + 1, FI_WIDECLASS + 2, FI_WIDECLASS + 3};
+    if (threadIdx.x < 8) flags[f[threadIdx.x]] = 0;
     if (threadIdx.x == 0) *count_end = 0;
 }
 
@@ -1446,7 +1446,13 @@ __global__ __launch_bounds__(256) void k_wide_list(int n_leaves, const int* __re
     const long long m = 5ll * l_off[n_leaves] / (2 * n_leaves);
     const int len = n_leaves >= SPH_WIDE_MANY ? SPH_WIDE_MAX : (int)min((long long)SPH_WIDE_MAX, max((long long)SPH_WIDE_MIN, m));
     if (A == 0) *wide_min = len;
-    if (A < n_leaves && l_off[A + 1] - l_off[A] > len) wide[atomicAdd(n_wide, 1)] = A;
+    const int n = A < n_leaves ? l_off[A + 1] - l_off[A] : 0;
+    if (n > len) {
+        // longest first: classes of lists of 4, 3, 2, 1 and more times `len`
+        const int k = 4 - min(4, n / len);
+        wide[(size_t)k * n_leaves + atomicAdd(&n_wide[FI_WIDECLASS - FI_NWIDE + k], 1)] = A;
+        atomicAdd(n_wide, 1);
+    }
 }
 
 sph_status relist(sph_ctx* c)
@@ -1499,7 +1505,7 @@ sph_status relist(sph_ctx* c)
     SPH_TRY(scan_exclusive(c, counts, counts, nL + 1, flags + FI_NLIST));
     const bool wide = nL > SPH_WIDE_ALL && c->prm.prune == SPH_PRUNE_BOX && c->prm.lists == SPH_LISTS_CELL;
     if (wide) {
-        SPH_TRY(buf_ensure(c->wide, (size_t)nL * sizeof(int)));
+        SPH_TRY(buf_ensure(c->wide, (size_t)nL * 4 * sizeof(int)));
         k_wide_list<<<blocks_for(nL, 256), 256, 0, c->stream>>>(nL, counts, (int*)c->wide.p, flags + FI_NWIDE,
                                                          flags + FI_WIDEMIN);
         SPH_CHECK_LAUNCH();

@@ -320,7 +320,7 @@ struct DensArgs {
     const int* nl_dev;  // graph mode: leaf count read from the device (NULL: n_leaves)
     int big_only;       // skip leaves of at most 64 particles (done by the packed kernel)
     const int* wide;        // leaves with lists above *wide_min (NULL: all are taken as such)
-    const int* n_wide_dev;  // graph mode: their number
+    const int* n_wide_dev;  // their number, later their classes' (FI_NWIDE, FI_WIDECLASS)
     const int* wide_min;
     int n_wide;
 };

@@ -454,8 +454,14 @@ __device__ __forceinline__ void for_wide_leaves(const Args& a, Work work)
         return;
     }
     const int n = a.nl_dev ? uniform(*a.n_wide_dev) : a.n_wide;
+    // the classes of the list one after another
+    const int nL = a.nl_dev ? uniform(*a.nl_dev) : a.n_leaves;
+    const int* cl = a.n_wide_dev + (FI_WIDECLASS - FI_NWIDE);
+    const int c0 = uniform(cl[0]), c1 = c0 + uniform(cl[1]), c2 = c1 + uniform(cl[2]);
     for (int b = blockIdx.x; b < n; b += gridDim.x) {
-        work(uniform(a.wide[b]), wave);
+        const int k = (b >= c0) + (b >= c1) + (b >= c2);
+        const int t = b - (k == 0 ? 0 : k == 1 ? c0 : k == 2 ? c1 : c2);
+        work(uniform(a.wide[(size_t)k * nL + t]), wave);
         __syncthreads();  // (the tiles are reused)
     }
 }
@@ -575,7 +581,7 @@ struct ForceArgs {
     const int* gate;    // graph mode: run only if *gate == 1 (NULL: always run)
     const int* nl_dev;  // graph mode: leaf count read from the device (NULL: n_leaves)
     const int* wide;        // leaves with lists above *wide_min (NULL: all are taken as such)
-    const int* n_wide_dev;  // graph mode: their number
+    const int* n_wide_dev;  // their number, later their classes' (FI_NWIDE, FI_WIDECLASS)
     const int* wide_min;
     int n_wide;
     int persistent;

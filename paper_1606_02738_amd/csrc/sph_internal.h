@@ -124,14 +124,15 @@ enum {
 
 // Slots of the int[64] flags buffer.
 enum { FI_FLAGS = 0, FI_SCRATCH = 8, FI_LEVELFULL = 9, FI_NLEAVES = 10, FI_NLIST = 11, FI_GATE = 12, FI_MAXLEAF = 13, FI_MAXLIST = 14, FI_PLROWS = 15, FI_WOVF = 16,
-       FI_WINC = 17, FI_NCHUNK = 18, FI_NWIDE = 19, FI_WIDEMIN = 20, FI_LEVEL = 32, FI_NFLAGS = 64 };
+       FI_WINC = 17, FI_NCHUNK = 18, FI_NWIDE = 19, FI_WIDEMIN = 20, FI_WIDECLASS = 21, FI_LEVEL = 32, FI_NFLAGS = 64 };
 
 // Waves that share a leaf with a long list, and the list length from which
 // they do: one wave on the longest lists of a clustered box (800 entries, the
 // mean is 75) outlasts the rest of the grid.  256 entries, or 2.5 times the mean
 // (at least 128) in boxes of fewer leaves, where the grid is over sooner.
 // Stages at 127^3 clustered 4.8 -> 4.3 ms (4 waves 4.5, 2 waves 5.0), at 64^3 FP64
-// 2.5 -> 2.0 ms. 
+// 2.5 -> 2.0 ms.  The longest are taken first (four classes): 127^3 3.87 -> 3.81,
+// step at 256^3 18.1 -> 17.86 ms (in the order found, a late one is waited for).
 #define SPH_WIDE_WAVES 8
 #define SPH_WIDE_MIN 128
 #define SPH_WIDE_MAX 256
