@@ -516,54 +516,67 @@ __global__ __launch_bounds__(256) void k_level_split(Node* nodes, int level, int
     }
 }
 
-// The children of a split cell, from node `out`; bnd: its octant bounds.
-__device__ inline void emit_cell(Node* nodes, int node, int out, int D, int n_split, double h_ratio, const int* bnd)
+// Child g of a split cell, as node `out`; bnd: the cell's octant bounds.
+// Returns the particles of the child.
+__device__ inline int emit_child(Node* nodes, int node, int first, int g, int D, int n_split, double h_ratio, const int* bnd)
 {
-    Node* nd = &nodes[node];
+    const Node* nd = &nodes[node];
     const uint64_t step = 1ull << (3 * (D - nd->level - 1));
     int bq[9], gq[8], gb[8], gc[8];
     for (int q = 0; q < 9; q++) bq[q] = bnd[q];
     const int ng = child_groups(bq, n_split, !extent_too_large(*nd, h_ratio), gq, gb, gc);
-    nd->first_child = out;
-    for (int g = 0; g < ng; g++) {
-        const int q = gq[g];
-        Node ch;
-        ch.key_lo = nd->key_lo + step * q;
-        ch.begin = gb[g];
-        ch.count = gc[g];
-        ch.first_child = -1;
-        ch.n_child = 0;
-        ch.level = nd->level + 1;
-        ch.domain = nd->domain;
-        ch.leaf = -1;
-        ch.top = nd->top;
-        const int o[3] = {(q >> 2) & 1, (q >> 1) & 1, q & 1};
-        for (int a = 0; a < 3; a++) {
-            ch.c_sz[a] = 0.5 * nd->c_sz[a];
-            ch.c_lo[a] = nd->c_lo[a] + o[a] * ch.c_sz[a];
-            ch.lo[a] = INFINITY;
-            ch.hi[a] = -INFINITY;
+    int q = 0, b = 0, c = 0;
+    for (int k = 0; k < 8; k++)
+        if (k == g) {
+            q = gq[k];
+            b = gb[k];
+            c = gc[k];
         }
-        ch.hmax = 0.0;
-        ch.hmin = INFINITY;
-        ch.merged = (q + 1 < 8 && gb[g] + gc[g] > bq[q + 1]) ? 1 : 0;
-        // escape link: the next sibling, the last child inherits its parent's
-        ch.next = g + 1 < ng ? out + g + 1 : nd->next;
-        nodes[out + g] = ch;
+    int bnext = 0;  // end of octant q
+    for (int k = 1; k < 9; k++)
+        if (k == q + 1) bnext = bq[k];
+    Node ch;
+    ch.key_lo = nd->key_lo + step * q;
+    ch.begin = b;
+    ch.count = c;
+    ch.first_child = -1;
+    ch.n_child = 0;
+    ch.level = nd->level + 1;
+    ch.domain = nd->domain;
+    ch.leaf = -1;
+    ch.top = nd->top;
+    const int o[3] = {(q >> 2) & 1, (q >> 1) & 1, q & 1};
+    for (int a = 0; a < 3; a++) {
+        ch.c_sz[a] = 0.5 * nd->c_sz[a];
+        ch.c_lo[a] = nd->c_lo[a] + o[a] * ch.c_sz[a];
+        ch.lo[a] = INFINITY;
+        ch.hi[a] = -INFINITY;
     }
+    ch.hmax = 0.0;
+    ch.hmin = INFINITY;
+    ch.merged = (q + 1 < 8 && b + c > bnext) ? 1 : 0;
+    // escape link: the next sibling, the last child inherits its parent's
+    ch.next = g + 1 < ng ? first + g + 1 : nd->next;
+    nodes[first + g] = ch;
+    return c;
 }
 
-// ... of a level, in the order of the cells, with their chunks: each workgroup
-// adds up the tiles before its own.  If they do not fit in the node buffer
-// nothing is written but their number.
+// ... of a level, in the order of the cells, with their chunks.  A workgroup
+// takes the children of EMIT_CELLS cells, one per lane: it adds up the tiles
+// before its own and scans the counts of its tile.  (One lane per cell, which
+// wrote its children in turn: 25 us a level at 128^3, 17 us now.)  If the
+// children do not fit in the node buffer nothing is written but their number.
+#define EMIT_CELLS 32
 __global__ __launch_bounds__(256) void k_emit_children(Node* nodes, int level, int cap, int D, int n_split, double h_ratio,
                                                        const int* __restrict__ bnd, const int* __restrict__ tile_sum,
                                                        int2* cmap, int* flags)
 {
     __shared__ int wsum[4];
+    __shared__ int nchild[EMIT_CELLS], at[EMIT_CELLS];
     const int start = flags[FI_LEVEL + level], next = flags[FI_LEVEL + level + 1];
     const int n = next - start, n_tiles = (n + 255) / 256;
-    for (int t = blockIdx.x; t < n_tiles || t == 0; t += gridDim.x) {
+    for (int w = blockIdx.x; w * EMIT_CELLS < n || w == 0; w += gridDim.x) {
+        const int t = w * EMIT_CELLS / 256;
         int before = 0, total = 0;
         for (int q = threadIdx.x; q < n_tiles; q += 256) {
             const int v = tile_sum[q];
@@ -574,29 +587,47 @@ __global__ __launch_bounds__(256) void k_emit_children(Node* nodes, int level, i
         wg_scan(before, wsum, base);
         wg_scan(total, wsum, all);
         const bool fits = all <= cap - next;
-        if (t == 0 && threadIdx.x == 0) {
+        if (w == 0 && threadIdx.x == 0) {
             flags[FI_LEVEL + level + 2] = next + (fits ? all : 0);
             if (!fits) flags[FI_LEVELFULL] = all;
         }
         if (!fits) return;
-        const int k = t * 256 + threadIdx.x;
+        const int k = t * 256 + threadIdx.x, first = w * EMIT_CELLS;
         const int nc = k < n ? nodes[start + k].n_child : 0;
         const int out = next + base + wg_scan(nc, wsum, all);
-        if (nc > 0) emit_cell(nodes, start + k, out, D, n_split, h_ratio, bnd + 9 * k);
-        for (int g = 0; __ballot(g < nc) != 0ull; g++)
-            add_chunks(out + g, g < nc ? nodes[out + g].count : 0, cmap, flags + FI_NCHUNK);
+        if (k >= first && k < first + EMIT_CELLS) {
+            nchild[k - first] = nc;
+            at[k - first] = out;
+            if (nc > 0) nodes[start + k].first_child = out;
+        }
+        __syncthreads();
+        const int c = threadIdx.x >> 3, g = threadIdx.x & 7;
+        int count = 0;
+        if (g < nchild[c]) count = emit_child(nodes, start + first + c, at[c], g, D, n_split, h_ratio, bnd + 9 * (first + c));
+        add_chunks(at[c] + g, count, cmap, flags + FI_NCHUNK);
+        __syncthreads();
     }
 }
 
-__global__ __launch_bounds__(256) void k_mark_leaves(const Node* __restrict__ nodes, int n_nodes, int* leafmark)
+// A leaf's number is that of leaves that begin at particles before its own:
+// one bit per particle where a leaf begins, and the leaves that begin in each
+// 64 of them, which are scanned.  (A mark and a scanned int per particle took
+// five launches at 128^3 and 20 us in one at 32^3.)
+__global__ __launch_bounds__(256) void k_mark_leaves(const Node* __restrict__ nodes, int n_nodes,
+                                                     unsigned long long* bits, int* counts)
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= n_nodes) return;
     const Node& nd = nodes[k];
-    if (nd.n_child == 0 && nd.count > 0) leafmark[nd.begin] = 1;
+    if (nd.n_child == 0 && nd.count > 0) {
+        atomicOr(&bits[nd.begin >> 6], 1ull << (nd.begin & 63));
+        atomicAdd(&counts[nd.begin >> 6], 1);
+    }
 }
 
-__global__ __launch_bounds__(256) void k_leaf_fill(Node* nodes, int n_nodes, const int* __restrict__ leafscan,
+__global__ __launch_bounds__(256) void k_leaf_fill(Node* nodes, int n_nodes,
+                                                   const unsigned long long* __restrict__ bits,
+                                                   const int* __restrict__ leafscan,
                                                    int* leaf_node, int* l_begin, int* l_count, double* l_origin,
                                                    double* l_lo, double* l_hi, double* l_hlist, int* l_dom, int* l_top,
                                                    double skin_abs, int* max_leaf)
@@ -609,7 +640,7 @@ __global__ __launch_bounds__(256) void k_leaf_fill(Node* nodes, int n_nodes, con
         return;
     }
     if (nd.count > 64) atomicMax(max_leaf, nd.count);
-    const int id = leafscan[nd.begin];
+    const int id = leafscan[nd.begin >> 6] + __popcll(bits[nd.begin >> 6] & ((1ull << (nd.begin & 63)) - 1ull));
     nd.leaf = id;
     leaf_node[id] = k;
     l_begin[id] = nd.begin;
@@ -1313,17 +1344,41 @@ static sph_status permute_all(sph_ctx* c, const uint32_t* perm, void* side_tmp)
         }
         return SPH_OK;
     };
+    // several arrays in two launches, through a buffer of the last build's that
+    // is not read before the next lists are made; false: it holds less than two
+    auto permute_group = [&](const std::vector<uint64_t*>& arrays, const DevBuf& b, hipStream_t st) {
+        const size_t rows = std::min<size_t>(b.cap / ((size_t)n * 8), 18);
+        if (!b.p || rows < 2) return false;
+        c->built = c->sorted = false;  // (the last build's lists are gone)
+        for (size_t k = 0; k < arrays.size(); k += rows) {
+            PermArrays P{};
+            while (P.n8 < (int)std::min(rows, arrays.size() - k)) {
+                P.a[P.n8] = arrays[k + P.n8];
+                P.n8++;
+            }
+            const dim3 g(blocks_for(n, 256), P.n8);
+            k_gather_all<<<g, 256, 0, st>>>((int)n, perm, P, (uint64_t*)b.p, 0);
+            k_gather_all<<<g, 256, 0, st>>>((int)n, perm, P, (uint64_t*)b.p, 1);
+        }
+        return true;
+    };
+    std::vector<uint64_t*> later;
     for (double* a : rest)
-        if (a) SPH_TRY(permute8(a, false, s2, t2));
-    if (c->P.id) SPH_TRY(permute8(c->P.id, true, s2, t2));
+        if (a) later.push_back((uint64_t*)a);
+    if (c->P.id) later.push_back((uint64_t*)c->P.id);
+    if (permute_group(later, c->walk_scratch, s2)) SPH_CHECK_LAUNCH();
+    else
+        for (uint64_t* a : later) SPH_TRY(permute8(a, a == (uint64_t*)c->P.id, s2, t2));
     if (c->P.domain) {
         k_gather<int32_t><<<nb4, 256, 0, s2>>>(n, perm, c->P.domain, (int32_t*)t2);
         SPH_CHECK_LAUNCH();
         SPH_CHECK_HIP(hipMemcpyAsync(c->P.domain, t2, (size_t)n * 4, hipMemcpyDeviceToDevice, s2));
     }
     if (split) SPH_CHECK_HIP(hipEventRecord(c->side_ev[1], c->side));
-    for (double* a : geo)
-        if (a) SPH_TRY(permute8(a, false, c->stream, c->tmp.p));
+    if (permute_group({(uint64_t*)c->P.x, (uint64_t*)c->P.y, (uint64_t*)c->P.z, (uint64_t*)c->P.H}, c->list, c->stream))
+        SPH_CHECK_LAUNCH();
+    else
+        for (double* a : geo) SPH_TRY(permute8(a, false, c->stream, c->tmp.p));
     if (c->mlp_pending) {
         // predictor features and previous H of this step follow their particles
         k_gather<double><<<nb4, 256, 0, c->stream>>>(n, perm, (const double*)c->mlp_hprev.p, (double*)c->tmp.p);
@@ -1451,8 +1506,10 @@ __global__ __launch_bounds__(256) void k_wide_list(int n_leaves, const int* __re
         // longest first: classes of lists of 4, 3, 2, 1 and more times `len`
         const int k = 4 - min(4, n / len);
         wide[(size_t)k * n_leaves + atomicAdd(&n_wide[FI_WIDECLASS - FI_NWIDE + k], 1)] = A;
-        atomicAdd(n_wide, 1);
     }
+    // (one atomic per wave)
+    const int nw = __popcll(__ballot(n > len));
+    if (nw && (threadIdx.x & 63) == 0) atomicAdd(n_wide, nw);
 }
 
 sph_status relist(sph_ctx* c)
@@ -1589,7 +1646,7 @@ sph_status build_all(sph_ctx* c)
         for (int a = 0; a < 3; a++) I.L[a] = c->boxes[3 * d + a];
     }
     SPH_TRY(set_domains(c, -1));
-    k_validate<<<std::min(blocks_for(n, 256), 2048), 256, 0, c->stream>>>(n, c->P.x, c->P.y, c->P.z, c->P.H, c->P.m, c->P.domain, nd,
+    k_validate<<<std::min(blocks_for(n, 1024), 512), 256, 0, c->stream>>>(n, c->P.x, c->P.y, c->P.z, c->P.H, c->P.m, c->P.domain, nd,
                                                         (const DomainInfo*)c->dom_d.p,
                                                         (unsigned long long*)c->dstat.p, flags);
     SPH_CHECK_LAUNCH();
@@ -1748,7 +1805,7 @@ sph_status build_all(sph_ctx* c)
                                                            (const int*)c->lvl_bnd.p, (int*)c->lvl_sum.p, flags,
                                                            !(again && l == level));
             SPH_CHECK_LAUNCH();
-            k_emit_children<<<wg_cells, 256, 0, c->stream>>>((Node*)c->nodes.p, l, (int)cap, D, c->prm.n_split, h_ratio,
+            k_emit_children<<<std::min(2048, 8 * wg_cells), 256, 0, c->stream>>>((Node*)c->nodes.p, l, (int)cap, D, c->prm.n_split, h_ratio,
                                                              (const int*)c->lvl_bnd.p, (const int*)c->lvl_sum.p,
                                                              (int2*)c->lvl_cmap.p, flags);
             SPH_CHECK_LAUNCH();
@@ -1802,12 +1859,14 @@ sph_status build_all(sph_ctx* c)
     c->n_nodes = n_nodes;
 
     // 5. leaves in Morton order
-    SPH_TRY(buf_ensure(c->leafmark, (size_t)(n + 1) * sizeof(int)));
-    SPH_CHECK_HIP(hipMemsetAsync(c->leafmark.p, 0, (size_t)(n + 1) * sizeof(int), c->stream));
-    k_mark_leaves<<<blocks_for(n_nodes, 256), 256, 0, c->stream>>>((const Node*)c->nodes.p, n_nodes, (int*)c->leafmark.p);
+    const int n_words = blocks_for(n, 64);
+    SPH_TRY(buf_ensure(c->leafmark, (size_t)n_words * (sizeof(uint64_t) + sizeof(int))));
+    unsigned long long* bits = (unsigned long long*)c->leafmark.p;
+    int* first = (int*)(bits + n_words);
+    SPH_CHECK_HIP(hipMemsetAsync(c->leafmark.p, 0, (size_t)n_words * (sizeof(uint64_t) + sizeof(int)), c->stream));
+    k_mark_leaves<<<blocks_for(n_nodes, 256), 256, 0, c->stream>>>((const Node*)c->nodes.p, n_nodes, bits, first);
     SPH_CHECK_LAUNCH();
-    SPH_TRY(buf_ensure(c->leafscan, (size_t)(n + 1) * sizeof(int)));
-    SPH_TRY(scan_exclusive(c, (const int*)c->leafmark.p, (int*)c->leafscan.p, (int)n, flags + FI_SCRATCH));
+    SPH_TRY(scan_exclusive(c, first, first, n_words, flags + FI_SCRATCH));
     c->n_leaves = nL;
     const size_t L1 = (size_t)nL + 1;
     SPH_TRY(buf_ensure(c->leaf_node, L1 * 4));
@@ -1823,7 +1882,7 @@ sph_status build_all(sph_ctx* c)
     SPH_TRY(buf_ensure(c->l_sorted, L1 * 4));
     SPH_TRY(buf_ensure(c->l_cnt, L1 * 4));
     k_leaf_fill<<<blocks_for(n_nodes, 256), 256, 0, c->stream>>>(
-        (Node*)c->nodes.p, n_nodes, (const int*)c->leafscan.p, (int*)c->leaf_node.p, (int*)c->l_begin.p,
+        (Node*)c->nodes.p, n_nodes, bits, first, (int*)c->leaf_node.p, (int*)c->l_begin.p,
         (int*)c->l_count.p, (double*)c->l_origin.p, (double*)c->l_lo.p, (double*)c->l_hi.p, (double*)c->l_hlist.p,
         (int*)c->l_dom.p, (int*)c->l_cnt.p, c->skin_abs, flags + FI_MAXLEAF);
     SPH_CHECK_LAUNCH();

@@ -86,7 +86,7 @@ struct sph_ctx {
     DevBuf nodes;                       // octree
     DevBuf lvl_cmap, lvl_bnd, lvl_sum;  // of one level: chunks, octant bounds (9 per cell), children per 256 cells
     DevBuf wnodes;                // compact cells for the list walk
-    DevBuf leafmark, leafscan;    // per particle
+    DevBuf leafmark;              // per 64 particles: where leaves begin, and how many
     DevBuf leaf_node;             // leaf -> node
     DevBuf l_begin, l_count, l_origin, l_lo, l_hi, l_hlist, l_dom, l_off, l_active, l_sorted, l_cnt;
     DevBuf list;
