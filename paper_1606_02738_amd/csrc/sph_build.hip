@@ -1019,17 +1019,28 @@ __device__ inline bool walk_near_f(const float* alo, const float* ahi, const flo
 // 64-entry chunks of the pool (at most two new ones per round).  One wave
 // per leaf, four per workgroup, eight waves per SIMD (64 VGPRs, no spills;
 // the walk waits on its loads).
+//
+// AGAIN: the leaves left incomplete, their entries in the same order straight
+// to the scanned offsets l_off (one thread per such leaf: 1.4 ms of each of the
+// 12 lists that the solve of 55^3 clustered particles from a guess of H makes
+// with the pool exhausted, 25.2 ms in all; 9.35 ms now).
+template <bool AGAIN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_walk_wave(
     int n_leaves, const int* __restrict__ leaf_node, const WNode* __restrict__ wn, const double* __restrict__ l_lo,
     const double* __restrict__ l_hi, const int* __restrict__ l_dom, const int* __restrict__ l_top,
-    const DomainInfo* __restrict__ di, const double* __restrict__ l_hlist, int* counts, ListEntry* __restrict__ list,
-    int list_cap, int with_dir, int sym, int* flags, ListEntry* ovf, int* link, int ovf_chunks)
+    const DomainInfo* __restrict__ di, const double* __restrict__ l_hlist, int* counts, const int* __restrict__ l_off,
+    ListEntry* __restrict__ list, int list_cap, int with_dir, int sym, int* flags, ListEntry* ovf, int* link,
+    int ovf_chunks)
 {
     __shared__ uint32_t stk[4][WALK_STACK];
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int A = __builtin_amdgcn_readfirstlane(xcd_block(blockIdx.x, gridDim.x) * 4 + w);
-    if (A >= n_leaves) return;
+    if (A >= n_leaves || (AGAIN && !link[n_leaves + A])) return;
     int* next = link + 2 * (size_t)n_leaves;
+    if (AGAIN) {
+        list += l_off[A];
+        list_cap = l_off[A + 1] - l_off[A];
+    }
     const DomainInfo& I = di[l_dom[A]];
     const int nt[3] = {I.n_top[0], I.n_top[1], I.n_top[2]};
     const double L[3] = {I.L[0], I.L[1], I.L[2]};
@@ -1127,7 +1138,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
             // last chunk taken when that one is partly filled), ch[1]: jl + 1
             const int jl = out > list_cap ? (out - list_cap) >> 6 : 0;
             int ch[2] = {last, -1};
-            if (!failed && out + k > list_cap) {
+            if (!AGAIN && !failed && out + k > list_cap) {
                 const int jh = (out + k - 1 - list_cap) >> 6;
                 for (int j = n_chunks; j <= jh; j++) {
                     int c = 0;
@@ -1150,7 +1161,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
             if (hit) {
                 ListEntry* dst = nullptr;
                 if (pos < list_cap) {
-                    dst = list + (size_t)A * list_cap + pos;
+                    dst = AGAIN ? list + pos : list + (size_t)A * list_cap + pos;
+                } else if (AGAIN) {
+                    atomicOr(flags, FLAG_INVALID);
                 } else {
                     const int j = (pos - list_cap) >> 6;
                     if (j < n_chunks) dst = ovf + (size_t)ch[j - jl] * 64 + ((pos - list_cap) & 63);
@@ -1161,6 +1174,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
         }
         // the next round reads the stack this one wrote
         walk_wave_sync();
+    }
+    if (AGAIN) {
+        // (fewer entries than counted)
+        if (lane == 0 && out != list_cap) atomicOr(flags, FLAG_INVALID);
+        return;
     }
     if (lane == 0) {
         counts[A] = out;
@@ -1540,10 +1558,10 @@ sph_status relist(sph_ctx* c)
         SPH_TRY(buf_ensure(c->walk_link, (2 * (size_t)nL + ovf_chunks) * sizeof(int)));
         // one wave per leaf (stack entries hold node << 5)
         if (c->n_nodes < (1 << 27)) {
-            k_walk_wave<<<blocks_for(nL, 4), 256, 0, c->stream>>>(
+            k_walk_wave<false><<<blocks_for(nL, 4), 256, 0, c->stream>>>(
                 nL, (const int*)c->leaf_node.p, (const WNode*)c->wnodes.p, (const double*)c->l_lo.p,
                 (const double*)c->l_hi.p, (const int*)c->l_dom.p, (const int*)c->l_cnt.p, (const DomainInfo*)c->dom_d.p,
-                (const double*)c->l_hlist.p, counts, (ListEntry*)c->walk_scratch.p, cap, with_dir, sym, flags,
+                (const double*)c->l_hlist.p, counts, nullptr, (ListEntry*)c->walk_scratch.p, cap, with_dir, sym, flags,
                 (ListEntry*)c->walk_ovf.p, (int*)c->walk_link.p, ovf_chunks);
         } else {
             k_walk<2><<<blocks_for(nL, 128), 128, 0, c->stream>>>(
@@ -1587,7 +1605,14 @@ sph_status relist(sph_ctx* c)
         c->rewalked = true;
         // leaves that found no free overflow chunk (all leaves without the
         // one pass): walked again, writing at the scanned offsets
-        k_walk<1><<<blocks_for(nL, 128), 128, 0, c->stream>>>(
+        if (one_pass && c->n_nodes < (1 << 27))
+            k_walk_wave<true><<<blocks_for(nL, 4), 256, 0, c->stream>>>(
+                nL, (const int*)c->leaf_node.p, (const WNode*)c->wnodes.p, (const double*)c->l_lo.p,
+                (const double*)c->l_hi.p, (const int*)c->l_dom.p, (const int*)c->l_cnt.p, (const DomainInfo*)c->dom_d.p,
+                (const double*)c->l_hlist.p, nullptr, (const int*)c->l_off.p, (ListEntry*)c->list.p, 0, with_dir, sym,
+                flags, nullptr, (int*)c->walk_link.p, 0);
+        else
+            k_walk<1><<<blocks_for(nL, 128), 128, 0, c->stream>>>(
             nL, (const int*)c->leaf_node.p, (const WNode*)c->wnodes.p, (const double*)c->l_lo.p,
             (const double*)c->l_hi.p, (const int*)c->l_dom.p, (const int*)c->l_cnt.p, (const DomainInfo*)c->dom_d.p,
             (const double*)c->l_hlist.p, nullptr, (const int*)c->l_off.p, (ListEntry*)c->list.p, 0, with_dir, sym,
