@@ -133,13 +133,18 @@ sph_status scan_exclusive(sph_ctx* c, const int* in, int* out, int n, int* d_tot
 // of the workgroup owns the contiguous quarter w of the tile, and lane l of
 // the wave holds keys r*64 + l of that quarter (r = 0..RS_ITEMS-1), so rounds
 // visit the quarter in order.  The per-digit global offsets come from an
-// exclusive scan of the digit-major [256][n_tiles] histogram; up to RS_FEW keys
+// exclusive scan of the digit-major [256][n_tiles] histogram.  Up to RS_FEW keys
 // the tiles are of RS_ITEMS = 4 rounds (more workgroups) and each workgroup of the
-// scatter sums the histogram itself (SUM; a pass is two launches instead of
-// five).
+// scatter sums the histogram itself (OFF_SUM; a pass is two launches).  Up to
+// RS_BLOCKS blocks of the histogram (16.7 million keys) the scan stops at its
+// blocks, and each workgroup of the scatter scans their sums (OFF_BLOCKS; three
+// launches: 2 million keys, 5 us less a pass).  Beyond, the whole scan
+// comes first (OFF_SCAN; five launches).
 // ---------------------------------------------------------------------------
 #define RS_WAVES 4
 #define RS_FEW 65536
+#define RS_BLOCKS 1024
+enum { OFF_SUM, OFF_BLOCKS, OFF_SCAN };
 
 template <int RS_ITEMS>
 __global__ __launch_bounds__(256) void k_rs_hist(const uint64_t* __restrict__ keys, int n, int shift, int* hist, int nb)
@@ -162,10 +167,11 @@ __global__ __launch_bounds__(256) void k_rs_hist(const uint64_t* __restrict__ ke
 // round, lane, i.e. input order within each digit), then written out in
 // that order: consecutive lanes write consecutive positions of one digit's
 // run, so the stores coalesce into runs of ~RS_TILE / 256 keys.
-template <int RS_ITEMS, bool SUM>
+template <int RS_ITEMS, int OFF>
 __global__ __launch_bounds__(256) void k_rs_scatter(const uint64_t* __restrict__ kin, const uint32_t* __restrict__ vin,
                                                     uint64_t* __restrict__ kout, uint32_t* __restrict__ vout, int n,
-                                                    int shift, const int* __restrict__ offs, int nb)
+                                                    int shift, const int* __restrict__ offs, int nb,
+                                                    const int* __restrict__ block_sums)
 {
     constexpr int RS_TILE = 64 * RS_WAVES * RS_ITEMS;
     __shared__ int wcount[RS_WAVES][256];
@@ -176,6 +182,29 @@ __global__ __launch_bounds__(256) void k_rs_scatter(const uint64_t* __restrict__
     __shared__ uint32_t sv[RS_TILE];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     for (int q = tid; q < RS_WAVES * 256; q += 256) (&wcount[0][0])[q] = 0;
+    __shared__ int bsum[OFF == OFF_BLOCKS ? RS_BLOCKS : 1];  // exclusive scan of the blocks' sums
+    if (OFF == OFF_BLOCKS) {
+        constexpr int PER = RS_BLOCKS / 256;
+        const int blocks = (int)((256l * nb + SCAN_BLOCK - 1) / SCAN_BLOCK);
+        int v[PER], s = 0;
+        for (int q = 0; q < PER; q++) {
+            v[q] = tid * PER + q < blocks ? block_sums[tid * PER + q] : 0;
+            s += v[q];
+        }
+        int inc = s;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int t = __shfl_up(inc, off);
+            if (lane >= off) inc += t;
+        }
+        if (lane == 63) wsum[w] = inc;
+        __syncthreads();
+        int ex = inc - s;
+        for (int q = 0; q < w; q++) ex += wsum[q];
+        for (int q = 0; q < PER; q++) {
+            bsum[tid * PER + q] = ex;
+            ex += v[q];
+        }
+    }
     __syncthreads();
     const long tile = (long)blockIdx.x * RS_TILE;
     const long wstart = tile + (long)w * 64 * RS_ITEMS;
@@ -210,7 +239,7 @@ __global__ __launch_bounds__(256) void k_rs_scatter(const uint64_t* __restrict__
         int start = inc - cnt;
         for (int q = 0; q < w; q++) start += wsum[q];
         int first;  // of the tile's run of digit d in the output
-        if (SUM) {
+        if (OFF == OFF_SUM) {
             int all = 0, before = 0;
             for (int q = 0; q < nb; q++) {
                 const int h = offs[(long)d * nb + q];
@@ -228,7 +257,9 @@ __global__ __launch_bounds__(256) void k_rs_scatter(const uint64_t* __restrict__
             first = in2 - all + before;
             for (int q = 0; q < w; q++) first += wsum[q];
         } else {
-            first = offs[(long)d * nb + blockIdx.x];
+            const long at = (long)d * nb + blockIdx.x;
+            first = offs[at];
+            if (OFF == OFF_BLOCKS) first += bsum[at / SCAN_BLOCK];
         }
         gshift[d] = first - start;
         int run = start;
@@ -284,6 +315,9 @@ sph_status radix_sort(sph_ctx* c, int n, int bits, DevBuf* kb, DevBuf* vb, int* 
         if (!few) SPH_TRY(buf_ensure(c->rs_hist, hist_bytes(nb)));
         int* hist = (int*)c->rs_hist.p;
         int* total = (int*)c->flags.p + FI_SCRATCH;
+        const int blocks = (int)((256l * nb + SCAN_BLOCK - 1) / SCAN_BLOCK);
+        if (!few && blocks <= RS_BLOCKS) SPH_TRY(buf_ensure(c->scan_tmp, (size_t)blocks * sizeof(int)));
+        int* sums = (int*)c->scan_tmp.p;
         for (int shift = 0; shift < bits; shift += 8) {
             uint64_t* kin = (uint64_t*)kb[cur].p;
             uint32_t* vin = (uint32_t*)vb[cur].p;
@@ -292,12 +326,18 @@ sph_status radix_sort(sph_ctx* c, int n, int bits, DevBuf* kb, DevBuf* vb, int* 
             if (few) {
                 k_rs_hist<4><<<nb, 256, 0, c->stream>>>(kin, n, shift, hist, nb);
                 SPH_CHECK_LAUNCH();
-                k_rs_scatter<4, true><<<nb, 256, 0, c->stream>>>(kin, vin, kout, vout, n, shift, hist, nb);
+                k_rs_scatter<4, OFF_SUM><<<nb, 256, 0, c->stream>>>(kin, vin, kout, vout, n, shift, hist, nb, nullptr);
+            } else if (blocks <= RS_BLOCKS) {
+                k_rs_hist<16><<<nb, 256, 0, c->stream>>>(kin, n, shift, hist, nb);
+                SPH_CHECK_LAUNCH();
+                k_scan_block<<<blocks, SCAN_T, 0, c->stream>>>(hist, hist, 256 * nb, sums);
+                SPH_CHECK_LAUNCH();
+                k_rs_scatter<16, OFF_BLOCKS><<<nb, 256, 0, c->stream>>>(kin, vin, kout, vout, n, shift, hist, nb, sums);
             } else {
                 k_rs_hist<16><<<nb, 256, 0, c->stream>>>(kin, n, shift, hist, nb);
                 SPH_CHECK_LAUNCH();
                 SPH_TRY(scan_exclusive(c, hist, hist, 256 * nb, total));
-                k_rs_scatter<16, false><<<nb, 256, 0, c->stream>>>(kin, vin, kout, vout, n, shift, hist, nb);
+                k_rs_scatter<16, OFF_SCAN><<<nb, 256, 0, c->stream>>>(kin, vin, kout, vout, n, shift, hist, nb, nullptr);
             }
             SPH_CHECK_LAUNCH();
             cur ^= 1;
