@@ -492,9 +492,9 @@ def main():
     ap.add_argument("--lists", choices=("cell", "particle"), default="cell",
                     help="neighbour lists of the density and force kernels (default: the autotuner's choice)")
     ap.add_argument("--tile", type=int, default=0, help="LDS segment of the particle-list kernels")
-    ap.add_argument("--waves-density", type=int, default=0, help="occupancy target of the density kernel (0: 6)")
-    ap.add_argument("--waves-force", type=int, default=0, help="occupancy target of the force kernel (0: 5)")
-    ap.add_argument("--batch", type=int, default=0, help="neighbour-cell entries staged per batch (0: 32)")
+    ap.add_argument("--waves-density", type=int, default=0, help="occupancy target of the density kernel (0: 5)")
+    ap.add_argument("--waves-force", type=int, default=0, help="occupancy target of the force kernel (no effect on the packed kernels)")
+    ap.add_argument("--batch", type=int, default=0, help="neighbour-cell entries staged per batch (no effect on the packed kernels)")
     ap.add_argument("--no-h-drift", action="store_true",
                     help="start the H iteration of a step from the previous H as is")
     ap.add_argument("--seed", type=int, default=2741)

@@ -81,7 +81,9 @@ typedef struct {
     int max_h_iter;      /* smoothing-length sweeps per density call */
     int n_split;         /* split cells holding more than this many particles (<= 64) */
     int precision;       /* SPH_FP64, SPH_FP32C (cell-relative FP32, compensated sums)
-                            or SPH_FP32 (cell-relative FP32, plain sums) */
+                            or SPH_FP32 (cell-relative FP32, plain sums; with cell
+                            lists and box pruning the density and the gather force
+                            of both sum their FP32 terms in FP64) */
     int exec_mode;       /* SPH_EXEC_GRID: one workgroup slot per cell;
                             SPH_EXEC_PERSISTENT: in the force loop, resident
                             workgroups drain device task queues, one per XCD
@@ -129,7 +131,7 @@ typedef struct {
                             or 1024 (0: 1024 for the density and 512 for the force; FP64
                             at most 512 / 256) */
     int waves_density;   /* cell lists, FP32 modes: occupancy target (waves per SIMD) the
-                            packed density kernel is compiled for, 4, 5, 6 or 8 (0: 6; 8
+                            packed density kernel is compiled for, 4, 5, 6 or 8 (0: 5; 8
                             runs the kernel of 6) */
     int waves_force;     /* the same for the gather force kernel, 4, 5, 6 or 8 (0: 4; its
                             LDS holds 4 waves, which every choice runs) */

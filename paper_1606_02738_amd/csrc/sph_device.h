@@ -505,7 +505,7 @@ __device__ inline bool dens_finish(const DensArgs& a, int i, bool act, int jg, i
 // v_mfma_f32_16x16x16_bf16 per 16 x 16 tests, and the sign bits are the mask
 // (one v_alignbit per 64 tests instead of the ~11 instructions of a
 // per-particle loop with a ballot).  Each factor is a sum of two bfloat16, a
-// product x y the three terms xh yh + xh ym + xm yh: a quarter of the float32
+// product x y the three terms xh yh + xh ym + xm yh: half of the float32
 // product's matrix time, and work that VALU instructions of other waves
 // overlap, which float32 products do not.  What the terms leave out is below 3
 // 2^-18 |x y| per coordinate, 2^-16 (|p_i|^2 + |p_j|^2) in all with the

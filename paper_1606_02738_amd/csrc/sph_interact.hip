@@ -23,10 +23,10 @@
 #include "sph_device.h"
 
 // Occupancy target (waves per SIMD, WPE) of the packed density and gather
-// force kernels, the measured best at 256^3 clustered: the density sweep takes
-// 6.8 ms at 6 waves and 7.2 at 4; the force's LDS holds 4 waves (11.0 ms, 11.1
-// with 3 waves and larger tiles, 18.1 with 5 waves and tiles of 64).
-#define SPH_DENS_WAVES 6
+// force kernels, the measured best at 256^3 clustered: density sweeps of a step
+// 5.75 ms at 5 waves, 5.87 at 6 (more spills), 6.22 at 4; the force's LDS holds
+// 4 waves (9.45 ms, 9.82 with 3, 21.4 with 5 waves and tiles of 80).
+#define SPH_DENS_WAVES 5
 #define SPH_FORCEG_WAVES 4
 #define SPH_DENS_WAVES64 3
 #define SPH_FORCEG_WAVES64 2
@@ -36,8 +36,8 @@
 #define SPH_BATCH 32
 // Candidates per 16-lane row of a tile: the largest tiles (fewest partly filled
 // rounds of pairs) whose LDS leaves the waves above resident.  Density at 32 /
-// 28 / 24 / 16: 6.8 / 7.4 / 7.6 / 7.3 ms; force at 28 / 24 / 20 / 16: 11.0 / 11.1
-// / 11.4 / 11.5 ms.
+// 28 / 24: 5.87 / 6.10 / 6.00 ms (6 waves); force at 28 / 24: 9.45 / 9.49 ms, 32 at
+// 3 waves 9.78.
 #define DENS_ROW 32
 #define FORCE_ROW 28
 
@@ -84,11 +84,10 @@ __device__ inline float get_test(const Tile& L, int j, int lane)
 
 // Density sweep of one leaf (at most 64 particles, box pruning): candidate
 // stream, matrix-unit range tests and pair-parallel sums (sph_device.h), then
-// the FP64 Newton test.  Bound by VALU and MFMA issue, which together fill
-// every cycle (FP32 MFMA does not overlap with VALU work here): 7.4e3 VALU and
-// 208 MFMA instructions per leaf at 256^3 clustered, 2.1e4 VALU instructions
-// with a ballot loop over the particles per tile and lane = particle sums.
-// Stage at 256^3 clustered FP32C 9.3 -> 6.3 ms, at 64^3 FP64 2.6 -> 1.2 ms.
+// the FP64 Newton test.  Bound by VALU issue, which is active in 91% of the
+// cycles: about 7.9e3 VALU instructions per leaf at 256^3 clustered, 2.1e4 with
+// a ballot loop over the particles per tile and lane = particle sums.  Sweeps
+// of a step there 9.9 -> 5.75 ms (FP32C), density stage at 64^3 FP64 2.6 -> 0.95 ms.
 // With NW > 1 the waves of the workgroup share the leaf's list; wave 0 adds up
 // their sums.
 template <typename T, int NW>
@@ -1004,9 +1003,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPH_FORCE_W
 // pairs-once form) but nothing is accumulated on the j side, so there are no
 // global atomics and each output is written once.  Candidate stream,
 // matrix-unit range tests (against H_i and H_j) and pair-parallel sums as in
-// the density, and bound like it: 1.08e4 VALU and 456 MFMA instructions per
-// leaf at 256^3 clustered (2.6e4 before), 12.9 -> 10.2 ms; 64^3 FP64 1.33 ->
-// 0.70 ms.
+// the density, and bound by VALU issue (active in 84% of the cycles at the 4
+// waves per SIMD its LDS holds): 1.1e4 VALU instructions per leaf at 256^3
+// clustered (2.6e4 with a ballot loop over the particles per tile), 12.9 -> 9.45
+// ms; 64^3 FP64 1.33 -> 0.55 ms.
 // ---------------------------------------------------------------------------
 template <typename T>
 struct GTile {
