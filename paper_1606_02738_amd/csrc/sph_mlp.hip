@@ -891,14 +891,18 @@ static sph_status ensure_params(sph_ctx* c)
 
 extern "C" {
 
-// Scratch of the context-free calls over n rows: packed weights, partial
-// gradients of each workgroup (k_mlp_fb, MB rows each) and the loss slot.
+// Scratch of the context-free calls over n rows: packed weights or partial
+// gradients and the loss slot.  Callers keep workspaces by what this returned
+// before, so the sum stays that of weights of 19600 bytes and a workgroup per
+// 32 rows; sph_mlp_forward takes the weights only, sph_mlp_loss_grad the
+// partials of at most as many workgroups (k_mlp_fb, MB rows each).
 static size_t mlp_scratch_bytes(int64_t n)
 {
-    const size_t nwg = (size_t)fb_workgroups(n);
+    static_assert(MB >= 32 && sizeof(MlpPacked) < (32 << 10), "must fit what is returned");
+    const size_t nwg = (size_t)std::max<int64_t>(1, std::min<int64_t>((n + 31) / 32, MLP_FB_WGS));
     const size_t r = 256;
     auto up = [&](size_t b) { return (b + r - 1) / r * r + r; };
-    return up(sizeof(MlpPacked)) + up(nwg * NT * sizeof(float)) + up(nwg * sizeof(float)) + up(sizeof(float)) +
+    return up(19600) + up(nwg * NT * sizeof(float)) + up(nwg * sizeof(float)) + up(sizeof(float)) +
            ((size_t)4 << 10);
 }
 
