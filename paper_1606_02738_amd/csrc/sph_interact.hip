@@ -1621,6 +1621,18 @@ __global__ __launch_bounds__(256) void k_extent_check(int n_leaves, const int* _
     if (lane == 0 && ext > 2.0 * SPH_FP32_EXTENT_RATIO * hm) atomicOr(flags, FLAG_REBUILD);
 }
 
+// FLAG_REBUILD in *flag if a splittable leaf is too wide for its smallest
+// converged H (FP32 cell-relative coordinates).
+static sph_status extent_check(sph_ctx* c, int* flag)
+{
+    k_extent_check<<<blocks_for(c->n_leaves, 4), 256, 0, c->stream>>>(
+        c->n_leaves, (const int*)c->l_begin.p, (const int*)c->l_count.p, (const double*)c->l_lo.p,
+        (const double*)c->l_hi.p, (const int*)c->leaf_node.p, (const Node*)c->nodes.p, c->D, c->P.H, 2.0 * c->delta,
+        flag);
+    SPH_CHECK_LAUNCH();
+    return SPH_OK;
+}
+
 static sph_status density_loop(sph_ctx* c, int done_sweeps, unsigned long long unconv0)
 {
     int* flags = (int*)c->flags.p;
@@ -1628,7 +1640,8 @@ static sph_status density_loop(sph_ctx* c, int done_sweeps, unsigned long long u
     int sweeps = 0;
     unsigned long long unconv = unconv0;
     int fl = 0;
-    bool prec_rebuilt = false;
+    unsigned long long nd = 0;  // CNT_NDENS as of the last sweep
+    bool prec_rebuilt = false, swept = false;
     sph_status status = SPH_OK;
     for (sweeps = done_sweeps + 1; sweeps <= c->prm.max_h_iter; sweeps++) {
         SPH_CHECK_HIP(hipMemsetAsync(flags, 0, sizeof(int), c->stream));
@@ -1650,6 +1663,8 @@ static sph_status density_loop(sph_ctx* c, int done_sweeps, unsigned long long u
             c->st.n_dens_evals = (int64_t)hc[CNT_DEVAL];
         }
         unconv = hc[CNT_UNCONV];
+        nd = hc[CNT_NDENS];
+        swept = true;
         if (sweeps <= 8) c->st.unconv_after[sweeps - 1] = (int)std::min<unsigned long long>(unconv, INT32_MAX);
         if (fl & FLAG_BOX_SMALL) status = SPH_ERR_BOX_TOO_SMALL;
         // (inside sph_step the refresh of the next step takes this test
@@ -1657,11 +1672,7 @@ static sph_status density_loop(sph_ctx* c, int done_sweeps, unsigned long long u
         if (unconv == 0 && c->prm.precision != SPH_FP64 && !prec_rebuilt && status == SPH_OK &&
             sweeps < c->prm.max_h_iter && !c->in_step) {
             SPH_CHECK_HIP(hipMemsetAsync(flags, 0, sizeof(int), c->stream));
-            k_extent_check<<<blocks_for(c->n_leaves, 4), 256, 0, c->stream>>>(
-                c->n_leaves, (const int*)c->l_begin.p, (const int*)c->l_count.p, (const double*)c->l_lo.p,
-                (const double*)c->l_hi.p, (const int*)c->leaf_node.p, (const Node*)c->nodes.p, c->D, c->P.H,
-                2.0 * c->delta, flags);
-            SPH_CHECK_LAUNCH();
+            SPH_TRY(extent_check(c, flags));
             SPH_CHECK_HIP(hipMemcpyAsync(&fl, flags, sizeof(int), hipMemcpyDeviceToHost, c->stream));
             SPH_CHECK_HIP(hipStreamSynchronize(c->stream));
             if (fl & FLAG_REBUILD) {
@@ -1699,9 +1710,10 @@ static sph_status density_loop(sph_ctx* c, int done_sweeps, unsigned long long u
             c->st.relists++;
         }
     }
-    unsigned long long nd = 0;
-    SPH_CHECK_HIP(hipMemcpyAsync(&nd, &cnt[CNT_NDENS], 8, hipMemcpyDeviceToHost, c->stream));
-    SPH_CHECK_HIP(hipStreamSynchronize(c->stream));
+    if (!swept) {
+        SPH_CHECK_HIP(hipMemcpyAsync(&nd, &cnt[CNT_NDENS], 8, hipMemcpyDeviceToHost, c->stream));
+        SPH_CHECK_HIP(hipStreamSynchronize(c->stream));
+    }
     c->st.sweeps = std::min(sweeps, c->prm.max_h_iter);
     c->st.n_unconverged = (int)unconv;
     c->st.n_dens = (int64_t)nd;
@@ -1740,6 +1752,11 @@ sph_status density_all(sph_ctx* c)
         SPH_CHECK_LAUNCH();
     }
     SPH_CHECK_HIP(hipEventRecord(c->kev[1], c->stream));
+    // the FP32 extent check of a call outside a step, read with the sweeps'
+    // outcome (in the host loop, after a sweep of no particle, it cost that sweep
+    // and three reads: cold run of 12^3 487 -> 400 us, stages at 127^3 3.75 -> 3.64 ms)
+    const bool check = c->prm.precision != SPH_FP64 && !c->in_step;
+    if (check) SPH_TRY(extent_check(c, flags + FI_EXTENT));
     FlagsCounters fc;
     SPH_TRY(read_flags(c, fc));
     const int* hfl = fc.flags;
@@ -1758,8 +1775,8 @@ sph_status density_all(sph_ctx* c)
                                     ? (int)std::min<unsigned long long>(hc[CNT_UHIST + k], INT32_MAX)
                                     : -1;
     sph_status st = SPH_OK;
-    if (g == 1 && (c->prm.precision == SPH_FP64 || c->in_step)) {
-        // converged (the FP32 extent check after a cold start runs in the host loop)
+    if (g == 1 && (!check || done >= c->prm.max_h_iter || !(hfl[FI_EXTENT] & FLAG_REBUILD))) {
+        // converged (cells too coarse for the final H: the host loop rebuilds)
         c->st.sweeps = done;
         c->st.n_unconverged = 0;
         c->st.n_dens = (int64_t)hc[CNT_NDENS];
@@ -1978,6 +1995,7 @@ __global__ void k_graph_begin(unsigned long long* cnt, int* flags, int* gate)
         cnt[CNT_GSWEEPS] = 1ull;  // the first sweep follows
         for (int k = CNT_UHIST; k < CNT_N; k++) cnt[k] = 0ull;
         flags[FI_FLAGS] = 0;
+        flags[FI_EXTENT] = 0;
         *gate = 0;
     }
 }

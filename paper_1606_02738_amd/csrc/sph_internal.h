@@ -124,7 +124,7 @@ enum {
 
 // Slots of the int[64] flags buffer.
 enum { FI_FLAGS = 0, FI_SCRATCH = 8, FI_LEVELFULL = 9, FI_NLEAVES = 10, FI_NLIST = 11, FI_GATE = 12, FI_MAXLEAF = 13, FI_MAXLIST = 14, FI_PLROWS = 15, FI_WOVF = 16,
-       FI_WINC = 17, FI_NCHUNK = 18, FI_NWIDE = 19, FI_WIDEMIN = 20, FI_WIDECLASS = 21, FI_LEVEL = 32, FI_NFLAGS = 64 };
+       FI_WINC = 17, FI_NCHUNK = 18, FI_NWIDE = 19, FI_WIDEMIN = 20, FI_WIDECLASS = 21, FI_EXTENT = 25, FI_LEVEL = 32, FI_NFLAGS = 64 };
 
 // Waves that share a leaf with a long list, and the list length from which
 // they do: one wave on the longest lists of a clustered box (800 entries, the
