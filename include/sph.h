@@ -300,7 +300,10 @@ sph_status sph_density_ghost_force(sph_ctx* ctx);
  * sums.  Requires a previous sph_force (forces of the current positions).
  * A rebuild inside the step reorders the particles without carrying rho,
  * drho_dH, omega and P along (the density and ghost stages then rewrite
- * them); after a failed step they are undefined. */
+ * them); after a failed step they are undefined.  Where the cells or lists
+ * could not be made (here or in sph_density: invalid particles, no room) there
+ * are none: sph_step may be called again, the other stages, sph_interpolate and
+ * sph_domain_sums give SPH_ERR_STATE until sph_build_cells succeeds. */
 sph_status sph_step(sph_ctx* ctx, double dt);
 
 /* SPH interpolation, Sec. 2, eq. (interp): out[k] = sum_i m_i Q_i / rho_i

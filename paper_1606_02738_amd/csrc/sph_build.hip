@@ -1367,7 +1367,6 @@ static sph_status permute_all(sph_ctx* c, const uint32_t* perm, void* side_tmp)
     auto permute_group = [&](const std::vector<uint64_t*>& arrays, const DevBuf& b, hipStream_t st) {
         const size_t rows = std::min<size_t>(b.cap / ((size_t)n * 8), 18);
         if (!b.p || rows < 2) return false;
-        c->built = c->sorted = false;  // (the last build's lists are gone)
         for (size_t k = 0; k < arrays.size(); k += rows) {
             PermArrays P{};
             while (P.n8 < (int)std::min(rows, arrays.size() - k)) {
@@ -1530,7 +1529,7 @@ __global__ __launch_bounds__(256) void k_wide_list(int n_leaves, const int* __re
     if (nw && (threadIdx.x & 63) == 0) atomicAdd(n_wide, nw);
 }
 
-sph_status relist(sph_ctx* c)
+static sph_status make_lists(sph_ctx* c)
 {
     // particle lists: radii and skins from the current H
     if (c->prm.lists == SPH_LISTS_PARTICLE) SPH_TRY(plist_ext(c, true, nullptr));
@@ -1633,6 +1632,19 @@ sph_status relist(sph_ctx* c)
     return SPH_OK;
 }
 
+// New lists over the cells of the last build.  Where this fails there are none:
+// the offsets are those of lists that found no room, and the list's buffer may
+// be gone.  Later calls must see that (sph_get_stats counts the lists' pairs).
+sph_status relist(sph_ctx* c)
+{
+    const bool built = c->built, sorted = c->sorted;
+    c->built = c->sorted = false;
+    SPH_TRY(make_lists(c));
+    c->built = built;
+    c->sorted = sorted;
+    return SPH_OK;
+}
+
 // c->dom_h to the device; n < 0: the start of a build, else its second call.
 static sph_status set_domains(sph_ctx* c, int n)
 {
@@ -1654,6 +1666,9 @@ sph_status build_all(sph_ctx* c)
     const int64_t n = c->n;
     const int nd = c->prm.n_domains;
     int* flags = (int*)c->flags.p;
+    // until this one is complete: a failure on the way (invalid particles, no
+    // room) leaves cells, lists and device flags that belong to no build
+    c->built = c->sorted = false;
 
     // a fresh build: no displacement since the lists were made
     c->delta = 0.0;

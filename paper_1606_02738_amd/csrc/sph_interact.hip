@@ -1846,7 +1846,7 @@ static sph_status set_prediction(sph_ctx* c)
 
 sph_status ghost_all(sph_ctx* c)
 {
-    if (!c->dens_done) return SPH_ERR_STATE;
+    if (!c->dens_done || !c->sorted) return SPH_ERR_STATE;
     const double *u = c->P.u, *vx = c->P.vx, *vy = c->P.vy, *vz = c->P.vz;
     SPH_TRY(set_prediction(c));
     SPH_CHECK_HIP(hipEventRecord(c->ev[2], c->stream));
@@ -1947,7 +1947,7 @@ __global__ __launch_bounds__(PART_N) void k_count_totals(unsigned long long* cnt
 // sph_get_stats (force_pending).
 sph_status force_all(sph_ctx* c)
 {
-    if (!c->ghost_done) return SPH_ERR_STATE;
+    if (!c->ghost_done || !c->sorted) return SPH_ERR_STATE;
     const size_t nb8 = (size_t)c->n * 8;
     unsigned long long* cnt = (unsigned long long*)c->counters.p;
     SPH_CHECK_HIP(hipEventRecord(c->ev[4], c->stream));
