@@ -1112,14 +1112,15 @@ __device__ __forceinline__ void force_leaf_gather(const ForceArgs& a, int A, typ
                 const T r = r2 * ir, qi = r * p.w, qj = r * ihj;
                 const T Fi = f.w * spline_dw6(qi);   // A_i dW/dr(r, H_i)
                 const T Fj = fj.w * spline_dw6(qj);  // A_j dW/dr(r, H_j)
-                const T F = (Fi + Fj) * ir;
+                // (a pair let in by the tests' margin adds nothing, whatever its
+                // velocities and factors)
+                const bool in = fmin(qi, qj) < T(1);
+                const T F = in ? (Fi + Fj) * ir : T(0);
                 const T dvdr = ((f.x - fj.x) * dx + (f.y - fj.y) * dy + (f.z - fj.z) * dz) * ir;
                 const T mjF = q.w * F;
                 ax -= (double)(mjF * dx);
                 ay -= (double)(mjF * dy);
                 az -= (double)(mjF * dz);
-                // (a pair let in by the tests' margin adds nothing, whatever its velocities)
-                const bool in = fmin(qi, qj) < T(1);
                 du += (double)(in ? q.w * Fi * dvdr : T(0));
                 cnt += qi < T(1);
                 nmax += in;
