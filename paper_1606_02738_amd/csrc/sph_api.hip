@@ -37,6 +37,22 @@ void* Pool::take(size_t bytes)
     return nullptr;
 }
 
+// (not in `high` and `needed`: the calls that borrow either do without or ask
+// for what must be there by take())
+void* Pool::take_last(size_t bytes)
+{
+    bytes = (bytes + POOL_ALIGN - 1) & ~(POOL_ALIGN - 1);
+    for (auto it = free_blocks.rbegin(); it != free_blocks.rend(); ++it) {
+        if (it->second < bytes) continue;
+        const size_t off = it->first + it->second - bytes;
+        it->second -= bytes;
+        if (it->second == 0) free_blocks.erase(it->first);
+        in_use += bytes;
+        return base + off;
+    }
+    return nullptr;
+}
+
 void Pool::give(void* p, size_t bytes)
 {
     bytes = (bytes + POOL_ALIGN - 1) & ~(POOL_ALIGN - 1);
@@ -212,7 +228,7 @@ sph_status sph_destroy(sph_ctx* c)
     for (hipEvent_t e : c->side_ev)
         if (e) (void)hipEventDestroy(e);
     DevBuf* all[] = {&c->dom_d, &c->dstat, &c->keys[0], &c->keys[1], &c->vals[0], &c->vals[1], &c->ikeys[0], &c->ikeys[1], &c->ivals[0], &c->ivals[1], &c->dranges, &c->tmp, &c->nodes, &c->wnodes,
-                     &c->lvl_cmap, &c->lvl_bnd, &c->lvl_sum, &c->leafmark, &c->leaf_node, &c->l_begin, &c->l_count,
+                     &c->leafmark, &c->leaf_node, &c->l_begin, &c->l_count,
                      &c->l_origin, &c->l_lo, &c->l_hi, &c->l_hlist, &c->l_dom, &c->l_off, &c->l_active, &c->l_sorted,
                      &c->l_cnt, &c->list, &c->wide, &c->pos4, &c->fv4, &c->hf, &c->skey, &c->sidx,
                      &c->hlo, &c->hhi, &c->conv, &c->state, &c->flags, &c->counters,

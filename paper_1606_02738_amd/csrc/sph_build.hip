@@ -565,11 +565,12 @@ __device__ inline int emit_child(Node* nodes, int node, int first, int g, int D,
 // takes the children of EMIT_CELLS cells, one per lane: it adds up the tiles
 // before its own and scans the counts of its tile.  (One lane per cell, which
 // wrote its children in turn: 25 us a level at 128^3, 17 us now.)  If the
-// children do not fit in the node buffer nothing is written but their number.
+// children do not fit in the node buffer, or their level in the room for one,
+// nothing is written but their number.
 #define EMIT_CELLS 32
-__global__ __launch_bounds__(256) void k_emit_children(Node* nodes, int level, int cap, int D, int n_split, double h_ratio,
-                                                       const int* __restrict__ bnd, const int* __restrict__ tile_sum,
-                                                       int2* cmap, int* flags)
+__global__ __launch_bounds__(256) void k_emit_children(Node* nodes, int level, int cap, int level_cap, int D, int n_split,
+                                                       double h_ratio, const int* __restrict__ bnd,
+                                                       const int* __restrict__ tile_sum, int2* cmap, int* flags)
 {
     __shared__ int wsum[4];
     __shared__ int nchild[EMIT_CELLS], at[EMIT_CELLS];
@@ -586,7 +587,7 @@ __global__ __launch_bounds__(256) void k_emit_children(Node* nodes, int level, i
         int base, all;
         wg_scan(before, wsum, base);
         wg_scan(total, wsum, all);
-        const bool fits = all <= cap - next;
+        const bool fits = all <= cap - next && all <= level_cap;
         if (w == 0 && threadIdx.x == 0) {
             flags[FI_LEVEL + level + 2] = next + (fits ? all : 0);
             if (!fits) flags[FI_LEVELFULL] = all;
@@ -1320,12 +1321,11 @@ static sph_status permute_all(sph_ctx* c, const uint32_t* perm, void* side_tmp)
             if (a) P.a[P.n8++] = (uint64_t*)a;
         P.d4 = (uint32_t*)c->P.domain;
         const int rows = P.n8 + (P.d4 ? 1 : 0);
-        DevBuf t;
-        if (buf_ensure(t, (size_t)rows * n * 8) == SPH_OK) {
+        Borrowed t;
+        if (t.take((size_t)rows * n * 8)) {
             const dim3 g(blocks_for(n, 256), rows);
             k_gather_all<<<g, 256, 0, c->stream>>>((int)n, perm, P, (uint64_t*)t.p, 0);
             k_gather_all<<<g, 256, 0, c->stream>>>((int)n, perm, P, (uint64_t*)t.p, 1);
-            buf_free(t);  // (its next owner's work follows on the stream)
             SPH_CHECK_LAUNCH();
             return SPH_OK;
         }
@@ -1549,7 +1549,8 @@ static sph_status make_lists(sph_ctx* c)
     int cap = c->walk_cap;
     while (cap > 16 && (size_t)nL * cap * sizeof(ListEntry) > (size_t)c->n * SPH_WALK_SLOT_BYTES) cap /= 2;
     const bool one_pass = (size_t)nL * cap * sizeof(ListEntry) <= (size_t)c->n * SPH_WALK_SLOT_BYTES + ((size_t)1 << 20);
-    const int ovf_chunks = (int)std::min<int64_t>(std::max<int64_t>(1024, c->n * SPH_WALK_OVF_BYTES / (64 * 16)),
+    // (at least 1 MB of chunks with the 32 KB of the partial counts' lines)
+    const int ovf_chunks = (int)std::min<int64_t>(std::max<int64_t>(992, c->n * SPH_WALK_OVF_BYTES / (64 * 16)),
                                                   INT32_MAX / 64);
     if (one_pass) {
         SPH_TRY(buf_ensure(c->walk_scratch, (size_t)nL * cap * sizeof(ListEntry)));
@@ -1660,6 +1661,67 @@ static sph_status set_domains(sph_ctx* c, int n)
     SPH_CHECK_LAUNCH();
     return SPH_OK;
 }
+
+// Room for the work on one octree level of up to `cells` cells: the bounds of
+// their octants, their chunks (one per STATS_CHUNK particles, at most one more per
+// cell) and their children per 256 cells.
+struct LevelRoom {
+    static constexpr size_t MOST = INT32_MAX / 9;  // (the bounds are indexed by int)
+    int* bnd = nullptr;
+    int2* cmap = nullptr;
+    int* sum = nullptr;
+    size_t cells = 0;
+    static size_t up(size_t b) { return (b + 255) & ~(size_t)255; }
+    static size_t bnd_bytes(size_t cells) { return up(cells * 9 * sizeof(int)); }
+    static size_t cmap_bytes(size_t cells, int64_t n) { return up(((size_t)n / STATS_CHUNK + cells) * sizeof(int2)); }
+    static size_t bytes(size_t cells, int64_t n)
+    {
+        return bnd_bytes(cells) + cmap_bytes(cells, n) + up((cells / 256 + 1) * sizeof(int));
+    }
+    static size_t cells_in(size_t b, int64_t n)
+    {
+        const size_t fixed = (size_t)n / STATS_CHUNK * sizeof(int2) + 1024;
+        return b > fixed ? std::min((b - fixed) / 45, MOST) : 0;  // (44 bytes a cell and 4 per 256)
+    }
+    void place(void* at, size_t n_cells, int64_t n)
+    {
+        bnd = (int*)at;
+        cmap = (int2*)((char*)at + bnd_bytes(n_cells));
+        sum = (int*)((char*)cmap + cmap_bytes(n_cells, n));
+        cells = n_cells;
+    }
+    bool borrow(size_t n_cells, int64_t n)
+    {
+        if (!mem.take(bytes(n_cells, n))) return false;
+        mem.pool->high = std::max(mem.pool->high, mem.pool->in_use);
+        place(mem.p, n_cells, n);
+        return true;
+    }
+    // (what sph_get_stats reports as needed)
+    sph_status refused(size_t n_cells, int64_t n)
+    {
+        if (mem.pool) mem.pool->needed = std::max(mem.pool->needed, mem.pool->in_use + bytes(n_cells, n));
+        return SPH_ERR_WORKSPACE;
+    }
+    void give()
+    {
+        mem.give();
+        cells = 0;
+    }
+    void swap(LevelRoom& o)
+    {
+        std::swap(bnd, o.bnd);
+        std::swap(cmap, o.cmap);
+        std::swap(sum, o.sum);
+        std::swap(cells, o.cells);
+        std::swap(mem.pool, o.mem.pool);
+        std::swap(mem.p, o.mem.p);
+        std::swap(mem.bytes, o.mem.bytes);
+    }
+
+private:
+    Borrowed mem;
+};
 
 sph_status build_all(sph_ctx* c)
 {
@@ -1803,20 +1865,23 @@ sph_status build_all(sph_ctx* c)
 
     // 4. octree, several levels between looks at them
     const int old_depth = c->depth;
-    size_t cap = std::max<size_t>((size_t)top * 2 + 1024, (size_t)(n / 8) + 1024);
-    auto level_buffers = [&]() -> sph_status {
-        // chunks of a level: one per STATS_CHUNK particles, at most one more per cell
-        SPH_TRY(buf_ensure(c->lvl_cmap, ((size_t)n / STATS_CHUNK + cap) * sizeof(int2)));
-        SPH_TRY(buf_ensure(c->lvl_sum, (cap / 256 + 1) * sizeof(int)));
-        return SPH_OK;
-    };
-    // (the buffers of an earlier build that needed more)
-    cap = std::max(cap, std::min({c->nodes.cap / sizeof(Node), c->lvl_bnd.cap / (9 * sizeof(int)), (size_t)INT32_MAX / 9}));
+    // (the buffer of an earlier build that needed more)
+    size_t cap = std::max({(size_t)top * 2 + 1024, (size_t)(n / 8) + 1024,
+                           std::min(c->nodes.cap / sizeof(Node), (size_t)INT32_MAX)});
     SPH_TRY(buf_ensure(c->nodes, cap * sizeof(Node)));
-    SPH_TRY(buf_ensure(c->lvl_bnd, cap * 9 * sizeof(int)));
-    SPH_TRY(level_buffers());
+    // room for the work on one level: the last lists, which nothing reads any
+    // more, or borrowed while they are not there yet (kept, it would be 5.5
+    // bytes a particle that a workspace needs and the lists cannot use)
+    LevelRoom room;
+    const size_t want = std::min(std::max((size_t)top, std::min((size_t)n, 4 * (size_t)n / c->prm.n_split)) + 64, LevelRoom::MOST);
+    const size_t in_list = c->list.p ? LevelRoom::cells_in(c->list.cap, n) : 0;
+    if (in_list >= want) room.place(c->list.p, in_list, n);
+    else if (!room.borrow(std::max(want, (size_t)n / 8 + 1024), n) && !room.borrow(want, n)) {
+        if (in_list < (size_t)top) return room.refused(want, n);
+        room.place(c->list.p, in_list, n);
+    }
     k_top_nodes<<<blocks_for(top, TOP_CELLS), 256, 0, c->stream>>>(top, nd, (const DomainInfo*)c->dom_d.p, keys, (int)n, D,
-                                                           (Node*)c->nodes.p, (int2*)c->lvl_cmap.p, flags);
+                                                           (Node*)c->nodes.p, room.cmap, flags);
     SPH_CHECK_LAUNCH();
     // FP32 cell-relative coordinates: keep every leaf's extent within
     // SPH_FP32_EXTENT_RATIO of its smallest smoothing length
@@ -1832,22 +1897,21 @@ sph_status build_all(sph_ctx* c)
     int n_nodes = 0, nL = 0;
     bool again = false;  // the first level enqueued was counted, but its children did not fit
     for (int level = 0; level <= D;) {
-        const int wg_cells = (int)std::min<size_t>(1024, (std::min<size_t>(cap, (size_t)n) + 255) / 256);
-        const int wg_stats = (int)std::min<size_t>(2048, ((size_t)n / STATS_CHUNK + std::min<size_t>(cap, (size_t)n) + 3) / 4);
+        const size_t most = std::min({cap, room.cells, (size_t)n});  // cells of a level
+        const int wg_cells = (int)std::min<size_t>(1024, (most + 255) / 256);
+        const int wg_stats = (int)std::min<size_t>(2048, ((size_t)n / STATS_CHUNK + most + 3) / 4);
         for (int l = level; l <= last; l++) {
             if (!(again && l == level)) {
-                k_level_stats<<<wg_stats, 256, 0, c->stream>>>((Node*)c->nodes.p, l, (const int2*)c->lvl_cmap.p, flags,
-                                                              keys, c->P.x, c->P.y, c->P.z, c->P.H, D,
-                                                              (int*)c->lvl_bnd.p);
+                k_level_stats<<<wg_stats, 256, 0, c->stream>>>((Node*)c->nodes.p, l, room.cmap, flags, keys, c->P.x,
+                                                              c->P.y, c->P.z, c->P.H, D, room.bnd);
                 SPH_CHECK_LAUNCH();
             }
-            k_level_split<<<wg_cells, 256, 0, c->stream>>>((Node*)c->nodes.p, l, D, c->prm.n_split, h_ratio,
-                                                           (const int*)c->lvl_bnd.p, (int*)c->lvl_sum.p, flags,
-                                                           !(again && l == level));
+            k_level_split<<<wg_cells, 256, 0, c->stream>>>((Node*)c->nodes.p, l, D, c->prm.n_split, h_ratio, room.bnd,
+                                                           room.sum, flags, !(again && l == level));
             SPH_CHECK_LAUNCH();
-            k_emit_children<<<std::min(2048, 8 * wg_cells), 256, 0, c->stream>>>((Node*)c->nodes.p, l, (int)cap, D, c->prm.n_split, h_ratio,
-                                                             (const int*)c->lvl_bnd.p, (const int*)c->lvl_sum.p,
-                                                             (int2*)c->lvl_cmap.p, flags);
+            k_emit_children<<<std::min(2048, 8 * wg_cells), 256, 0, c->stream>>>(
+                (Node*)c->nodes.p, l, (int)cap, (int)room.cells, D, c->prm.n_split, h_ratio, room.bnd, room.sum, room.cmap,
+                flags);
             SPH_CHECK_LAUNCH();
         }
         again = false;
@@ -1870,25 +1934,27 @@ sph_status build_all(sph_ctx* c)
         }
         if (again) {
             const int nl = off[level + 1] - off[level];
-            const size_t ncap = std::max(((size_t)n_nodes + fl[FI_LEVELFULL]) * 3 / 2, cap * 2);
-            DevBuf nb2, bb2;
-            SPH_TRY(buf_ensure(nb2, ncap * sizeof(Node)));
-            const sph_status st = buf_ensure(bb2, ncap * 9 * sizeof(int));
-            if (st != SPH_OK) {
-                buf_free(nb2);
-                return st;
+            const size_t more = fl[FI_LEVELFULL];
+            if ((size_t)n_nodes + more > cap) {
+                const size_t ncap = std::max(((size_t)n_nodes + more) * 3 / 2, cap * 2);
+                DevBuf nb2;
+                SPH_TRY(buf_ensure(nb2, ncap * sizeof(Node)));
+                SPH_CHECK_HIP(hipMemcpyAsync(nb2.p, c->nodes.p, (size_t)n_nodes * sizeof(Node), hipMemcpyDeviceToDevice,
+                                             c->stream));
+                SPH_CHECK_HIP(hipStreamSynchronize(c->stream));
+                buf_free(c->nodes);
+                c->nodes = nb2;
+                cap = ncap;
             }
-            SPH_CHECK_HIP(hipMemcpyAsync(nb2.p, c->nodes.p, (size_t)n_nodes * sizeof(Node), hipMemcpyDeviceToDevice,
-                                         c->stream));
-            SPH_CHECK_HIP(hipMemcpyAsync(bb2.p, c->lvl_bnd.p, (size_t)nl * 9 * sizeof(int), hipMemcpyDeviceToDevice,
-                                         c->stream));
-            SPH_CHECK_HIP(hipStreamSynchronize(c->stream));
-            buf_free(c->nodes);
-            buf_free(c->lvl_bnd);
-            c->nodes = nb2;
-            c->lvl_bnd = bb2;
-            cap = ncap;
-            SPH_TRY(level_buffers());
+            if (more > room.cells) {
+                // (this level's bounds go on being read)
+                LevelRoom larger;
+                if (more > LevelRoom::MOST) return SPH_ERR_WORKSPACE;
+                if (!larger.borrow(std::min(more * 9 / 8, LevelRoom::MOST), n)) return larger.refused(more, n);
+                SPH_CHECK_HIP(hipMemcpyAsync(larger.bnd, room.bnd, (size_t)nl * 9 * sizeof(int), hipMemcpyDeviceToDevice,
+                                             c->stream));
+                room.swap(larger);
+            }
         }
         if (done) {
             nL = fl[FI_NLEAVES];
@@ -1897,6 +1963,7 @@ sph_status build_all(sph_ctx* c)
         last = std::min(std::max(last, level) + 2, D);
     }
     c->n_nodes = n_nodes;
+    room.give();
 
     // 5. leaves in Morton order
     const int n_words = blocks_for(n, 64);

@@ -18,6 +18,9 @@ struct Pool {
     size_t needed = 0;  // in-use bytes plus the request that did not fit (0: none failed)
     void init(void* mem, size_t bytes);
     void* take(size_t bytes);
+    // from the end of the last block that holds it: what is given back within
+    // the call leaves the blocks taken meanwhile where they would have been
+    void* take_last(size_t bytes);
     void give(void* p, size_t bytes);
 };
 
@@ -31,6 +34,30 @@ struct DevBuf {
 // point for its duration (the context's pool, or one over the workspace a
 // context-free call is given).
 extern thread_local Pool* g_pool;
+
+// Scratch of one call, given back at its end (its next owner's work follows on
+// the stream).  NULL where there is no room.
+struct Borrowed {
+    Pool* pool = nullptr;
+    void* p = nullptr;
+    size_t bytes = 0;
+    Borrowed() = default;
+    Borrowed(const Borrowed&) = delete;
+    Borrowed& operator=(const Borrowed&) = delete;
+    ~Borrowed() { give(); }
+    void* take(size_t b)
+    {
+        give();
+        pool = g_pool;
+        p = pool ? pool->take_last(bytes = b) : nullptr;
+        return p;
+    }
+    void give()
+    {
+        if (p) pool->give(p, bytes);
+        p = nullptr;
+    }
+};
 struct PoolScope {
     Pool* prev;
     explicit PoolScope(Pool* p) : prev(g_pool) { g_pool = p; }
@@ -84,7 +111,6 @@ struct sph_ctx {
     const void* keys_sorted = nullptr;  // sorted Morton keys of the last build
     DevBuf tmp;                   // permutation scratch (8 B per particle)
     DevBuf nodes;                       // octree
-    DevBuf lvl_cmap, lvl_bnd, lvl_sum;  // of one level: chunks, octant bounds (9 per cell), children per 256 cells
     DevBuf wnodes;                // compact cells for the list walk
     DevBuf leafmark;              // per 64 particles: where leaves begin, and how many
     DevBuf leaf_node;             // leaf -> node
