@@ -562,9 +562,11 @@ __device__ inline int emit_child(Node* nodes, int node, int first, int g, int D,
 }
 
 // ... of a level, in the order of the cells, with their chunks.  A workgroup
-// takes the children of EMIT_CELLS cells, one per lane: it adds up the tiles
-// before its own and scans the counts of its tile.  (One lane per cell, which
-// wrote its children in turn: 25 us a level at 128^3, 17 us now.)  If the
+// takes the children of EMIT_CELLS cells at a time, one per lane: it adds up the
+// tiles before its own, all of them once and then those from one set of cells to
+// the next, and scans the counts of its tile.  (One lane per cell, which wrote its
+// children in turn: 25 us a level at 128^3, 17 us now.  All tiles added up for each
+// set: 2.26 ms at a level of 4 million cells and 7.78 at 8 million, 0.62 and 1.21 now.)  If the
 // children do not fit in the node buffer, or their level in the room for one,
 // nothing is written but their number.
 #define EMIT_CELLS 32
@@ -576,23 +578,28 @@ __global__ __launch_bounds__(256) void k_emit_children(Node* nodes, int level, i
     __shared__ int nchild[EMIT_CELLS], at[EMIT_CELLS];
     const int start = flags[FI_LEVEL + level], next = flags[FI_LEVEL + level + 1];
     const int n = next - start, n_tiles = (n + 255) / 256;
-    for (int w = blockIdx.x; w * EMIT_CELLS < n || w == 0; w += gridDim.x) {
-        const int t = w * EMIT_CELLS / 256;
-        int before = 0, total = 0;
-        for (int q = threadIdx.x; q < n_tiles; q += 256) {
-            const int v = tile_sum[q];
-            total += v;
-            if (q < t) before += v;
-        }
-        int base, all;
+    if (blockIdx.x > 0 && blockIdx.x * EMIT_CELLS >= n) return;
+    int t = blockIdx.x * EMIT_CELLS / 256;
+    int before = 0, total = 0;  // this lane's share of the tiles before t, and of all
+    for (int q = threadIdx.x; q < n_tiles; q += 256) {
+        const int v = tile_sum[q];
+        total += v;
+        if (q < t) before += v;
+    }
+    int base, all;
+    wg_scan(total, wsum, all);
+    const bool fits = all <= cap - next && all <= level_cap;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        flags[FI_LEVEL + level + 2] = next + (fits ? all : 0);
+        if (!fits) flags[FI_LEVELFULL] = all;
+    }
+    if (!fits) return;
+    for (int w = blockIdx.x; w * EMIT_CELLS < n; w += gridDim.x) {
+        // (only the tiles passed over since the last cells are added)
+        const int t1 = w * EMIT_CELLS / 256;
+        for (int q = t + threadIdx.x; q < t1; q += 256) before += tile_sum[q];
+        t = t1;
         wg_scan(before, wsum, base);
-        wg_scan(total, wsum, all);
-        const bool fits = all <= cap - next && all <= level_cap;
-        if (w == 0 && threadIdx.x == 0) {
-            flags[FI_LEVEL + level + 2] = next + (fits ? all : 0);
-            if (!fits) flags[FI_LEVELFULL] = all;
-        }
-        if (!fits) return;
         const int k = t * 256 + threadIdx.x, first = w * EMIT_CELLS;
         const int nc = k < n ? nodes[start + k].n_child : 0;
         const int out = next + base + wg_scan(nc, wsum, all);

@@ -36,11 +36,12 @@ def test_small_workspace_holds(n_side, least):
     assert high[1] < 1.1 * least
 
 
-@pytest.mark.parametrize("n_side", [9, 27])
+@pytest.mark.parametrize("n_side", [9, 27, 64])
 def test_levels_of_more_cells_than_expected(n_side):
     """Smoothing lengths far below the spacing: in the FP32 modes every particle
     gets a cell of its own, where up to 64 would share one.  The first build borrows
-    its room, the second has lists of one entry a leaf."""
+    its room, the second has lists of one entry a leaf.  Beyond 65536 cells a
+    workgroup writes the children of several sets of cells."""
     log("case one particle a leaf, %d^3" % n_side)
     d = gen.lattice(n_side, vsigma=0.1, seed=72)
     n = d["x"].size
@@ -64,7 +65,8 @@ def test_levels_of_more_cells_than_expected(n_side):
     t["H"].copy_(H[t["id"]])
     sim.run()
     g = S.to_host(t)
-    o = oracle_run(d)
-    assert np.max(np.abs(g["rho"] - o["rho"]) / o["rho"]) < 1e-5
-    assert np.max(np.abs(g["H"] - o["H"]) / o["H"]) < 1e-5
     sim.close()
+    if n < 20000:
+        o = oracle_run(d)
+        assert np.max(np.abs(g["rho"] - o["rho"]) / o["rho"]) < 1e-5
+        assert np.max(np.abs(g["H"] - o["H"]) / o["H"]) < 1e-5
