@@ -11,9 +11,11 @@ capture of the density, ghost and force stages, and how many steps the
 cells and lists are kept (the list skin).  A second stage sweeps, around
 the fastest of those, the kernel axes: the occupancy target (waves per SIMD)
 the density and the force kernels are compiled for, and the neighbour-cell
-entries they stage per batch (the packed kernels have one instantiation of
-the last two: they make no difference there).  Every candidate starts from the same saved state, so each is timed
-on identical work; the particle tensors are restored afterwards.  Steps are
+entries they stage per batch.  Candidates that launch the same kernels (see
+launched()) are timed once and share the time, so that the choice among them
+is the default and not the one that noise favoured.  Every candidate starts
+from the same saved state, so each is timed on identical work; the particle
+tensors are restored afterwards.  Steps are
 averaged (not the median) so that the occasional rebuild of a candidate
 that keeps its lists is paid for.
 
@@ -91,8 +93,23 @@ def kernel_candidates(best):
     return out
 
 
+WIDE_ALL = 2048  # leaves up to which several waves share every leaf (SPH_WIDE_ALL of the library)
+
+
+def launched(cfg, n_leaves):
+    """`cfg` with kernel axes that select no kernel of their own at the value
+    whose kernel runs: the density kernel of one wave a leaf (cell lists, box
+    pruning, more than WIDE_ALL leaves) has forms for 4, 5 (the default) and 6
+    waves per SIMD, 8 runs that of 6; the gather force and the entries per batch
+    have one form."""
+    c = dict(cfg, waves_density=0, waves_force=0, batch=0)
+    if c.get("lists", "cell") == "cell" and c.get("prune", "box") == "box" and n_leaves > WIDE_ALL:
+        c["waves_density"] = {5: 0, 8: 6}.get(cfg.get("waves_density", 0), cfg.get("waves_density", 0))
+    return c
+
+
 def _time_config(boxes, t, state, cfg, precision, dt, steps, warmup):
-    """Mean ms per step.  A candidate that keeps its cells and lists for
+    """(Mean ms per step, leaves).  A candidate that keeps its cells and lists for
     many steps may rebuild rarely or never inside the few timed steps, so
     its builds are amortised: the timed steps without their builds, plus the
     mean build time over the interval between builds (seen in the timed
@@ -118,7 +135,7 @@ def _time_config(boxes, t, state, cfg, precision, dt, steps, warmup):
             per.append(sim.stats())
         torch.cuda.synchronize()
         wall_ms = (time.perf_counter() - t0) * 1e3
-        return amortised_ms(wall_ms, per, nb, cold_build_ms, cfg.get("rebuild_steps", 0))
+        return amortised_ms(wall_ms, per, nb, cold_build_ms, cfg.get("rebuild_steps", 0)), per[-1]["n_leaves"]
     finally:
         sim.close()
 
@@ -165,25 +182,40 @@ def autotune(boxes, t, precision, dt, steps=8, warmup=1, cands=None, cache=DEFAU
 
     def run(cfgs):
         for cfg in cfgs:
-            ms = _time_config(boxes, t, state, cfg, precision, dt, steps, warmup)
+            ms, leaves = _time_config(boxes, t, state, cfg, precision, dt, steps, warmup)
             table.append((cfg, ms))
+            n_leaves.append(leaves)
             if log:
                 log("autotune %s: %.2f ms/step" % (cfg, ms))
 
+    n_leaves = []  # of the first stage's rows
     try:
         run(cands or candidates())
         n_first = len(table)
         if kernel_axes and precision != "fp64":
-            stage1 = min(table, key=lambda r: r[1])[0]
-            run(kernel_candidates(stage1))
+            k = min(range(n_first), key=lambda r: table[r][1])
+            (stage1, ms1), leaves = table[k], n_leaves[k]
+            timed = [(launched(stage1, leaves), ms1)]
+
+            def run_new(cfg):
+                """Time cfg unless its kernels have been timed."""
+                k = launched(cfg, leaves)
+                for c, ms in timed:
+                    if c == k:
+                        table.append((cfg, ms))
+                        return
+                run([cfg])
+                timed.append((k, table[-1][1]))
+
             # the best value of each kernel axis together
             best_of = {}
-            for cfg, ms in table[-len(kernel_candidates(stage1)):]:
+            for cfg in kernel_candidates(stage1):
+                run_new(cfg)
+                ms = table[-1][1]
                 for ax in ("waves_density", "waves_force", "batch"):
-                    if cfg[ax] and (ax not in best_of or ms < best_of[ax][1]):
+                    if launched(cfg, leaves)[ax] and (ax not in best_of or ms < best_of[ax][1]):
                         best_of[ax] = (cfg[ax], ms)
-            combo = dict(stage1, **{ax: v for ax, (v, _) in best_of.items()})
-            run([combo])
+            run_new(dict(stage1, **{ax: v for ax, (v, _) in best_of.items()}))
     finally:
         for k in t:
             t[k].copy_(state[k])

@@ -2076,8 +2076,6 @@ static std::vector<uint8_t> graph_key(sph_ctx* c, const double* u, const double*
     key_put(k, c->prm.lists);
     key_put(k, c->prm.tile);
     key_put(k, c->prm.waves_density);
-    key_put(k, c->prm.waves_force);
-    key_put(k, c->prm.batch);
     return k;
 }
 
