@@ -316,7 +316,8 @@ __device__ __forceinline__ void fb_layer(const float (*W)[LSTR], const f32x4 x[4
 __global__ __launch_bounds__(256) void k_mlp_fb(TrainArgs a)
 {
     __shared__ __align__(16) float W1[NIN][LSTR], W2[NH][LSTR], W3[NH][LSTR];
-    __shared__ float bb[3][NH], w4[NH], xmu[NIN], rxsd[NIN];
+    __shared__ __align__(16) float bb[3][NH];  // (read four at a time)
+    __shared__ float w4[NH], xmu[NIN], rxsd[NIN];
     __shared__ __align__(16) float xh[MB][XSTR];
     __shared__ __align__(16) float hA[3][MB][LSTR];   // activations h1, h2, h3
     __shared__ __align__(16) float dA[3][MB][LSTR];   // dL/dz1, dL/dz2, dL/dz3
