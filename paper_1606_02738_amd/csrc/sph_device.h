@@ -292,8 +292,6 @@ struct DensArgs {
     const int* l_count;
     const double* l_origin;
     const double* l_hlist;
-    const double* l_lo;   // leaf boxes at the build (3 per leaf)
-    const double* l_hi;
     const int* l_dom;
     const int* l_off;
     const ListEntry* list;

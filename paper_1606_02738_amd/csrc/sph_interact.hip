@@ -558,8 +558,6 @@ struct ForceArgs {
     const int* l_count;
     const double* l_origin;
     const double* l_hlist;
-    const double* l_lo;
-    const double* l_hi;
     const int* l_dom;
     const int* l_off;
     const ListEntry* list;
@@ -1447,8 +1445,6 @@ static void dens_args(sph_ctx* c, const int* gate, bool graph, DensArgs& a, int&
     a.l_count = (const int*)c->l_count.p;
     a.l_origin = (const double*)c->l_origin.p;
     a.l_hlist = (const double*)c->l_hlist.p;
-    a.l_lo = (const double*)c->l_lo.p;
-    a.l_hi = (const double*)c->l_hi.p;
     a.l_dom = (const int*)c->l_dom.p;
     a.l_off = (const int*)c->l_off.p;
     a.list = (const ListEntry*)c->list.p;
@@ -1866,8 +1862,6 @@ static void force_args(sph_ctx* c, const int* gate, bool graph, ForceArgs& a, in
     a.l_count = (const int*)c->l_count.p;
     a.l_origin = (const double*)c->l_origin.p;
     a.l_hlist = (const double*)c->l_hlist.p;
-    a.l_lo = (const double*)c->l_lo.p;
-    a.l_hi = (const double*)c->l_hi.p;
     a.l_dom = (const int*)c->l_dom.p;
     a.l_off = (const int*)c->l_off.p;
     a.list = (const ListEntry*)c->list.p;

@@ -6,7 +6,6 @@
 
 #include "sph.h"
 
-#define SPH_WAVE 64
 #define SPH_MAX_LEAF 64          // particles per leaf cell (one wave of lanes)
 #define SPH_NDIR 13              // axis directions between neighbouring cells
 #define SPH_MAX_DEPTH 16         // octree levels below the top grid
@@ -164,27 +163,6 @@ enum { CNT_STALE_MOVED = CNT_N + XQ_N * XQ_STRIDE, CNT_STALE_GROWN,
 enum { PART_N = 256, PART_STRIDE = 16, CNT_PART = (CNT_ALLOC + 15) / 16 * 16, CNT_TOTAL = CNT_PART + PART_N * PART_STRIDE };
 enum { PART_UNCONV = 0, PART_NDENS, PART_DEVAL, PART_NFORCE, PART_NDENS_F, PART_USED };
 
-// Leaf arrays (device SoA).
-struct LeafArrays {
-    int* begin;
-    int* count;
-    double* origin;   // 3 per leaf: reference point of the cell-relative coordinates
-    double* lo;       // 3 per leaf
-    double* hi;       // 3 per leaf
-    double* hlist;    // radius the neighbour lists were built for
-    int* dom;
-    int* list_off;    // n_leaves + 1
-    int* active;      // leaf has unconverged particles
-    int* sorted;      // 1 if the per-direction sort is valid
-};
-
-// Kernel-side view of the per-box constants and physics parameters.
-struct PhysParams {
-    double gamma;
-    double C_fac;     // (kernel_gamma * eta)^3
-    double h_tol;
-};
-
 // Workgroups are dealt to the 8 XCDs of the chip round-robin (workgroup b
 // runs on XCD b mod 8), and each XCD has its own L2.  The logical block
 // index below gives every XCD one contiguous range of blocks, so
@@ -199,12 +177,3 @@ __device__ inline int xcd_block(int b, int G)
 template <typename T> struct vec4;
 template <> struct vec4<float> { typedef float4 type; };
 template <> struct vec4<double> { typedef double4 type; };
-
-__device__ inline uint64_t double_as_u64(double v) { return (uint64_t)__double_as_longlong(v); }
-__device__ inline double u64_as_double(uint64_t v) { return __longlong_as_double((long long)v); }
-
-// Positive doubles order like their bit patterns: atomic max via integer max.
-__device__ inline void atomic_max_pos_double(double* addr, double v)
-{
-    atomicMax((unsigned long long*)addr, (unsigned long long)double_as_u64(v));
-}

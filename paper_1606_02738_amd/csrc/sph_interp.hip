@@ -33,7 +33,6 @@ struct InterpArgs {
     int n_dom;
     const DomainInfo* di;
     const Node* nodes;
-    const WNode* wn;
     const double *x, *y, *z, *m, *rho, *H, *Q;
     double margin;
     double* out;
@@ -462,7 +461,6 @@ extern "C" sph_status sph_interpolate(sph_ctx* c, const double* Q, const double*
     a.n_dom = c->prm.n_domains;
     a.di = (const DomainInfo*)c->dom_d.p;
     a.nodes = (const Node*)c->nodes.p;
-    a.wn = (const WNode*)c->wnodes.p;
     a.x = c->P.x;
     a.y = c->P.y;
     a.z = c->P.z;
