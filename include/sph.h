@@ -89,7 +89,10 @@ typedef struct {
                             workgroups drain device task queues, one per XCD
                             over a contiguous Morton range of cells, and help
                             the other XCDs' queues once their own is empty
-                            (density sweeps run as a grid in both modes) */
+                            (density sweeps run as a grid in both modes, and so
+                            does the gather force of boxes of up to 2048 cells,
+                            where several waves share every cell, and of the cells
+                            with the longest lists of larger ones) */
     int n_domains;       /* number of independent periodic boxes (>= 1) */
     int persistent_wgs;  /* resident workgroups for the persistent mode (0: auto) */
     int use_graph;       /* 1: density sweeps, ghost and force run as one captured
@@ -132,7 +135,7 @@ typedef struct {
                             at most 512 / 256) */
     int waves_density;   /* cell lists, FP32 modes: occupancy target (waves per SIMD) the
                             packed density kernel is compiled for, 4, 5, 6 or 8 (0: 5; 8
-                            runs the kernel of 6) */
+                            runs the kernel of 6), in boxes of more than 2048 cells */
     int waves_force;     /* the same for the gather force kernel, 4, 5, 6 or 8 (0: 4; its
                             LDS holds 4 waves, which every choice runs) */
     int batch;           /* cell lists, FP32 modes: neighbour-cell entries staged per batch
