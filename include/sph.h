@@ -214,7 +214,8 @@ typedef struct {
                                    list radius */
     int64_t workspace_bytes;    /* usable bytes of the workspace */
     int64_t workspace_in_use;   /* bytes the context's buffers hold now */
-    int64_t workspace_high;     /* most bytes held at once */
+    int64_t workspace_high;     /* most bytes held at once (without a block that a build borrows
+                                   where there is room and does without where not) */
     int64_t workspace_needed;   /* after SPH_ERR_WORKSPACE: bytes that call needed (0: none failed) */
     int64_t n_force_total;      /* sum of n_force over every force stage since sph_create */
     int64_t n_dens_total;       /* sum of n_dens (force stage's count) since sph_create */
